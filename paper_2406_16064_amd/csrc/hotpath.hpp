@@ -1571,16 +1571,22 @@ __device__ inline void control_step(DevCtl& C, const double* __restrict__ replay
   C.h_att = hn;
 }
 
-// End of an error pass in one workgroup: the largest error norm emax (and,
-// for relaxations, the largest |k_7|^2 kmax) of its cells go into the
-// instance's running maxima; the last of the instance's bpi workgroups to
-// arrive takes the step decision.  The arrival uses the maxima's returned
+// End of an error pass in one workgroup (number lb of the instance's bpi): the
+// largest error norm emax (and, for relaxations, the largest |k_7|^2 kmax) of
+// its cells go into running maxima; the last of the instance's workgroups to
+// arrive takes the step decision.  Each arrival uses the maxima's returned
 // values (their top bits, always 0 for non-negative doubles), so it is issued
 // only once the maxima are complete; the atomics are performed where every
 // XCD sees them, so no fence (an L2 write-back on this part) is needed.
+// Atomics on one line are performed one after the other (about 18 ns a
+// workgroup: at 1024 workgroups they took longer than the pass, 34 us against
+// 14.5 us for the stage kernel on a 128x128x8 mesh), so the workgroups arrive
+// at kErrSlots slots on lines of their own, and the last one of each slot
+// carries the slot's maxima to the instance; up to 2 kErrSlots workgroups the
+// second level costs as much as it saves and they arrive at the instance.
 // red: the workgroup's LDS scratch, at least [2][waves].
-__device__ __forceinline__ void error_pass_end(double emax, double kmax, DevCtl* ctl, int b, int bpi,
-                                               const double* replay, double (*red)[512 / 64]) {
+__device__ __forceinline__ void error_pass_end(double emax, double kmax, DevCtl* ctl, ErrSlot* eslot, int b, int lb,
+                                               int bpi, const double* replay, double (*red)[512 / 64]) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const bool relax = ldu(&ctl[b].stop_dmdt) > 0.0;
   const double w = wave_max(emax);
@@ -1593,15 +1599,30 @@ __device__ __forceinline__ void error_pass_end(double emax, double kmax, DevCtl*
   if (threadIdx.x == 0) {
     double v = red[0][0];
     for (int j = 1; j < (int)(blockDim.x >> 6); ++j) v = fmax(v, red[0][j]);
-    const unsigned long long prev = atomicMax(&ctl[b].err_bits, (unsigned long long)__double_as_longlong(v));
-    unsigned long long prevk = 0ull;
+    unsigned long long ebits = (unsigned long long)__double_as_longlong(v), kbits = 0ull;
     if (relax) {
       double vk = red[1][0];
       for (int j = 1; j < (int)(blockDim.x >> 6); ++j) vk = fmax(vk, red[1][j]);
-      prevk = atomicMax(&ctl[b].dmdt_bits, (unsigned long long)__double_as_longlong(sqrt(vk)));
+      kbits = (unsigned long long)__double_as_longlong(sqrt(vk));
     }
+    int arrivals = bpi;  // at the instance
+    if (bpi > 2 * kErrSlots) {
+      ErrSlot* const q = eslot + (size_t)b * kErrSlots + lb % kErrSlots;
+      const unsigned long long prev = atomicMax(&q->err_bits, ebits);
+      const unsigned long long prevk = relax ? atomicMax(&q->dmdt_bits, kbits) : 0ull;
+      const int inc = 1 + (int)(prev >> 63) + (int)(prevk >> 63);
+      const int members = (bpi - lb % kErrSlots + kErrSlots - 1) / kErrSlots;
+      if (atomicAdd(&q->arrive, inc) != members - 1) return;
+      // the slot is complete: its maxima go on, and it is zero for the next pass
+      ebits = atomicExch(&q->err_bits, 0ull);
+      if (relax) kbits = atomicExch(&q->dmdt_bits, 0ull);
+      q->arrive = 0;
+      arrivals = kErrSlots;
+    }
+    const unsigned long long prev = atomicMax(&ctl[b].err_bits, ebits);
+    const unsigned long long prevk = relax ? atomicMax(&ctl[b].dmdt_bits, kbits) : 0ull;
     const int inc = 1 + (int)(prev >> 63) + (int)(prevk >> 63);
-    if (atomicAdd(&ctl[b].arrive, inc) == bpi - 1) {
+    if (atomicAdd(&ctl[b].arrive, inc) == arrivals - 1) {
       ctl[b].arrive = 0;
       ctl[b].err_bits = atomicOr(&ctl[b].err_bits, 0ull);  // the complete maxima
       if (relax) ctl[b].dmdt_bits = atomicOr(&ctl[b].dmdt_bits, 0ull);
@@ -2043,7 +2064,7 @@ __global__ void __launch_bounds__(512) k_inv_x(Launch<T> L) {
     }
   }
   if constexpr (MODE == MODE_ERROR) {
-    error_pass_end(emax, kmax, ctl, b, tiles * g.nz, epi.replay, red);
+    error_pass_end(emax, kmax, ctl, epi.eslot, b, (int)(bid0 % (tiles * g.nz)), tiles * g.nz, epi.replay, red);
   } else if constexpr (energy) {
     energy_pass_end(esum, epi.partial, b, tiles * g.nz, (int)(bid0 % (tiles * g.nz)), red);
   }

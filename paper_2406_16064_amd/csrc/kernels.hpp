@@ -51,6 +51,7 @@ template <typename T> struct Epi {
   int project;            // STAGE: store the next stage input projected onto |m| = 1
   double* partial;        // energy partials [batch][blocks_per_inst][5]
   DevCtl* ctl;            // per-instance controller (skip done instances; h_att; err)
+  ErrSlot* eslot;         // MODE_ERROR: arrival slots [batch][kErrSlots]
   const double* replay;   // MODE_ERROR: replayed step sizes (controller in the last workgroup)
   long long inst_stride;  // elements per instance of m-like arrays (3N)
   // step begin

@@ -168,4 +168,14 @@ struct DevCtl {
   int pad;
 };
 
+// Arrival slots of the error pass, kErrSlots per instance, each on a cache line
+// of its own (error_pass_end): the slot's running maxima (bits, as err_bits and
+// dmdt_bits above) and its workgroups so far.  All zero between launches.
+constexpr int kErrSlots = 32;
+struct alignas(128) ErrSlot {
+  unsigned long long err_bits, dmdt_bits;
+  int arrive;
+  int pad[27];
+};
+
 }  // namespace mmx

@@ -269,6 +269,7 @@ struct Engine {
   hipStream_t cap = nullptr;  // capture stream (default priority)
   DevParams* prm = nullptr;
   DevCtl* ctl = nullptr;
+  ErrSlot* eslot = nullptr;  // arrival slots of the error pass, kErrSlots per instance, zero between launches
   double* partial = nullptr;
   double* e5 = nullptr;
   double* replay = nullptr;
@@ -660,7 +661,7 @@ void free_engine(Engine& E) {
   if (E.gexec) (void)hipGraphExecDestroy(E.gexec);
   E.gexec = nullptr;
   for (Group& G : E.groups) free_group(G);
-  void* bufs[] = {E.prm, E.ctl, E.partial, E.e5, E.replay, E.dhot, E.depi, E.nebH, E.nebB, E.nebS, E.nebP};
+  void* bufs[] = {E.prm, E.ctl, E.eslot, E.partial, E.e5, E.replay, E.dhot, E.depi, E.nebH, E.nebB, E.nebS, E.nebP};
   for (void* b : bufs)
     if (b) (void)hipFree(b);
   if (E.hctl) (void)hipHostFree(E.hctl);
@@ -776,13 +777,17 @@ mm_status engine_reserve(Engine& E, const std::vector<int>& per_group) {
   if (total > E.inst_cap) {
     if (E.prm) (void)hipFree(E.prm);
     if (E.ctl) (void)hipFree(E.ctl);
+    if (E.eslot) (void)hipFree(E.eslot);
     if (E.e5) (void)hipFree(E.e5);
     if (E.hctl) (void)hipHostFree(E.hctl);
     if (E.hctl2) (void)hipHostFree(E.hctl2);
     if (E.he5) (void)hipHostFree(E.he5);
-    E.prm = nullptr; E.ctl = nullptr; E.e5 = nullptr; E.hctl = nullptr; E.hctl2 = nullptr; E.he5 = nullptr;
+    E.prm = nullptr; E.ctl = nullptr; E.eslot = nullptr; E.e5 = nullptr; E.hctl = nullptr; E.hctl2 = nullptr; E.he5 = nullptr;
     MMCHK(dev_alloc((void**)&E.prm, sizeof(DevParams) * total));
     MMCHK(dev_alloc((void**)&E.ctl, sizeof(DevCtl) * total));
+    MMCHK(dev_alloc((void**)&E.eslot, sizeof(ErrSlot) * kErrSlots * total));
+    const std::vector<char> zero(sizeof(ErrSlot) * kErrSlots * total, 0);
+    HIPCHK(hipMemcpy(E.eslot, zero.data(), zero.size(), hipMemcpyHostToDevice));
     MMCHK(dev_alloc((void**)&E.e5, sizeof(double) * 5 * total));
     HIPCHK(hipHostMalloc((void**)&E.hctl, sizeof(DevCtl) * total));
     HIPCHK(hipHostMalloc((void**)&E.hctl2, sizeof(DevCtl) * total));
@@ -1102,6 +1107,7 @@ mm_status upload_step_epis(Engine& E, const std::vector<T*>& m, const std::vecto
         for (int j = 0; j < st - 1; ++j) e.kprev[j] = stage_buf<T>(G, 2 + j);
         e.nk = st;
         e.replay = E.replay;
+        e.eslot = E.eslot + (size_t)inst0[i] * kErrSlots;
         for (int j = 0; j < st; ++j) e.coef[j] = st < 7 ? kDP.a[st + 1][j] : kDP.e[j];
       } else {  // step begin
         e.bm = m[i];

@@ -430,7 +430,8 @@ __global__ void __launch_bounds__(512) k_pot_x(HotPlan<T> hp, const Epi<T>* __re
         }
     }
   }
-  if constexpr (MODE == MODE_ERROR) error_pass_end(emax, kmax, ctl, b, tiles * g.nz, epi.replay, red);
+  if constexpr (MODE == MODE_ERROR)
+    error_pass_end(emax, kmax, ctl, epi.eslot, b, (int)(bidx % (tiles * g.nz)), tiles * g.nz, epi.replay, red);
   if constexpr (MODE == MODE_ENERGY) energy_pass_end(esum, epi.partial, b, tiles * g.nz, (int)(bidx % (tiles * g.nz)), red);
 }
 
