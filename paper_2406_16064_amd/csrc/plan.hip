@@ -269,7 +269,10 @@ struct Engine {
   hipStream_t cap = nullptr;  // capture stream (default priority)
   DevParams* prm = nullptr;
   DevCtl* ctl = nullptr;
-  ErrSlot* eslot = nullptr;  // arrival slots of the error pass, kErrSlots per instance, zero between launches
+  // arrival slots of the error pass, kErrSlots per instance, zero between
+  // launches; behind ctl in its allocation, cleared before the first adaptive run
+  ErrSlot* eslot = nullptr;
+  bool eslot_clear = false;
   double* partial = nullptr;
   double* e5 = nullptr;
   double* replay = nullptr;
@@ -407,8 +410,10 @@ DevParams dev_params(const mm_params& r, const Group& G, bool general) {
 
 // Launch shapes of one group.  Each workgroup keeps its LDS within 80 KiB (two
 // per CU), the per-thread butterfly budget of the transforms is respected, and
-// tiles shrink until a pass has about 4 workgroups per CU (small meshes) or
-// reach their coalescing-friendly maximum (large meshes).
+// tiles shrink until a pass has the workgroups it needs (small meshes) or
+// reach their coalescing-friendly maximum (large meshes).  The lines between
+// the shapes were measured in evaluation order (times in us, FP32 unless
+// stated); mm_plan_autotune measures them for one mesh.
 // launch_rows: rows (nz ny per instance) of every group of a batch launch, 0
 // for one instance of this group alone: the workgroup count aimed at counts
 // the whole launch, so that the meshes of a large batch take rows per
@@ -427,30 +432,64 @@ mm_status choose_tuning(Group& G, mm_precision prec, size_t csz, long long launc
   const size_t xtab = (size_t)(2 * g.Lx + 1) * csz;  // twiddle + post tables in LDS
   const size_t ytab = (size_t)g.Py * csz;
   const size_t ktab2 = y2d_tensor_in_lds(g) ? (size_t)4 * g.Ky * (csz / 2) : 0;  // per kx column of the fused 2-D y pass
-  {  // forward x: rows of one component
-    const long long rows = 3LL * (launch_rows > 0 ? launch_rows : (long long)g.nz * g.ny);
-    int ty = 16;
-    while (ty > 1 && ((size_t)ty * rowb + xtab > budget || ty * tpx > 512 || rows / ty < want)) ty /= 2;
+  const long long all_rows = launch_rows > 0 ? launch_rows : (long long)g.nz * g.ny;
+  {  // forward x: rows of one component.  4 rows a workgroup (up to 16 in batch
+     // launches with workgroups enough): the table copies are shared and a kx
+     // block takes whole lines; 1 row only where 4 would leave CUs idle
+     // (512x512x1 16.6 -> 12.2, 1024x1024x1 22.3 -> 19.3, 256x256x1 9.2 -> 8.9).
+     // Long rows in many workgroups run best on 256 threads (512x512x16: 38.7
+     // against 42.5 with 8 rows on 512, 40.8 with 4 on 512).
+    const long long rows = 3 * all_rows;
+    int ty = launch_rows > 0 ? 16 : 4;
+    while (ty > 1 && ((size_t)ty * rowb + xtab > budget || ty * tpx > 512 || rows / ty < (ty > 4 ? want : 192))) ty /= 2;
+    // short rows: more of them, to 512 entries a workgroup (30x1000x20: 22 with 16
+    // rows, 29 with 4)
+    while (ty >= 4 && ty < 16 && ty * g.Lx < 512 && rows / (2 * ty) >= want) ty *= 2;
     while (ty > g.ny) ty /= 2;  // a power of two (the kernels split rows by shifts)
     if ((size_t)ty * rowb + xtab > 160 * 1024 || ty * tpx > 512) return fail(MM_E_ARG, "mesh too long along x");
     t.ty_f = ty;
-    t.nt_f = std::min(512, std::max(64, pow2ceil(std::max(ty * tpx, ty * g.Lx / 4))));
+    const int cap = ty <= 4 && rows / ty > want ? 256 : 512;
+    t.nt_f = std::min(512, std::max(64, pow2ceil(std::max(ty * tpx, std::min(cap, ty * g.Lx / 4)))));
     t.tpc_f = t.nt_f / ty;
   }
-  {  // inverse x + epilogue: rows of all 3 components (3 columns per row)
-    const long long rows = launch_rows > 0 ? launch_rows : (long long)g.nz * g.ny;
+  {  // inverse x + epilogue: rows of all 3 components (3 columns per row).  A
+     // 2-D film's rows lie 8 or 16 bytes apart in its x spectrum, so that a
+     // second row halves the lines touched: worth it down to one workgroup a CU
+     // (1024x1024x1 33.1 -> 28.2, 512x512x1 17.6 -> 12.8), unless the film's
+     // single rows all run at once (238x678x1: 14.4 against 19.4 in twos).
+    const long long rows = all_rows;
     int ty = 16;
-    while (ty > 1 && ((size_t)3 * ty * rowb + xtab > budget || 3 * ty * tpx > 512 || rows / ty < want)) ty /= 2;
+    const bool at_once = rows * ((g.nx + 63) / 64) <= 12 * 256;  // one cell a thread, three waves a SIMD
+    const long long aim = g.nz == 1 && launch_rows == 0 && !at_once ? 256 : want;
+    while (ty > 1 && ((size_t)3 * ty * rowb + xtab > budget || 3 * ty * tpx > 512 || rows / ty < aim)) ty /= 2;
     while (ty > g.ny) ty /= 2;  // a power of two (the kernels split rows by shifts)
     if ((size_t)3 * ty * rowb + xtab > 160 * 1024 || 3 * ty * tpx > 512)
       return fail(MM_E_ARG, "mesh too long along x");
     t.ty_x = ty;
-    t.nt_i = std::min(512, std::max(64, pow2ceil(std::max(3 * ty * tpx, ty * g.nx))));
+    // Threads.  One cell a thread is the shortest chain but takes 145-166
+    // registers (three waves a SIMD, and one workgroup of 512 threads a CU):
+    // kept while the launch's waves all run at once, 12 a CU.  Beyond that two
+    // or four cells a thread (122-126 registers) in workgroups of 256 threads,
+    // 512 where a tile has more than 1024 cells (256x256x8 stage kernel 41.2 ->
+    // 22.6, 512x512x4 38.4 -> 36.1, 32 films of 128x128 29 -> 14; 512x512x16
+    // FP64 346 -> 288).  With at most two workgroups a CU the transform's
+    // threads bound the chain instead: 8 entries a thread up to 512 threads.
+    const long long cells = (long long)ty * g.nx;
+    const long long wgs = rows / ty;
+    int nt;
+    if (wgs * ((cells + 63) / 64) <= 12 * 256) nt = pow2ceil((int)std::min<long long>(cells, 512));
+    else if (wgs <= 512) nt = pow2ceil((int)std::min<long long>(std::max<long long>(3LL * ty * g.Lx / 8, cells / 2), 512));
+    else if (2 * ((size_t)3 * ty * rowb + xtab) > 160 * 1024) nt = 512;
+    else nt = cells <= 1024 ? pow2ceil((int)std::min<long long>(std::max<long long>(cells / 2, 64), 256)) : 512;
+    t.nt_i = std::min(512, std::max(64, pow2ceil(std::max(3 * ty * tpx, nt))));
     t.tpc_x = t.nt_i / (3 * ty);
   }
   const int tmin = tpc_for(g.Py, true);
   if (g.nz == 1) {
-    const int tpc = std::max(tmin, std::min(2 * tmin, 64));
+    // 8 entries a thread where three columns fit a workgroup so: Py = 1024 and
+    // below (512x512x1 18.4 -> 16.3, 1024x512x1 FP64 61.6 -> 49.5)
+    int tpc = std::max(tmin, std::min(2 * tmin, 64));
+    if (2 * g.ny == g.Py && g.Py <= 1024 && (g.Py & (g.Py - 1)) == 0) tpc = std::max(tpc, g.Py / 8);
     const size_t colb = 3 * (size_t)col_stride(g.Py) * csz;
     int cb = 8;
     // packed: the tile of slot 0 also holds the tensor rows of kx = Lx
@@ -462,11 +501,22 @@ mm_status choose_tuning(Group& G, mm_precision prec, size_t csz, long long launc
     t.tpc_y2 = tpc;
     t.nt_y = 3 * cb * tpc;
   } else {
-    const int tpc = std::max(tmin, std::min(2 * tmin, 64));
+    // one kx block (4 columns) a workgroup: more columns leave too few
+    // workgroups a CU to overlap loads with transforms (512x512x16: forward
+    // 57 and inverse 68 with 4 columns, 85 and 75 with 8); FP64 columns of 512
+    // points and more with a compiled transform in twos on twice the threads (FP64 123 and 130 with 4,
+    // 118 and 112 with 2); short columns as many as fill a wave where the launch
+    // has the columns (700x16x12: forward 11.3 with 16, 14.5 with 4)
+    int tpc = std::max(tmin, std::min(2 * tmin, 64));
     const size_t colb = (size_t)col_stride(g.Py) * csz;
-    const long long rows = 3LL * g.nz * g.Xp;
-    int cb = 16;  // whole kx blocks of the x-pass buffer
-    while (cb > kSxB && (cb * colb > budget || cb * tpc > 512 || rows / cb < want)) cb -= kSxB;
+    int cb = kSxB;
+    const bool compiled = 2 * g.ny == g.Py && (g.Py & (g.Py - 1)) == 0;
+    if (prec == MM_F64 && compiled && g.Py >= 512 && 2 * tpc <= 256) {
+      cb = 2;
+      tpc *= 2;
+    }
+    while (cb < 16 && cb * tpc < 64 && 3LL * g.nz * g.Xp / (2 * cb) >= want) cb *= 2;
+    while (cb > 1 && (cb * colb > budget || cb * tpc > 512)) cb /= 2;
     if (cb * colb > 160 * 1024 || cb * tpc > 512) return fail(MM_E_ARG, "mesh too long along y");
     t.cb_y = cb;
     t.tpc_y = tpc;
@@ -661,7 +711,7 @@ void free_engine(Engine& E) {
   if (E.gexec) (void)hipGraphExecDestroy(E.gexec);
   E.gexec = nullptr;
   for (Group& G : E.groups) free_group(G);
-  void* bufs[] = {E.prm, E.ctl, E.eslot, E.partial, E.e5, E.replay, E.dhot, E.depi, E.nebH, E.nebB, E.nebS, E.nebP};
+  void* bufs[] = {E.prm, E.ctl, E.partial, E.e5, E.replay, E.dhot, E.depi, E.nebH, E.nebB, E.nebS, E.nebP};
   for (void* b : bufs)
     if (b) (void)hipFree(b);
   if (E.hctl) (void)hipHostFree(E.hctl);
@@ -777,17 +827,16 @@ mm_status engine_reserve(Engine& E, const std::vector<int>& per_group) {
   if (total > E.inst_cap) {
     if (E.prm) (void)hipFree(E.prm);
     if (E.ctl) (void)hipFree(E.ctl);
-    if (E.eslot) (void)hipFree(E.eslot);
     if (E.e5) (void)hipFree(E.e5);
     if (E.hctl) (void)hipHostFree(E.hctl);
     if (E.hctl2) (void)hipHostFree(E.hctl2);
     if (E.he5) (void)hipHostFree(E.he5);
     E.prm = nullptr; E.ctl = nullptr; E.eslot = nullptr; E.e5 = nullptr; E.hctl = nullptr; E.hctl2 = nullptr; E.he5 = nullptr;
     MMCHK(dev_alloc((void**)&E.prm, sizeof(DevParams) * total));
-    MMCHK(dev_alloc((void**)&E.ctl, sizeof(DevCtl) * total));
-    MMCHK(dev_alloc((void**)&E.eslot, sizeof(ErrSlot) * kErrSlots * total));
-    const std::vector<char> zero(sizeof(ErrSlot) * kErrSlots * total, 0);
-    HIPCHK(hipMemcpy(E.eslot, zero.data(), zero.size(), hipMemcpyHostToDevice));
+    const size_t ctl_bytes = (sizeof(DevCtl) * total + 127) / 128 * 128;
+    MMCHK(dev_alloc((void**)&E.ctl, ctl_bytes + sizeof(ErrSlot) * kErrSlots * total));
+    E.eslot = (ErrSlot*)((char*)E.ctl + ctl_bytes);
+    E.eslot_clear = false;
     MMCHK(dev_alloc((void**)&E.e5, sizeof(double) * 5 * total));
     HIPCHK(hipHostMalloc((void**)&E.hctl, sizeof(DevCtl) * total));
     HIPCHK(hipHostMalloc((void**)&E.hctl2, sizeof(DevCtl) * total));
@@ -1493,6 +1542,10 @@ mm_status run_core(Engine& E, const std::vector<T*>& m, const std::vector<int>& 
     }
   }
   HIPCHK(hipMemcpyAsync(E.ctl, E.hctl, sizeof(DevCtl) * n_total, hipMemcpyHostToDevice, s));
+  if (!E.eslot_clear) {  // outside every capture: the run's graph is captured on another stream
+    HIPCHK(hipMemsetAsync(E.eslot, 0, sizeof(ErrSlot) * kErrSlots * E.inst_cap, s));
+    E.eslot_clear = true;
+  }
   MMCHK(upload_step_epis<T>(E, m, inst0, s));
   long long extra_rhs = 0;
   if (need_k1) {
