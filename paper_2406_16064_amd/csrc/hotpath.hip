@@ -23,6 +23,8 @@ extern template void inv_x_launch<double, false, false>(int, int, bool, const La
                                                        hipStream_t);
 extern template void inv_x_launch<double, false, true>(int, int, bool, const Launch<double>&, long long, int, size_t,
                                                        hipStream_t);
+extern template void yzy_launch<float>(int, int, const Launch<float>&, long long, int, size_t, hipStream_t);
+extern template void yzy_launch<double>(int, int, const Launch<double>&, long long, int, size_t, hipStream_t);
 
 // ---------------------------------------------------------------------------
 // Step begin: finish the previous accepted attempt (project y5, FSAL copy),
@@ -493,6 +495,27 @@ int y_key(const HotPlan<T>& h) {
   return L == 2 * h.g.ny && (L == 256 || L == 512 || L == 1024 || L == 2048) ? L : 0;
 }
 
+// Pz / 2 where a 3-D group takes the fused y and z passes (k_yzy), 0 where it
+// takes the separate ones.  Fused: nz = 2 to 4 (FP64 to 3), Py = 2 ny of 256, 512
+// or 1024, and the columns of a kx in 64 KB of LDS, so that two workgroups and
+// more share a CU.  The fused workgroup is one serial chain, so that larger
+// planes, which leave one a CU, and the general transform lose (FP32, y + z +
+// inverse y in us, separate -> fused: 256x256x2 13.9 -> 9.9, eight of them
+// 48.7 -> 35.3, eight 128x128x2 14.7 -> 10.1, eight 256x256x4 90 -> 79, 256x256x2
+// FP64 22.5 -> 16.5; but 512x512x4 57 -> 73, eight 128x128x8 49 -> 70, eight
+// 128x128x4 FP64 49 -> 55, eight 192x192x2 57 -> 107).
+template <typename T>
+int yzy_m(const Geo& g) {
+  if (g.nz < 2 || g.nz > (sizeof(T) == 8 ? 3 : 4) || g.Pz != 2 * g.nz) return 0;
+  if (g.Py != 2 * g.ny || (g.Py != 256 && g.Py != 512 && g.Py != 1024)) return 0;
+  return yzy_lds(g, sizeof(Cx<T>)) <= 64 * 1024 ? g.nz : 0;
+}
+template <typename T>
+int yzy_m(const HotPlan<T>& h) { return h.kt ? yzy_m<T>(h.g) : 0; }  // no tensor: the scalar-potential route
+
+template <typename T>
+bool eval_needs_sy(const Geo& g) { return g.nz > 1 && yzy_m<T>(g) == 0; }
+
 template <typename T>
 hipError_t launch_eval(const GroupSet<T>& gs, const Epi<T>* epis, int mode, bool demag, hipStream_t s,
                        hipEvent_t* ev, bool skip_fwd, bool fuse_next, unsigned pass_mask) {
@@ -548,32 +571,51 @@ hipError_t launch_eval(const GroupSet<T>& gs, const Epi<T>* epis, int mode, bool
     }
     if (on(1)) {  // y forward (2-D groups: fused forward / product / inverse)
       mark();
-      int keys[kMaxGroups], nkeys = 0;
+      // one launch per y length and z length of the fused 3-D groups; a 2-D
+      // group joins the fused launch of its length where its columns fit one
+      int key_of[kMaxGroups], keys[kMaxGroups], nkeys = 0;
       for (int i = 0; i < gs.n; ++i) {
-        const int k = y_key(gs.h[i]);
+        const HotPlan<T>& h = gs.h[i];
+        key_of[i] = 32 * y_key(h) + yzy_m<T>(h);
+        for (int j = 0; j < gs.n && h.g.nz == 1; ++j) {
+          const int m = yzy_m<T>(gs.h[j]), sl = y_key(h);
+          if (m == 0 || y_key(gs.h[j]) != sl || gs.h[j].batch == 0) continue;
+          if (3 * h.tu.cb_y2 * (sl / 8) <= 512) key_of[i] = 32 * sl + m;
+          break;
+        }
         bool seen = false;
-        for (int j = 0; j < nkeys; ++j) seen = seen || keys[j] == k;
-        if (!seen) keys[nkeys++] = k;
+        for (int j = 0; j < nkeys; ++j) seen = seen || keys[j] == key_of[i];
+        if (!seen) keys[nkeys++] = key_of[i];
       }
       for (int kk = 0; kk < nkeys; ++kk) {
+      const int m = keys[kk] % 32;
       bool use[kMaxGroups];
       LaunchBuilder<T> lb(gs, epis);
       int nt = 64;
       size_t lds = 0;
       for (int i = 0; i < gs.n; ++i) {
         const HotPlan<T>& h = gs.h[i];
-        use[i] = y_key(h) == keys[kk];
+        use[i] = key_of[i] == keys[kk];
         if (!use[i]) {
           lb.set(i, 0);
         } else if (h.g.nz == 1) {
           lb.set(i, y2d_blocks(h.g, h.tu, h.batch));
           lds = std::max(lds, ((size_t)3 * h.tu.cb_y2 * col_stride(h.g.Py) + h.g.Py) * csz +
                                   (y2d_tensor_in_lds(h.g) ? (size_t)4 * (h.tu.cb_y2 + y2d_packed(h.g)) * h.g.Ky * (csz / 2) : 0));
+        } else if (m > 0) {
+          lb.set(i, yzy_blocks(h.g, h.batch));
+          lds = std::max(lds, yzy_lds(h.g, csz));
         } else {
           lb.set(i, y3d_blocks(h.g, h.tu, h.batch));
           lds = std::max(lds, (size_t)h.tu.cb_y * col_stride(h.g.Py) * csz);
         }
-        if (use[i]) nt = std::max(nt, h.tu.nt_y);
+        if (!use[i]) continue;
+        const int cols = 3 * (h.g.nz == 1 ? h.tu.cb_y2 : h.g.nz);  // fused launches
+        nt = std::max(nt, m > 0 ? std::min(512, cols * (keys[kk] / 32 / 8)) : h.tu.nt_y);
+      }
+      if (m > 0) {
+        yzy_launch<T>(m, keys[kk] / 32, lb.L, lb.total, nt, lds, s);
+        continue;
       }
       int nts = 0, ept = 16;
       const dim3 grid((unsigned)lb.total);
@@ -603,7 +645,7 @@ hipError_t launch_eval(const GroupSet<T>& gs, const Epi<T>* epis, int mode, bool
       for (int i = 0; i < gs.n && on(2); ++i) {
         const HotPlan<T>& hi = gs.h[i];
         const int kind = z_kind<T>(hi.g);
-        if (hi.g.nz == 1 || kind == 2) continue;
+        if (hi.g.nz == 1 || kind == 2 || yzy_m<T>(hi) > 0) continue;
         const bool half = 2 * hi.g.nz == hi.g.Pz;
         const int key = (2 * hi.g.Pz + (half ? 1 : 0)) * 4 + kind;
         bool seen = false;
@@ -613,7 +655,8 @@ hipError_t launch_eval(const GroupSet<T>& gs, const Epi<T>* epis, int mode, bool
         LaunchBuilder<T> lb(gs, epis);
         for (int j = 0; j < gs.n; ++j) {
           const HotPlan<T>& h = gs.h[j];
-          const bool use = h.g.nz > 1 && (2 * h.g.Pz + (2 * h.g.nz == h.g.Pz ? 1 : 0)) * 4 + z_kind<T>(h.g) == key;
+          const bool use = h.g.nz > 1 && yzy_m<T>(h) == 0 &&
+                           (2 * h.g.Pz + (2 * h.g.nz == h.g.Pz ? 1 : 0)) * 4 + z_kind<T>(h.g) == key;
           const long long nb = kind == 0 ? zpair_blocks(h.g, h.batch)
                                : kind == 3 ? zs_blocks(h.g, h.batch, zs_q<T>(h.g.Pz))
                                            : zreg_blocks(h.g, h.batch);
@@ -632,7 +675,7 @@ hipError_t launch_eval(const GroupSet<T>& gs, const Epi<T>* epis, int mode, bool
       size_t lds = 0;
       for (int j = 0; j < gs.n; ++j) {
         const HotPlan<T>& h = gs.h[j];
-        const bool use = h.g.nz > 1 && z_kind<T>(h.g) == 2;
+        const bool use = h.g.nz > 1 && yzy_m<T>(h) == 0 && z_kind<T>(h.g) == 2;
         lz.set(j, use ? zlds_blocks(h.g, h.tu, h.batch) : 0);
         if (use) {
           nt = std::max(nt, 3 * h.tu.qz * h.tu.tpc_z);
@@ -644,7 +687,7 @@ hipError_t launch_eval(const GroupSet<T>& gs, const Epi<T>* epis, int mode, bool
       mark();
       int keys[kMaxGroups], nkeys = 0;
       for (int i = 0; i < gs.n && on(3); ++i) {
-        if (gs.h[i].g.nz == 1) continue;
+        if (gs.h[i].g.nz == 1 || yzy_m<T>(gs.h[i]) > 0) continue;
         const int k = y_key(gs.h[i]);
         bool seen = false;
         for (int j = 0; j < nkeys; ++j) seen = seen || keys[j] == k;
@@ -657,7 +700,7 @@ hipError_t launch_eval(const GroupSet<T>& gs, const Epi<T>* epis, int mode, bool
       size_t ldsy = 0;
       for (int j = 0; j < gs.n; ++j) {
         const HotPlan<T>& h = gs.h[j];
-        usey[j] = h.g.nz > 1 && y_key(h) == keys[kk];
+        usey[j] = h.g.nz > 1 && yzy_m<T>(h) == 0 && y_key(h) == keys[kk];
         ly.set(j, usey[j] ? y3d_blocks(h.g, h.tu, h.batch) : 0);
         if (usey[j]) {
           nty = std::max(nty, h.tu.nt_y);
@@ -761,6 +804,7 @@ hipError_t launch_neb(const Geo& g, int n_img, const T* img, T* img_out, const T
 #define MMX_INST(T)                                                                               \
   template hipError_t launch_eval<T>(const GroupSet<T>&, const Epi<T>*, int, bool, hipStream_t,    \
                                      hipEvent_t*, bool, bool, unsigned);                          \
+  template bool eval_needs_sy<T>(const Geo&);                                                     \
   template bool eval_fusable<T>(const GroupSet<T>&);                                              \
   template hipError_t launch_begin<T>(const GroupSet<T>&, const Epi<T>*, hipStream_t);            \
   template hipError_t launch_sd_iteration<T>(T*, const T*, T*, T*, T*, double*, double*, int, long long,   \

@@ -653,6 +653,92 @@ __device__ __forceinline__ void y_rows3d(const HotPlan<T>& hp, const Epi<T>& ep,
   }
 }
 
+// ---------------------------------------------------------------------------
+// Fused y and z passes of 3-D groups (yzy_m() > 0): one workgroup a kx, the
+// 3 nz columns of that kx in LDS.  Forward y of every column, then per ky the
+// z transform, the tensor product and its inverse (lane pairs, below), then
+// inverse y, in place in Sx.  The three separate passes write and read the
+// doubled y spectrum twice over (Sy, 4 times the bytes of Sx) and take two
+// more launches; here only Sx and the tensor spectrum move.  Bound by the
+// chain of one workgroup (loads, transforms, stores), so it pays where the LDS
+// of a kx lets several workgroups share a CU (yzy_m()).
+// The y, z and inverse-y passes of 256x256x2, FP32: 13.9 us apart, 9.9 us fused;
+// eight of them 48.7 and 35.3 us.
+// ---------------------------------------------------------------------------
+__host__ __device__ inline size_t yzy_lds(const Geo& g, size_t csz) {
+  return ((size_t)3 * g.nz * col_stride(g.Py) + g.Py) * csz;
+}
+__host__ __device__ inline long long yzy_blocks(const Geo& g, int batch) { return (long long)batch * g.Xp; }
+
+// z transform, tensor product and inverse z of one (kx, ky) by a lane pair
+// (the scheme of k_z3d_pair below), in place in the LDS columns: column
+// c nz + z holds component c of plane z, entry o this ky.
+template <typename T, int M>
+__device__ __forceinline__ void yzy_point(const HotPlan<T>& hp, Cx<T>* lds, int cs, int o, int kx, int ky, int p, T s);
+
+// Compiled for Py = SL = 2 ny, 8 entries a thread.
+template <typename T, int M, int SL>
+__device__ __forceinline__ void yzy3d(const HotPlan<T>& hp, const Epi<T>& ep, long long bid0, Cx<T>* lds) {
+  const Geo& g = hp.g;
+  const unsigned bid = (unsigned)bid0;
+  const int kx = (int)(bid % (unsigned)g.Xp);
+  const int b = (int)(bid / (unsigned)g.Xp);
+  if (ep.ctl && ldu(&ep.ctl[b].done)) return;
+  const int nz = g.nz, ny = g.ny, ncol = 3 * nz;
+  const int cs = col_stride(g.Py);
+  constexpr int sh = p2_psh(SL, false);
+  constexpr int tpc = SL / 8;
+  const int many = (int)blockDim.x / tpc;  // columns transformed at a time
+  const int mc = (int)threadIdx.x / tpc;
+  Cx<T>* const twl = lds + ncol * cs;
+  TableCopy<T, 4> tab;
+  tab.issue(hp.fd[1].tw, g.Py, nullptr, 0);
+  // Sx blocks [3 nz][XB][ny][kSxB] of the instance, column kx of plane c nz + z
+  Cx<T>* const base = hp.Sx + (size_t)b * g.sx;
+  const uint32_t plane = (uint32_t)(g.XB * kSxB * ny);
+  const uint32_t k0 = (uint32_t)((kx >> 2) * kSxB * ny + (kx & 3));
+  constexpr uint32_t sb = kSxB * sizeof(Cx<T>);
+  for (int c0 = 0; c0 < ncol; c0 += many) {
+    const int nc = ncol - c0 < many ? ncol - c0 : many;
+    const uint32_t coff = ((uint32_t)(c0 + (mc < nc ? mc : 0)) * plane + k0) * (uint32_t)sizeof(Cx<T>);
+    const ColLoadS<T> ld{base, coff, sb, ny};
+    auto hook = [&]() {
+      if (c0 == 0) tab.store(twl);
+    };
+    fft_static<T, SL, false, false, true, false, true, true, false, 8>(lds + c0 * cs, twl, cs, nc, ld, NoStore<T>{},
+                                                                      hook);
+  }
+  const T s = T(ldu(&hp.prm[b].demag_scale));
+  for (int ky = (int)threadIdx.x >> 1; ky < g.Py; ky += (int)blockDim.x >> 1)
+    yzy_point<T, M>(hp, lds, cs, pidx(ky, sh), kx, ky, (int)threadIdx.x & 1, s);
+  __syncthreads();
+  for (int c0 = 0; c0 < ncol; c0 += many) {
+    const int nc = ncol - c0 < many ? ncol - c0 : many;
+    const uint32_t coff = ((uint32_t)(c0 + (mc < nc ? mc : 0)) * plane + k0) * (uint32_t)sizeof(Cx<T>);
+    const ColStoreS<T> st{base, coff, sb, ny};
+    fft_static<T, SL, false, true, false, true, true, false, true, 8>(lds + c0 * cs, twl, cs, nc, NoLoad<T>{}, st,
+                                                                     NoHook{});
+  }
+}
+
+// One launch: fused 3-D groups of one Pz = 2 M and one y length SL = 2 ny, and
+// 2-D groups of that length.
+template <typename T, int M, int SL>
+__global__ void __launch_bounds__(512) k_yzy(Launch<T> L) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  Cx<T>* lds = reinterpret_cast<Cx<T>*>(smem);
+  long long bid;
+  const int gi = group_of(L, bid);
+  const HotPlan<T> hp = hot_plan(L, gi);
+  if (hp.g.nz == 1) {
+    if (bid >= y2d_blocks(hp.g, hp.tu, hp.batch)) return;
+    y_fused2d<T, false, SL, 8>(hp, ldu(L.epis + gi), bid, lds);
+  } else {
+    if (bid >= yzy_blocks(hp.g, hp.batch)) return;
+    yzy3d<T, M, SL>(hp, ldu(L.epis + gi), bid, lds);
+  }
+}
+
 // Forward y pass of every group: fused 2-D or 3-D forward rows.
 // R16: the y plans hold radix-16 stages (lengths beyond 512 points).
 template <typename T, bool R16>
@@ -983,6 +1069,78 @@ __device__ __forceinline__ double pair_swap(double v) {
   const int lo = __builtin_amdgcn_mov_dpp((int)(b & 0xffffffffLL), 0xB1, 0xF, 0xF, false);
   const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), 0xB1, 0xF, 0xF, false);
   return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
+template <typename T, int M>
+__device__ __forceinline__ void yzy_point(const HotPlan<T>& hp, Cx<T>* lds, int cs, int o, int kx, int ky, int p,
+                                          T s) {
+  constexpr int PZ = 2 * M;
+  const Geo& g = hp.g;
+  const int nz = g.nz;
+  Cx<T> v[3][M];
+#pragma unroll
+  for (int c = 0; c < 3; ++c)
+#pragma unroll
+    for (int z = 0; z < M; ++z) {
+      v[c][z] = {T(0), T(0)};
+      if (z < nz) v[c][z] = lds[(c * nz + z) * cs + o];  // uniform branch
+    }
+  // odd lanes: pre-multiply by exp(-2 pi i z / 2M)
+#pragma unroll
+  for (int z = 1; z < M; ++z) {
+    Cx<T> w = ldu(hp.twz + z);
+    if (!p) w = Cx<T>{T(1), T(0)};
+#pragma unroll
+    for (int c = 0; c < 3; ++c) v[c][z] = cmul(v[c][z], w);
+  }
+#pragma unroll
+  for (int c = 0; c < 3; ++c) RegFft<T, M, 1, false, 2>::run(v[c], hp.twz);
+  const int kyf = ky <= g.Py - ky ? ky : g.Py - ky;
+  const T sy = ky > g.Py - ky ? T(-1) : T(1);
+  const size_t cstride = (size_t)g.Kz * g.Xp * g.Ky;
+  const uint32_t XK = (uint32_t)g.Xp * (uint32_t)g.Ky;
+  const uint32_t kxy0 = (uint32_t)kx * (uint32_t)g.Ky + (uint32_t)kyf;
+#pragma unroll
+  for (int k = 0; k < M; ++k) {
+    const int kz = 2 * k + p;
+    const int kzf = kz <= PZ - kz ? kz : PZ - kz;
+    const T sz = kz > PZ - kz ? T(-1) : T(1);
+    const uint32_t ko = ((uint32_t)kzf * XK + kxy0) * (uint32_t)sizeof(T);
+    Ten<T> t;
+    t.xx = gldo(hp.kt, ko) * s;
+    t.yy = gldo(hp.kt + cstride, ko) * s;
+    t.zz = gldo(hp.kt + 2 * cstride, ko) * s;
+    t.xy = gldo(hp.kt + 3 * cstride, ko) * (s * sy);
+    t.xz = gldo(hp.kt + 4 * cstride, ko) * (s * sz);
+    t.yz = gldo(hp.kt + 5 * cstride, ko) * (s * sy * sz);
+    tensor_mul(t, v[0][k], v[1][k], v[2][k]);
+  }
+#pragma unroll
+  for (int c = 0; c < 3; ++c) RegFft<T, M, 1, true, 2>::run(v[c], hp.twz);
+  // odd lanes: post-multiply by exp(+2 pi i z / 2M)
+#pragma unroll
+  for (int z = 1; z < M; ++z) {
+    Cx<T> w = ldu(hp.twz + z);
+    w.y = -w.y;
+    if (!p) w = Cx<T>{T(1), T(0)};
+#pragma unroll
+    for (int c = 0; c < 3; ++c) v[c][z] = cmul(v[c][z], w);
+  }
+  // z of parity p: own half + partner's half (both lanes have read every plane
+  // of this ky before either writes: one wave, in program order)
+#pragma unroll
+  for (int z0 = 0; z0 < M; z0 += 2) {
+    const int ze = z0, zo = z0 + 1 < M ? z0 + 1 : z0;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      const Cx<T> send = p ? v[c][ze] : v[c][zo];
+      const Cx<T> got = {pair_swap(send.x), pair_swap(send.y)};
+      const Cx<T> mine = p ? v[c][zo] : v[c][ze];
+      const Cx<T> sum = cadd(mine, got);
+      const int zz = p ? zo : ze;
+      if (zz < nz && (p == 0 || z0 + 1 < M)) lds[(c * nz + zz) * cs + o] = sum;
+    }
+  }
 }
 
 template <typename T, int M>
@@ -2105,5 +2263,25 @@ void inv_x_launch(int mode, int cpt, bool fuse, const Launch<T>& L, long long to
   }
 }
 
+
+template <typename T, int M>
+void yzy_launch_m(int sl, const Launch<T>& L, long long total, int nt, size_t lds, hipStream_t s) {
+  const dim3 grid((unsigned)total);
+  switch (sl) {
+    case 256: k_yzy<T, M, 256><<<grid, nt, lds, s>>>(L); break;
+    case 512: k_yzy<T, M, 512><<<grid, nt, lds, s>>>(L); break;
+    default: k_yzy<T, M, 1024><<<grid, nt, lds, s>>>(L); break;
+  }
+}
+
+// m: Pz / 2 of the launch's fused groups; sl: the y length it is compiled for
+template <typename T>
+void yzy_launch(int m, int sl, const Launch<T>& L, long long total, int nt, size_t lds, hipStream_t s) {
+  switch (m) {
+    case 2: yzy_launch_m<T, 2>(sl, L, total, nt, lds, s); break;
+    case 3: yzy_launch_m<T, 3>(sl, L, total, nt, lds, s); break;
+    default: yzy_launch_m<T, 4>(sl, L, total, nt, lds, s); break;
+  }
+}
 
 }  // namespace mmx

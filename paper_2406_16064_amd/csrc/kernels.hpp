@@ -103,7 +103,7 @@ template <typename T> struct HotPlan {
   int ncomp;               // 4 (nz = 1) or 6
   int batch;               // instances in the group
   Cx<T>* Sx;               // [batch][sx] (layout above)
-  Cx<T>* Sy;               // [batch][3][nz][Xp][Py] (3-D only)
+  Cx<T>* Sy;               // [batch][3][nz][Xp][Py] (3-D; null where the y and z passes are fused)
   const DevParams* prm;    // [batch]
   const T* cells;          // cell-based material [batch][3][N] (Ms, A, D per cell) or null
   int gen;                 // launch the general-material form of the inverse-x epilogue
@@ -149,6 +149,11 @@ hipError_t launch_eval(const GroupSet<T>& gs, const Epi<T>* epis, int mode, bool
 
 template <typename T>
 bool eval_fusable(const GroupSet<T>& gs);
+
+// Whether the Newell passes of a mesh use the y-pass buffer Sy (3-D meshes
+// whose y and z passes are not fused).
+template <typename T>
+bool eval_needs_sy(const Geo& g);
 
 template <typename T>
 hipError_t launch_begin(const GroupSet<T>& gs, const Epi<T>* epis, hipStream_t s);

@@ -817,7 +817,9 @@ mm_status engine_reserve(Engine& E, const std::vector<int>& per_group) {
       if (G.Sy) (void)hipFree(G.Sy);
       G.Sx = G.Sy = nullptr;
       MMCHK(dev_alloc(&G.Sx, E.csz * G.g.sx * n));
-      if (G.g.nz > 1) MMCHK(dev_alloc(&G.Sy, E.csz * G.g.sy * n));
+      const bool sy = (E.terms & MM_DEMAG_POTENTIAL) != 0 ||
+                      (E.prec == MM_F32 ? eval_needs_sy<float>(G.g) : eval_needs_sy<double>(G.g));
+      if (G.g.nz > 1 && sy) MMCHK(dev_alloc(&G.Sy, E.csz * G.g.sy * n));
       G.cap = n;
       if (E.gexec) { (void)hipGraphExecDestroy(E.gexec); E.gexec = nullptr; }
     } else if (n > G.cap) {

@@ -7,7 +7,7 @@ from oracle import dp45
 from oracle import fields as F
 from paper_2406_16064_amd import inputs
 
-from _util import field_err, gpu_params, oracle_params, to_dev
+from _util import field_err, gpu_params, oracle_params, representable, to_dev
 
 torch = pytest.importorskip("torch")
 
@@ -51,3 +51,39 @@ def test_error_norm_over_many_workgroups_fp64(mm, ny):
             assert bool(st[b].last_accepted) == acc
             assert abs(st[b].last_err - ost[b].last_err) <= 1e-9 * max(1.0, ost[b].last_err)
             assert field_err(md[b].cpu().numpy(), mo[b]) <= 1e-12
+
+
+@pytest.mark.parametrize("prec,tol", [("f32", 1e-5), ("f64", 1e-11)])
+@pytest.mark.parametrize("mesh", [(20, 128, 2), (9, 128, 3), (16, 128, 4), (10, 256, 2), (6, 256, 3), (5, 512, 2),
+                                  (8, 256, 4), (6, 512, 3), (12, 127, 2), (12, 128, 5)])
+def test_fused_yz_planes(mm, mesh, prec, tol):
+    """Fields of small 3-D meshes on both sides of the fused y and z passes:
+    nz = 2 to 4 with 128, 256 and 512 rows (fused while a kx fits 64 KB of LDS),
+    a length and a plane count that keep the separate passes.  Two instances."""
+    mesh = mesh + (3e-9, 2e-9, 2.5e-9)
+    plan = mm.Plan(mesh, prec, terms=F.ALL_TERMS, max_batch=2)
+    gp, op = gpu_params(mm, PAR, F.ALL_TERMS), oracle_params(PAR, F.ALL_TERMS)
+    kern = F.DemagKernel(F.Mesh(*mesh))
+    m = [representable(_m(mesh, s), plan.dtype) for s in (21, 22)]
+    H = plan.effective_field([gp, gp], to_dev(np.stack(m), plan.dtype)).double().cpu().numpy()
+    for b in range(2):
+        assert field_err(H[b], F.effective_field(m[b], F.Mesh(*mesh), op, kern)) <= tol
+
+
+def test_fused_yz_batch_with_films_fp64(mm):
+    """A batch whose films and fused planes share one y launch (Py = 256), next
+    to a mesh with the separate passes: each trajectory against the oracle's."""
+    meshes = [(12, 128, 1, 2e-9, 2e-9, 2e-9), (10, 128, 2, 2e-9, 2e-9, 2e-9), (10, 20, 2, 2e-9, 2e-9, 2e-9)]
+    batch = mm.Batch(meshes, "f64")
+    gp, op = gpu_params(mm, PAR, F.ALL_TERMS), oracle_params(PAR, F.ALL_TERMS)
+    which = [1, 0, 2, 1]
+    m0 = [_m(meshes[k], 30 + i) for i, k in enumerate(which)]
+    md = [to_dev(m, torch.float64) for m in m0]
+    t_end = 8e-14
+    batch.run([dict(mesh_id=k, params=gp, m=md[i], t_end=t_end, state=mm.new_states(1, h=2e-14, h_max=2e-14)[0])
+               for i, k in enumerate(which)])
+    for i, k in enumerate(which):
+        mesh = F.Mesh(*meshes[k])
+        kern = F.DemagKernel(mesh)
+        mo = dp45.run(lambda y: F.llg_rhs(y, mesh, op, kern), m0[i], dp45.State(h=2e-14, h_max=2e-14), t_end=t_end)
+        assert np.max(np.abs(md[i].cpu().numpy() - mo)) <= 1e-9
