@@ -3,6 +3,9 @@
 // compiled in invx_*.hip, one translation unit each).
 #include "hotpath.hpp"
 
+#include <cstddef>
+#include <cstring>
+
 namespace mmx {
 
 int eval_blocks_per_inst(const Geo& g, const Tuning& tu) { return ((g.ny + tu.ty_x - 1) / tu.ty_x) * g.nz; }
@@ -775,6 +778,43 @@ hipError_t launch_sd_iteration(T* m, const T* H, T* g, T* mp, T* gp, double* par
     const long long total = (long long)batch * N;
     k_sd_update<T><<<dim3((unsigned)((total + kNT - 1) / kNT)), kNT, 0, s>>>(m, H, g, mp, gp, tau, N, total, ctl);
   }
+  return hipGetLastError();
+}
+
+// The kernel argument itself is the source: it is read through its segment
+// pointer, by lane, so that no copy of it goes to scratch memory.
+struct PutArgs {
+  uint32_t* dst;
+  uint32_t n;
+  uint32_t pad;
+  uint32_t w[kPutBytes / 4];
+};
+__global__ void __launch_bounds__(kNT) k_put(PutArgs a) {
+  const MMX_CONST uint32_t* src =
+      (const MMX_CONST uint32_t*)((const MMX_CONST char*)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(PutArgs, w));
+  MMX_GLOBAL uint32_t* dst = (MMX_GLOBAL uint32_t*)a.dst;
+  for (uint32_t i = threadIdx.x; i < a.n; i += kNT) dst[i] = src[i];
+}
+__global__ void __launch_bounds__(kNT) k_get(uint32_t* __restrict__ dst, const uint32_t* __restrict__ src, size_t n) {
+  for (size_t i = blockIdx.x * (size_t)kNT + threadIdx.x; i < n; i += (size_t)gridDim.x * kNT) dst[i] = src[i];
+}
+
+hipError_t launch_put(void* dst, const void* src, size_t bytes, hipStream_t s) {
+  PutArgs a;
+  a.pad = 0;
+  for (size_t o = 0; o < bytes; o += kPutBytes) {
+    const size_t n = std::min(kPutBytes, bytes - o);
+    a.dst = (uint32_t*)((char*)dst + o);
+    a.n = (uint32_t)(n / 4);
+    std::memcpy(a.w, (const char*)src + o, n);
+    k_put<<<dim3(1), kNT, 0, s>>>(a);
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_get(void* host, const void* src, size_t bytes, hipStream_t s) {
+  const size_t n = bytes / 4;
+  k_get<<<dim3((unsigned)std::min<size_t>(64, (n + kNT - 1) / kNT)), kNT, 0, s>>>((uint32_t*)host, (const uint32_t*)src, n);
   return hipGetLastError();
 }
 

@@ -158,6 +158,13 @@ bool eval_needs_sy(const Geo& g);
 template <typename T>
 hipError_t launch_begin(const GroupSet<T>& gs, const Epi<T>* epis, hipStream_t s);
 
+// Host bytes into device memory through kernel arguments, kPutBytes a launch
+// (a multiple of 4; the source is free again on return), and device bytes into
+// pinned host memory.
+constexpr size_t kPutBytes = 3584;
+hipError_t launch_put(void* dst, const void* src, size_t bytes, hipStream_t s);
+hipError_t launch_get(void* host, const void* src, size_t bytes, hipStream_t s);
+
 hipError_t launch_controller(DevCtl* ctl, int n, const double* replay_h, hipStream_t s);
 // One steepest-descent iteration k of `batch` instances after H = H_eff(m):
 // g = m x (m x H), for k >= 1 the Barzilai-Borwein step from the block sums

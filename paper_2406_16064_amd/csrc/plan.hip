@@ -273,7 +273,17 @@ struct Engine {
   // launches; behind ctl in its allocation, cleared before the first adaptive run
   ErrSlot* eslot = nullptr;
   bool eslot_clear = false;
+  // What each device table last received (by content), so that a call sends only
+  // what changed (put()): parameters, plan tables, then the epilogue slots.
+  struct Sent {
+    std::vector<char> bytes;
+    void* dst = nullptr;
+    hipStream_t s = nullptr;
+  };
+  Sent sent[2 + kEpiSlots];
   double* partial = nullptr;
+  void* sd_scratch = nullptr;  // steepest descent: block sums and step sizes
+  size_t sd_bytes = 0;
   double* e5 = nullptr;
   double* replay = nullptr;
   long long replay_cap = 0;
@@ -711,7 +721,7 @@ void free_engine(Engine& E) {
   if (E.gexec) (void)hipGraphExecDestroy(E.gexec);
   E.gexec = nullptr;
   for (Group& G : E.groups) free_group(G);
-  void* bufs[] = {E.prm, E.ctl, E.partial, E.e5, E.replay, E.dhot, E.depi, E.nebH, E.nebB, E.nebS, E.nebP};
+  void* bufs[] = {E.prm, E.ctl, E.sd_scratch, E.partial, E.e5, E.replay, E.dhot, E.depi, E.nebH, E.nebB, E.nebS, E.nebP};
   for (void* b : bufs)
     if (b) (void)hipFree(b);
   if (E.hctl) (void)hipHostFree(E.hctl);
@@ -833,6 +843,7 @@ mm_status engine_reserve(Engine& E, const std::vector<int>& per_group) {
     if (E.hctl) (void)hipHostFree(E.hctl);
     if (E.hctl2) (void)hipHostFree(E.hctl2);
     if (E.he5) (void)hipHostFree(E.he5);
+    E.sent[0].dst = nullptr;
     E.prm = nullptr; E.ctl = nullptr; E.eslot = nullptr; E.e5 = nullptr; E.hctl = nullptr; E.hctl2 = nullptr; E.he5 = nullptr;
     MMCHK(dev_alloc((void**)&E.prm, sizeof(DevParams) * total));
     const size_t ctl_bytes = (sizeof(DevCtl) * total + 127) / 128 * 128;
@@ -856,9 +867,49 @@ mm_status engine_reserve(Engine& E, const std::vector<int>& per_group) {
   return MM_OK;
 }
 
+// Stream-ordered copies of small host tables to device memory without a wait:
+// the bytes travel in a kernel's argument (k_put), so the host memory is free
+// again on return and no copy engine takes part.  Larger tables take a copy
+// and a wait.  A call of a film used to spend 30 to 60 us on three such
+// copies, each waited for (16x16x1 FP64 field: 59 us, 25 of them in kernels).
+constexpr size_t kPutLimit = 5 * kPutBytes;
+
+mm_status send(void* dst, const void* src, size_t bytes, hipStream_t s) {
+  if (bytes <= kPutLimit) {
+    HIPCHK(launch_put(dst, src, bytes, s));
+    return MM_OK;
+  }
+  HIPCHK(hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s));
+  HIPCHK(hipStreamSynchronize(s));
+  return MM_OK;
+}
+
+// Table `region` (0 parameters, 1 plan tables, 2 + k epilogue slot k) at dst:
+// sent unless the same bytes were the last ones sent there on this stream.
+mm_status put(Engine& E, int region, void* dst, const void* src, size_t bytes, hipStream_t s) {
+  Engine::Sent& t = E.sent[region];
+  if (t.dst == dst && t.s == s && t.bytes.size() == bytes && std::memcmp(t.bytes.data(), src, bytes) == 0) return MM_OK;
+  t.dst = nullptr;
+  MMCHK(send(dst, src, bytes, s));
+  t.bytes.assign((const char*)src, (const char*)src + bytes);
+  t.dst = dst;
+  t.s = s;
+  return MM_OK;
+}
+
+// The compute calls keep tables on the device between calls and are not
+// recorded into a caller's graph.
+mm_status not_capturing(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  HIPCHK(hipStreamIsCapturing(s, &st));
+  if (st != hipStreamCaptureStatusNone) return fail(MM_E_HIP, "the stream is being captured");
+  return MM_OK;
+}
+
 // Upload parameters (in group order) and remember whether demag is on.
 mm_status upload_params(Engine& E, const std::vector<const mm_params*>& q, const std::vector<int>& grp,
                         hipStream_t s) {
+  MMCHK(not_capturing(s));
   std::vector<DevParams> d(q.size());
   E.any_demag = false;
   E.any_pot = false;
@@ -869,9 +920,7 @@ mm_status upload_params(Engine& E, const std::vector<const mm_params*>& q, const
     E.any_demag = E.any_demag || (q[b]->terms & MM_DEMAG) != 0;
     E.any_pot = E.any_pot || (q[b]->terms & MM_DEMAG_POTENTIAL) != 0;
   }
-  HIPCHK(hipMemcpyAsync(E.prm, d.data(), sizeof(DevParams) * d.size(), hipMemcpyHostToDevice, s));
-  HIPCHK(hipStreamSynchronize(s));
-  return MM_OK;
+  return put(E, 0, E.prm, d.data(), sizeof(DevParams) * d.size(), s);
 }
 
 // Host and device views of the groups for the given per-group instance counts
@@ -905,9 +954,8 @@ mm_status make_set(Engine& E, const std::vector<int>& nb, GroupSet<T>& gs, std::
     acc += nb[i];
   }
   gs.dh = (const HotPlan<T>*)E.dhot;
-  HIPCHK(hipMemcpyAsync(E.dhot, gs.h, sizeof(HotPlan<T>) * gs.n, hipMemcpyHostToDevice, s));
-  HIPCHK(hipStreamSynchronize(s));
-  return MM_OK;
+  if (gs.n == 1) return MM_OK;  // group 0 travels with the kernel arguments
+  return put(E, 1, E.dhot, gs.h, sizeof(HotPlan<T>) * gs.n, s);
 }
 
 template <typename T>
@@ -917,9 +965,7 @@ Epi<T>* epi_slot(Engine& E, int slot) {
 
 template <typename T>
 mm_status upload_epis(Engine& E, int slot, const std::vector<Epi<T>>& ep, hipStream_t s) {
-  HIPCHK(hipMemcpyAsync(epi_slot<T>(E, slot), ep.data(), sizeof(Epi<T>) * ep.size(), hipMemcpyHostToDevice, s));
-  HIPCHK(hipStreamSynchronize(s));
-  return MM_OK;
+  return put(E, 2 + slot, epi_slot<T>(E, slot), ep.data(), sizeof(Epi<T>) * ep.size(), s);
 }
 
 template <typename T>
@@ -1096,8 +1142,8 @@ mm_status profile_impl(mm_plan* p, const mm_params* q, int batch, const void* m,
 mm_status energy_finish(Engine& E, const mm_params* q, int batch, const double* partial, double* e5,
                         double* E_out, hipStream_t s) {
   const Group& G = E.groups[0];
-  HIPCHK(launch_energy_reduce(partial, batch, eval_blocks_per_inst(G.g, G.tu), e5, s));
-  HIPCHK(hipMemcpyAsync(E.he5, e5, sizeof(double) * 5 * batch, hipMemcpyDeviceToHost, s));
+  // the sums go straight to the pinned host buffer
+  HIPCHK(launch_energy_reduce(partial, batch, eval_blocks_per_inst(G.g, G.tu), E.he5, s));
   HIPCHK(hipStreamSynchronize(s));
   for (int b = 0; b < batch; ++b) {
     const double c = kMu0 * (E.use_general ? 1.0 : q[b].Ms) * G.g.dV;  // general form: Ms in the sums
@@ -1235,7 +1281,7 @@ mm_status heun_impl(mm_plan* p, const mm_params* q, int batch, T* m, double h, l
     std::memset(&E.hctl[b], 0, sizeof(DevCtl));
     E.hctl[b].h_att = h;
   }
-  HIPCHK(hipMemcpyAsync(E.ctl + inst0[0], E.hctl, sizeof(DevCtl) * batch, hipMemcpyHostToDevice, s));
+  MMCHK(send(E.ctl + inst0[0], E.hctl, sizeof(DevCtl) * batch, s));
   Epi<T> e1 = epi_base<T>(G, MODE_STAGE);
   e1.ctl = E.ctl + inst0[0];
   Epi<T> e2 = e1;
@@ -1312,7 +1358,7 @@ mm_status sd_impl(mm_plan* p, const mm_params* q, int batch, T* m, long long n_i
       std::memset(&E.hctl[b], 0, sizeof(DevCtl));
       E.hctl[b].stop_dmdt = stop;
     }
-    HIPCHK(hipMemcpyAsync(ctl, E.hctl, sizeof(DevCtl) * batch, hipMemcpyHostToDevice, s));
+    MMCHK(send(ctl, E.hctl, sizeof(DevCtl) * batch, s));
   }
   T* const H = stage_buf<T>(G, 4);
   Epi<T> e = epi_base<T>(G, MODE_FIELD);
@@ -1329,12 +1375,19 @@ mm_status sd_impl(mm_plan* p, const mm_params* q, int batch, T* m, long long n_i
     part = (double*)ext;
     tau = (double*)(ext + sd_part_bytes(G, batch));
   } else {
-    MMCHK(dev_alloc((void**)&part, sizeof(double) * 4 * bpi * batch));
-    st = dev_alloc((void**)&tau, sizeof(double) * batch);
+    if (E.sd_bytes < sd_scratch_bytes(G, batch)) {
+      if (E.sd_scratch) (void)hipFree(E.sd_scratch);
+      E.sd_scratch = nullptr;
+      E.sd_bytes = 0;
+      MMCHK(dev_alloc(&E.sd_scratch, sd_scratch_bytes(G, batch)));
+      E.sd_bytes = sd_scratch_bytes(G, batch);
+    }
+    part = (double*)E.sd_scratch;
+    tau = (double*)((char*)E.sd_scratch + sd_part_bytes(G, batch));
   }
   std::vector<double> t0(batch, tau0);
-  hipError_t er = st == MM_OK ? hipMemcpyAsync(tau, t0.data(), sizeof(double) * batch, hipMemcpyHostToDevice, s)
-                              : hipSuccess;
+  st = send(tau, t0.data(), sizeof(double) * batch, s);
+  hipError_t er = hipSuccess;
   const long long n_launch = relax ? n_iter + 1 : n_iter;
   for (long long k = 0; st == MM_OK && er == hipSuccess && k < n_launch; ++k) {
     er = eval_slot<T>(E, gs, 4, MODE_FIELD, s);
@@ -1349,7 +1402,7 @@ mm_status sd_impl(mm_plan* p, const mm_params* q, int batch, T* m, long long n_i
       if (all) break;
     }
   }
-  {  // the buffers are freed below: nothing may still use them
+  {
     const hipError_t es = hipStreamSynchronize(s);
     if (er == hipSuccess) er = es;
   }
@@ -1358,10 +1411,6 @@ mm_status sd_impl(mm_plan* p, const mm_params* q, int batch, T* m, long long n_i
   if (st == MM_OK && er == hipSuccess && relax) er = hipMemcpy(E.hctl, ctl, sizeof(DevCtl) * batch,
                                                                hipMemcpyDeviceToHost);
   if (st == MM_OK && er != hipSuccess) st = fail(MM_E_HIP, hipGetErrorString(er));
-  if (!ext) {
-    (void)hipFree(part);
-    if (tau) (void)hipFree(tau);
-  }
   if (st != MM_OK || !relax) return st;
   bool all_stopped = true;
   for (int b = 0; b < batch; ++b) {
@@ -1543,7 +1592,7 @@ mm_status run_core(Engine& E, const std::vector<T*>& m, const std::vector<int>& 
       else if (c.h_att < r.h_min) return fail(MM_E_STEP_UNDERFLOW, "initial step below h_min");
     }
   }
-  HIPCHK(hipMemcpyAsync(E.ctl, E.hctl, sizeof(DevCtl) * n_total, hipMemcpyHostToDevice, s));
+  MMCHK(send(E.ctl, E.hctl, sizeof(DevCtl) * n_total, s));
   if (!E.eslot_clear) {  // outside every capture: the run's graph is captured on another stream
     HIPCHK(hipMemsetAsync(E.eslot, 0, sizeof(ErrSlot) * kErrSlots * E.inst_cap, s));
     E.eslot_clear = true;
@@ -1561,75 +1610,89 @@ mm_status run_core(Engine& E, const std::vector<T*>& m, const std::vector<int>& 
   if (single) {
     MMCHK(enqueue_attempt<T>(E, gs, n_total, s));
   } else {
-    const int K = 8;  // attempts per graph launch between host polls
+    // Attempts are submitted in chunks of K as one captured graph, or one by one
+    // where fewer are expected: as many as the step size asks for to the end
+    // (t_end or the replayed steps), or the attempt limit allows.  A kernel of
+    // an attempt past the end still takes 2 to 16 us (the last of eight attempts
+    // of a 256x256x1 film 45 us, of a 512x512x16 slab 265 us), so nothing is
+    // queued beyond what the last seen states expect.  Up to two chunks are in
+    // flight, each followed by a copy of the controllers into its own host
+    // buffer: the host reads one while the next runs.
+    const long long K = 8;
+    for (hipEvent_t& ev : E.poll_ev)
+      if (!ev) HIPCHK(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
+    DevCtl* const hb[2] = {E.hctl, E.hctl2};
+    // attempts still expected by the instance that needs most; 0: all done
+    auto expected = [&](const DevCtl* h) {
+      long long r = 0;
+      for (int b = 0; b < n_total; ++b) {
+        if (h[b].done) continue;
+        long long need = h[b].max_attempt - h[b].n_attempt;
+        if (h[b].replay_n > 0) need = std::min(need, h[b].replay_n - h[b].replay_pos);
+        else if (h[b].t_end < HUGE_VAL) {
+          const double q = (h[b].t_end - h[b].t) / std::min(h[b].h, h[b].h_max);
+          if (q < 1e9) need = std::min(need, (long long)std::ceil(q * (1 - 1e-9)));
+        }
+        r = std::max(r, std::max(need, 1LL));
+      }
+      return r;
+    };
+    long long rem = expected(E.hctl);  // the states just uploaded
+    // a graph costs about 1.5 ms to capture: worth it for long runs, or once there
     std::vector<const void*> key;
     for (int i = 0; i < ng; ++i) {
       key.push_back(m[i]);
       key.push_back((const void*)(intptr_t)nb[i]);
     }
-    key.push_back((const void*)(intptr_t)(demag_on(E) ? 1 : 0));
-    if (!E.gexec || E.g_key != key) {
-      if (E.gexec) { (void)hipGraphExecDestroy(E.gexec); E.gexec = nullptr; }
-      HIPCHK(hipStreamBeginCapture(E.cap, hipStreamCaptureModeThreadLocal));
-      mm_status cs = MM_OK;
-      for (int k = 0; k < K && cs == MM_OK; ++k) cs = enqueue_attempt<T>(E, gs, n_total, E.cap);
-      hipGraph_t graph = nullptr;
-      hipError_t ee = hipStreamEndCapture(E.cap, &graph);
-      if (cs != MM_OK) { if (graph) (void)hipGraphDestroy(graph); return cs; }
-      if (ee != hipSuccess) return fail(MM_E_HIP, std::string("capture: ") + hipGetErrorString(ee));
-      ee = hipGraphInstantiate(&E.gexec, graph, nullptr, nullptr, 0);
-      (void)hipGraphDestroy(graph);
-      if (ee != hipSuccess) { E.gexec = nullptr; return fail(MM_E_HIP, std::string("instantiate: ") + hipGetErrorString(ee)); }
-      E.g_key = key;
-    }
-    // Up to two graph launches in flight, each followed by a copy of the
-    // controllers into its own host buffer: the host reads one while the next
-    // graph runs.  A further launch is queued only while some instance may
-    // still have attempts left after the ones in flight (bounded by its
-    // attempt limit as last seen), so a run bounded by max_steps launches no
-    // graph that has nothing to do; one that ends at t_end may queue one
-    // (every kernel of it returns at once for finished instances).
-    for (hipEvent_t& ev : E.poll_ev)
-      if (!ev) HIPCHK(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
-    DevCtl* const hb[2] = {E.hctl, E.hctl2};
-    auto remaining = [&](const DevCtl* h, bool& all) {
-      long long r = 0;
-      all = true;
-      for (int b = 0; b < n_total; ++b) {
-        if (h[b].done) continue;
-        all = false;
-        r = std::max(r, h[b].max_attempt - h[b].n_attempt);
-      }
-      return r;
-    };
-    bool all = false;
-    long long rem = remaining(E.hctl, all);  // the state just uploaded
+    // the kernels of the sequence: demag route, uniform or general material
+    key.push_back((const void*)(intptr_t)((demag_on(E) ? 1 : 0) + (E.any_pot ? 2 : 0) + (E.use_general ? 4 : 0)));
+    bool have = E.gexec && E.g_key == key;
+    long long flying[2] = {0, 0};  // attempts of each chunk in flight
     int head = 0, inflight = 0;
-    auto launch = [&]() -> mm_status {
+    auto submit = [&](long long n) -> mm_status {
+      if (n == K && !have && rem >= 8 * K) {
+        if (E.gexec) { (void)hipGraphExecDestroy(E.gexec); E.gexec = nullptr; }
+        HIPCHK(hipStreamBeginCapture(E.cap, hipStreamCaptureModeThreadLocal));
+        mm_status cs = MM_OK;
+        for (int k = 0; k < K && cs == MM_OK; ++k) cs = enqueue_attempt<T>(E, gs, n_total, E.cap);
+        hipGraph_t graph = nullptr;
+        hipError_t ee = hipStreamEndCapture(E.cap, &graph);
+        if (cs != MM_OK) { if (graph) (void)hipGraphDestroy(graph); return cs; }
+        if (ee != hipSuccess) return fail(MM_E_HIP, std::string("capture: ") + hipGetErrorString(ee));
+        ee = hipGraphInstantiate(&E.gexec, graph, nullptr, nullptr, 0);
+        (void)hipGraphDestroy(graph);
+        if (ee != hipSuccess) { E.gexec = nullptr; return fail(MM_E_HIP, std::string("instantiate: ") + hipGetErrorString(ee)); }
+        E.g_key = key;
+        have = true;
+      }
       const int slot = (head + inflight) & 1;
-      HIPCHK(hipGraphLaunch(E.gexec, s));
-      HIPCHK(hipMemcpyAsync(hb[slot], E.ctl, sizeof(DevCtl) * n_total, hipMemcpyDeviceToHost, s));
+      if (n == K && have) HIPCHK(hipGraphLaunch(E.gexec, s));
+      else
+        for (long long k = 0; k < n; ++k) MMCHK(enqueue_attempt<T>(E, gs, n_total, s));
+      HIPCHK(launch_get(hb[slot], E.ctl, sizeof(DevCtl) * n_total, s));
       HIPCHK(hipEventRecord(E.poll_ev[slot], s));
+      flying[slot] = n;
       ++inflight;
       return MM_OK;
     };
-    if (!all) {
-      MMCHK(launch());
-      for (;;) {
-        if (inflight < 2 && rem > (long long)K * inflight) MMCHK(launch());
-        HIPCHK(hipEventSynchronize(E.poll_ev[head]));
-        rem = remaining(hb[head], all);
-        head ^= 1;
-        --inflight;
-        if (all) break;
-        if (inflight == 0) MMCHK(launch());
+    while (rem > 0) {
+      long long queued = 0;
+      for (int i = 0; i < inflight; ++i) queued += flying[(head + i) & 1];
+      while (inflight < 2 && rem > queued) {
+        const long long n = std::min(K, rem - queued);
+        MMCHK(submit(n));
+        queued += n;
       }
+      HIPCHK(hipEventSynchronize(E.poll_ev[head]));
+      rem = expected(hb[head]);
+      head ^= 1;
+      --inflight;
     }
-    HIPCHK(hipStreamSynchronize(s));
+    if (inflight > 0) HIPCHK(hipStreamSynchronize(s));
   }
   // finish: project the last accepted y5 and move k7 into k1
   HIPCHK(launch_begin<T>(gs, epi_slot<T>(E, 8), s));
-  HIPCHK(hipMemcpyAsync(E.hctl, E.ctl, sizeof(DevCtl) * n_total, hipMemcpyDeviceToHost, s));
+  HIPCHK(launch_get(E.hctl, E.ctl, sizeof(DevCtl) * n_total, s));
   HIPCHK(hipStreamSynchronize(s));
   status.assign(n_total, MM_OK);
   mm_status worst = MM_OK;
@@ -1791,7 +1854,7 @@ mm_status neb_impl(mm_plan* p, const mm_params* q, void* images, int n_img, doub
   };
   // two iterations per captured graph (A -> B -> A)
   hipGraphExec_t ge = nullptr;
-  if (n_iter >= 2) {
+  if (n_iter >= 64) {  // shorter runs launch their kernels one by one (a capture costs about 0.5 ms)
     HIPCHK(hipStreamBeginCapture(E.cap, hipStreamCaptureModeThreadLocal));
     mm_status cs = iteration(A, B, E.cap);
     if (cs == MM_OK) cs = iteration(B, A, E.cap);
@@ -1806,6 +1869,11 @@ mm_status neb_impl(mm_plan* p, const mm_params* q, void* images, int n_img, doub
   long long it = 0;
   mm_status st = MM_OK;
   for (; it + 2 <= n_iter && st == MM_OK; it += 2) {
+    if (!ge) {
+      st = iteration(A, B, s);
+      if (st == MM_OK) st = iteration(B, A, s);
+      continue;
+    }
     hipError_t ee = hipGraphLaunch(ge, s);
     if (ee != hipSuccess) st = fail(MM_E_HIP, hipGetErrorString(ee));
   }
@@ -1822,7 +1890,7 @@ mm_status neb_impl(mm_plan* p, const mm_params* q, void* images, int n_img, doub
     HIPCHK(launch_eval<T>(gs, epi_slot<T>(E, 2), MODE_FIELD_ENERGY, demag_on(E), s));
     HIPCHK(launch_energy_reduce(E.partial, n_img, bpi, E.e5, s));
   }
-  HIPCHK(hipMemcpyAsync(E.he5, E.e5, sizeof(double) * 5 * n_img, hipMemcpyDeviceToHost, s));
+  HIPCHK(launch_get(E.he5, E.e5, sizeof(double) * 5 * n_img, s));
   HIPCHK(hipStreamSynchronize(s));
   if (E_out)
     for (int n = 0; n < n_img; ++n) {

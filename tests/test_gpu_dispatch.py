@@ -87,3 +87,50 @@ def test_fused_yz_batch_with_films_fp64(mm):
         kern = F.DemagKernel(mesh)
         mo = dp45.run(lambda y: F.llg_rhs(y, mesh, op, kern), m0[i], dp45.State(h=2e-14, h_max=2e-14), t_end=t_end)
         assert np.max(np.abs(md[i].cpu().numpy() - mo)) <= 1e-9
+
+
+@pytest.mark.parametrize("steps", [1, 7, 8, 9, 17, 70])
+def test_run_submits_the_attempts_it_needs_fp64(mm, steps):
+    """A run of `steps` equal steps, submitted one by one (up to 63 expected) or
+    in graphs of eight and a rest (70), against as many single attempts: the
+    same kernels, so the same bits, and no attempt more or less."""
+    mesh = (16, 12, 1, 2e-9, 2e-9, 2e-9)
+    gp = gpu_params(mm, PAR, F.ALL_TERMS)
+    plan = mm.Plan(mesh, "f64", terms=F.ALL_TERMS)
+    m0 = inputs.add_noise(inputs.s_state(*mesh[:4]), 1e-2, np.random.default_rng(5))
+    h = 1e-14
+    a, b = to_dev(m0, torch.float64), to_dev(m0, torch.float64)
+    sa, sb = mm.new_states(1, h=h, h_max=h), mm.new_states(1, h=h, h_max=h)
+    for t_end in (steps * h, 2 * steps * h):
+        plan.rk45_run(gp, a, sa, t_end=t_end)
+        for _ in range(steps):  # one attempt a call, to the same end (the last step is what is left to it)
+            plan.rk45_run(gp, b, sb, t_end=t_end, max_steps=1, check=False)
+        assert sa[0].n_accept == sb[0].n_accept == round(t_end / h) and sa[0].n_reject == 0
+        assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("n", [1, 12, 60])
+def test_parameter_tables_follow_every_call(mm, n):
+    """The device tables are sent when their bytes change (one kernel argument,
+    several, and a copy for 60 instances): parameters, arrays, batch sizes and
+    streams changed from call to call on one plan, each result bit for bit that
+    of a fresh plan."""
+    mesh = (8, 6, 1, 2e-9, 2e-9, 2e-9)
+    plan = mm.Plan(mesh, "f64", terms=F.ALL_TERMS, max_batch=n)
+    m = [to_dev(np.stack([_m(mesh, 50 + 100 * k + i) for i in range(n)]), torch.float64) for k in range(2)]
+    side = torch.cuda.Stream()
+
+    def pars(seed):
+        r = np.random.default_rng(seed)
+        return [gpu_params(mm, dict(PAR, Ms=r.uniform(4e5, 9e5), A=r.uniform(5e-12, 2e-11)), F.ALL_TERMS)
+                for _ in range(n)]
+
+    for seed, k, nb, other in ((1, 0, n, False), (1, 0, n, False), (1, 1, n, False), (2, 1, n, False), (1, 0, 1, False),
+                               (1, 0, n, True), (1, 0, n, False), (2, 0, n, True)):
+        p = pars(seed)[:nb]
+        fresh = mm.Plan(mesh, "f64", terms=F.ALL_TERMS, max_batch=n).llg_rhs(p, m[k][:nb])
+        torch.cuda.synchronize()
+        with torch.cuda.stream(side if other else torch.cuda.current_stream()):
+            got = plan.llg_rhs(p, m[k][:nb])
+        torch.cuda.synchronize()
+        assert torch.equal(got, fresh)
