@@ -116,10 +116,60 @@ __device__ __forceinline__ void dft16(Cx<T>* v) {
   }
 }
 
+// 6 points as 2 x 3 (coprime, so no twiddles): length-3 transforms of
+// x[0, 2, 4] and x[3, 5, 1], whose sums and differences are the outputs
+// 0, 4, 2 and 3, 1, 5.
+template <typename T, bool INV>
+__device__ __forceinline__ void dft6(Cx<T>* v) {
+  Cx<T> a[3] = {v[0], v[2], v[4]};
+  Cx<T> b[3] = {v[3], v[5], v[1]};
+  dft3<T, INV>(a);
+  dft3<T, INV>(b);
+  v[0] = cadd(a[0], b[0]);
+  v[3] = csub(a[0], b[0]);
+  v[4] = cadd(a[1], b[1]);
+  v[1] = csub(a[1], b[1]);
+  v[2] = cadd(a[2], b[2]);
+  v[5] = csub(a[2], b[2]);
+}
+
+// 9 points as 3 x 3: length-3 transforms over n1 of x[3 n1 + n2], twiddles
+// W9^(n2 k1), length-3 transforms over n2; output in natural order.
+template <typename T, bool INV>
+__device__ __forceinline__ void dft9(Cx<T>* v) {
+  // cos, sin of 2 pi / 9, 4 pi / 9, 8 pi / 9
+  const T c[3] = {T(0.76604444311897803520239265055542), T(0.17364817766693034885171662676931),
+                  T(-0.93969262078590838405410927732473)};
+  const T s[3] = {T(0.64278760968653932632264340990726), T(0.98480775301220805936674302458952),
+                  T(0.34202014332566873304409961468226)};
+  auto tw = [&](Cx<T> x, int m) -> Cx<T> {  // x exp(-+ 2 pi i / 9 {1, 2, 4}), m the place in the tables
+    const T w = INV ? s[m] : -s[m];
+    return Cx<T>{x.x * c[m] - x.y * w, x.x * w + x.y * c[m]};
+  };
+  Cx<T> a[3][3];
+#pragma unroll
+  for (int n2 = 0; n2 < 3; ++n2) {
+    a[n2][0] = v[n2]; a[n2][1] = v[3 + n2]; a[n2][2] = v[6 + n2];
+    dft3<T, INV>(a[n2]);
+  }
+  a[1][1] = tw(a[1][1], 0);
+  a[1][2] = tw(a[1][2], 1);
+  a[2][1] = tw(a[2][1], 1);
+  a[2][2] = tw(a[2][2], 2);
+#pragma unroll
+  for (int k1 = 0; k1 < 3; ++k1) {
+    Cx<T> b[3] = {a[0][k1], a[1][k1], a[2][k1]};
+    dft3<T, INV>(b);
+    v[k1] = b[0]; v[k1 + 3] = b[1]; v[k1 + 6] = b[2];
+  }
+}
+
 template <typename T, int R, bool INV>
 __device__ __forceinline__ void dftR(Cx<T>* v) {
   if constexpr (R == 2) dft2<T, INV>(v);
   else if constexpr (R == 3) dft3<T, INV>(v);
+  else if constexpr (R == 6) dft6<T, INV>(v);
+  else if constexpr (R == 9) dft9<T, INV>(v);
   else if constexpr (R == 4) dft4<T, INV>(v);
   else if constexpr (R == 8) dft8<T, INV>(v);
   else dft16<T, INV>(v);
@@ -364,17 +414,18 @@ __device__ __forceinline__ void fft_run(Cx<T>* lds, const FftDesc<T>& p, const C
 // shortens each stage where a transform has few columns to share the CU):
 // every index, stride and LDS offset is a constant and no butterfly is
 // predicated, which keeps the kernels that use it small in registers.
-template <typename T, int R, int L, int NS, int SH, int EPT, bool INV, bool GIN, bool GOUT, bool TWL, bool HIN,
-          bool HOUT, class Load, class Store, class Hook>
+// TPC threads a column, NB butterflies each, the last one of some threads past
+// the end where they do not divide.  CHK: ends read and written with the
+// callers' bounds checks (shorter data than the half or whole length).
+template <typename T, int R, int L, int NS, int SH, int TPC, bool INV, bool GIN, bool GOUT, bool TWL, bool HIN,
+          bool HOUT, bool CHK, class Load, class Store, class Hook>
 __device__ __forceinline__ void fft_stage_s(Cx<T>* __restrict__ col, int c, int lane, bool active,
                                             const Cx<T>* __restrict__ tw, Load& ld, Store& st, Hook& hook) {
   static_assert(!(HIN || HOUT) || R % 2 == 0, "half-length ends need an even radix");
   constexpr bool FIRST = NS == 1;
-  static_assert(R <= EPT, "a butterfly fits the entries of one thread");
-  constexpr int TPC = L / EPT;
-  constexpr int NB = EPT / R;
   constexpr int NBF = L / R;
-  static_assert(NB * TPC == NBF, "L/EPT threads cover every butterfly");
+  constexpr int NB = (NBF + TPC - 1) / TPC;
+  constexpr bool EVEN_SPLIT = NB * TPC == NBF;
   constexpr int RI = HIN ? R / 2 : R;
   constexpr int RO = HOUT ? R / 2 : R;
   constexpr int NBP = NBF + (NBF >> SH);
@@ -385,9 +436,10 @@ __device__ __forceinline__ void fft_stage_s(Cx<T>* __restrict__ col, int c, int 
 #pragma unroll
     for (int k = 0; k < NB; ++k) {
       const int j = lane + k * TPC;
+      if (!EVEN_SPLIT && j >= NBF) continue;
       if constexpr (GIN) {
 #pragma unroll
-        for (int r = 0; r < RI; ++r) v[k][r] = ld.template get<!HIN>(c, j + r * NBF);
+        for (int r = 0; r < RI; ++r) v[k][r] = ld.template get<!HIN || CHK>(c, j + r * NBF);
       } else {
         const int a = j + (j >> SH);
 #pragma unroll
@@ -403,13 +455,14 @@ __device__ __forceinline__ void fft_stage_s(Cx<T>* __restrict__ col, int c, int 
 #pragma unroll
     for (int k = 0; k < NB; ++k) {
       const int j = lane + k * TPC;
+      if (!EVEN_SPLIT && j >= NBF) continue;
       const int q = j / NS, kk = j % NS;
       if constexpr (!FIRST) twiddle_powers<T, R, INV, TWL>(v[k], tw, kk * TSTEP);
       dftR<T, R, INV>(v[k]);
       const int base = q * NS * R + kk;
       if constexpr (GOUT) {
 #pragma unroll
-        for (int r = 0; r < RO; ++r) st.template put<!HOUT>(c, base + r * NS, v[k][r]);
+        for (int r = 0; r < RO; ++r) st.template put<!HOUT || CHK>(c, base + r * NS, v[k][r]);
       } else if constexpr (FIRST) {
         const int a = base + (base >> SH);
 #pragma unroll
@@ -433,7 +486,8 @@ __device__ __forceinline__ void fft_static_from(Cx<T>* col, int c, int lane, boo
   constexpr int R = p2_radix(A, A16, S);
   constexpr int SH = p2_psh(L, A16);
   constexpr bool FIRST = S == 0, LAST = S == NST - 1;
-  fft_stage_s<T, R, L, NS, SH, EPT, INV, GIN && FIRST, GOUT && LAST, TWL, HIN && FIRST, HOUT && LAST>(
+  static_assert(R <= EPT && L % EPT == 0, "a butterfly fits the entries of one thread");
+  fft_stage_s<T, R, L, NS, SH, L / EPT, INV, GIN && FIRST, GOUT && LAST, TWL, HIN && FIRST, HOUT && LAST, false>(
       col, c, lane, active, tw, ld, st, hook);
   if constexpr (!LAST) {
     NoHook nh;
@@ -456,6 +510,37 @@ __device__ __forceinline__ void fft_static(Cx<T>* lds, const Cx<T>* tw, int cs, 
   Cx<T>* col = lds + (active ? c : 0) * cs;
   fft_static_from<T, L, A16, EPT, INV, GIN, GOUT, TWL, HIN, HOUT, 0, 1>(col, c, lane, active, tw, ld, st, hook);
 }
+
+// The transform compiled for a 3-smooth length (sr_plan, sr_tpc threads a
+// column).  HIN / HOUT: at most L/2 inputs / outputs; taken where the plan's end
+// radix is even, with CHK always (the data may be shorter than L/2).
+template <typename T, int L, bool INV, bool GIN, bool GOUT, bool TWL, bool HIN, bool HOUT, bool CHK, int S, int NS,
+          class Load, class Store, class Hook>
+__device__ __forceinline__ void fft_mix_from(Cx<T>* col, int c, int lane, bool active, const Cx<T>* tw, Load& ld,
+                                             Store& st, Hook& hook) {
+  constexpr SrPlan P = sr_plan(L);
+  constexpr int R = P.rad[S];
+  constexpr bool FIRST = S == 0, LAST = S == P.nst - 1;
+  fft_stage_s<T, R, L, NS, sr_psh(L), sr_tpc(L), INV, GIN && FIRST, GOUT && LAST, TWL, HIN && FIRST && R % 2 == 0,
+              HOUT && LAST && R % 2 == 0, CHK>(col, c, lane, active, tw, ld, st, hook);
+  if constexpr (!LAST) {
+    NoHook nh;
+    fft_mix_from<T, L, INV, false, GOUT, TWL, false, HOUT, CHK, S + 1, NS * R>(col, c, lane, active, tw, ld, st, nh);
+  }
+}
+template <typename T, int L, bool INV, bool GIN, bool GOUT, bool TWL, bool HIN, bool HOUT, bool CHK, class Load,
+          class Store, class Hook>
+__device__ __forceinline__ void fft_mix(Cx<T>* lds, const Cx<T>* tw, int cs, int ncol, Load ld, Store st, Hook hook) {
+  static_assert(sr_plan(L).nst >= 2, "two stages and more");
+  constexpr int TPC = sr_tpc(L);
+  const int c = (int)threadIdx.x / TPC;
+  const int lane = (int)threadIdx.x - c * TPC;
+  const bool active = c < ncol;
+  Cx<T>* col = lds + (active ? c : 0) * cs;
+  fft_mix_from<T, L, INV, GIN, GOUT, TWL, HIN, HOUT, CHK, 0, 1>(col, c, lane, active, tw, ld, st, hook);
+}
+// Whether the plan of L leaves the upper half of its input unread
+constexpr bool mix_hin(int L) { return sr_plan(L).rad[0] % 2 == 0; }
 
 // Loads / stores that are never called (LDS input or output)
 template <typename T>

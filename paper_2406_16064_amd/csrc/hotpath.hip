@@ -26,6 +26,18 @@ extern template void inv_x_launch<double, false, false>(int, int, bool, const La
                                                        hipStream_t);
 extern template void inv_x_launch<double, false, true>(int, int, bool, const Launch<double>&, long long, int, size_t,
                                                        hipStream_t);
+extern template void fwd_x_launch_m<float>(int, const Launch<float>&, long long, int, size_t, hipStream_t);
+extern template void y_launch_m<float>(bool, int, const Launch<float>&, long long, int, size_t, hipStream_t);
+extern template void inv_x_launch_s<float, false, false>(int, int, int, bool, const Launch<float>&, long long, int,
+                                                         size_t, hipStream_t);
+extern template void inv_x_launch_s<float, false, true>(int, int, int, bool, const Launch<float>&, long long, int,
+                                                         size_t, hipStream_t);
+extern template void fwd_x_launch_m<double>(int, const Launch<double>&, long long, int, size_t, hipStream_t);
+extern template void y_launch_m<double>(bool, int, const Launch<double>&, long long, int, size_t, hipStream_t);
+extern template void inv_x_launch_s<double, false, false>(int, int, int, bool, const Launch<double>&, long long, int,
+                                                         size_t, hipStream_t);
+extern template void inv_x_launch_s<double, false, true>(int, int, int, bool, const Launch<double>&, long long, int,
+                                                         size_t, hipStream_t);
 extern template void yzy_launch<float>(int, int, const Launch<float>&, long long, int, size_t, hipStream_t);
 extern template void yzy_launch<double>(int, int, const Launch<double>&, long long, int, size_t, hipStream_t);
 
@@ -453,6 +465,22 @@ int inv_cpt(const GroupSet<T>& gs, int nt) {
   return 0;
 }
 
+// Length of the inverse-x kernel compiled for one Lx (inv_x_launch_s), 0 for the
+// general one: every group has that Lx, a power of two (whose plan is the general
+// kernel's, so that a mesh gives the same bits alone and in a batch of others),
+// the workgroup holds its columns' threads, one or two cells a thread, and the
+// mode is one it is compiled for (a stage without the next forward pass is not).
+template <typename T>
+int inv_x_static(const GroupSet<T>& gs, int nt, int cpt, int mode, bool fuse) {
+  if (cpt != 1 && cpt != 2) return 0;
+  if (mode == MODE_STAGE && !fuse) return 0;
+  const int L = gs.h[0].g.Lx;
+  if ((L & (L - 1)) != 0 || (!sr_compiled(L) && L != 1024)) return 0;
+  for (int i = 0; i < gs.n; ++i)
+    if (gs.h[i].g.Lx != L || 3 * gs.h[i].tu.ty_x * sr_tpc(L) > nt) return 0;
+  return L;
+}
+
 template <typename T>
 bool eval_fusable(const GroupSet<T>& gs) {
   int nt = 64;
@@ -490,12 +518,22 @@ int static_y(const GroupSet<T>& gs, bool inv, int& nt, int& ept, const bool* use
 }
 
 // The y passes launch once per length with a compiled transform (Py = 2 ny of
-// 256 to 2048) among the groups, and once for the rest (the general
-// transform): key of group i, 0 for the general kernels.
+// 256 to 2048, or kMixKey + Py for the other lengths of fft_mix) among the
+// groups, and once for the rest (the general transform): key of group i, 0 for
+// the general kernels.
+constexpr int kMixKey = 4096;
 template <typename T>
 int y_key(const HotPlan<T>& h) {
   const int L = h.g.Py;
-  return L == 2 * h.g.ny && (L == 256 || L == 512 || L == 1024 || L == 2048) ? L : 0;
+  if (L == 2 * h.g.ny && (L == 256 || L == 512 || L == 1024 || L == 2048)) return L;
+  if (!sr_compiled(L)) return 0;
+  const int cols = h.g.nz == 1 ? 3 * h.tu.cb_y2 : h.tu.cb_y;
+  return cols * sr_tpc(L) <= 512 && (h.g.nz == 1 || h.tu.cb_y <= kSxB) ? kMixKey + L : 0;
+}
+template <typename T>
+int mix_threads(const HotPlan<T>& h) {
+  const int cols = h.g.nz == 1 ? 3 * h.tu.cb_y2 : h.tu.cb_y;
+  return (cols * sr_tpc(h.g.Py) + 63) / 64 * 64;
 }
 
 // Pz / 2 where a 3-D group takes the fused y and z passes (k_yzy), 0 where it
@@ -538,14 +576,18 @@ hipError_t launch_eval(const GroupSet<T>& gs, const Epi<T>* epis, int mode, bool
   if (demag) {
     if (!skip_fwd && on(0)) {  // x forward (skipped when the previous stage's inverse-x pass did it)
       // one launch per static length (every group with an even nx = Lx of
-      // 128 to 1024 shares the kernel compiled for its Lx), one for the rest
-      auto x_key = [&](const Geo& g) {
-        return g.nx == g.Lx && (g.Lx == 128 || g.Lx == 256 || g.Lx == 512 || g.Lx == 1024) ? g.Lx : 0;
+      // 128 to 1024 shares the kernel compiled for its Lx; other row lengths of
+      // the list share the one of fft_mix, key 4096 + Lx, where the workgroup
+      // holds its threads), one for the rest
+      auto x_key = [&](const HotPlan<T>& h) {
+        const Geo& g = h.g;
+        if (g.nx == g.Lx && (g.Lx == 128 || g.Lx == 256 || g.Lx == 512 || g.Lx == 1024)) return g.Lx;
+        return sr_compiled(g.Lx) && h.tu.ty_f * sr_tpc(g.Lx) <= 512 ? 4096 + g.Lx : 0;
       };
       mark();
       int keys[kMaxGroups], nkeys = 0;
       for (int i = 0; i < gs.n; ++i) {
-        const int k = x_key(gs.h[i].g);
+        const int k = x_key(gs.h[i]);
         bool seen = false;
         for (int j = 0; j < nkeys; ++j) seen = seen || keys[j] == k;
         if (!seen) keys[nkeys++] = k;
@@ -556,13 +598,18 @@ hipError_t launch_eval(const GroupSet<T>& gs, const Epi<T>* epis, int mode, bool
         size_t lds = 0;
         for (int i = 0; i < gs.n; ++i) {
           const HotPlan<T>& h = gs.h[i];
-          const bool use = x_key(h.g) == keys[kk];
+          const bool use = x_key(h) == keys[kk];
           lb.set(i, use ? fwd_blocks(h.g, h.tu, h.batch) : 0);
           if (!use) continue;
-          nt = std::max(nt, h.tu.nt_f);
+          nt = std::max(nt, keys[kk] > 4096 ? (h.tu.ty_f * sr_tpc(h.g.Lx) + 63) / 64 * 64 : h.tu.nt_f);
           lds = std::max(lds, ((size_t)h.tu.ty_f * col_stride(h.g.Lx) + 2 * h.g.Lx + 1) * csz);
         }
+        if (lb.total == 0) continue;  // no instance of these meshes in this launch
         const dim3 grid((unsigned)lb.total);
+        if (keys[kk] > 4096) {
+          fwd_x_launch_m<T>(keys[kk] - 4096, lb.L, lb.total, nt, lds, s);
+          continue;
+        }
         switch (keys[kk]) {
           case 128: k_fwd_x<T, 128><<<grid, nt, lds, s>>>(lb.L); break;
           case 256: k_fwd_x<T, 256><<<grid, nt, lds, s>>>(lb.L); break;
@@ -582,7 +629,7 @@ hipError_t launch_eval(const GroupSet<T>& gs, const Epi<T>* epis, int mode, bool
         key_of[i] = 32 * y_key(h) + yzy_m<T>(h);
         for (int j = 0; j < gs.n && h.g.nz == 1; ++j) {
           const int m = yzy_m<T>(gs.h[j]), sl = y_key(h);
-          if (m == 0 || y_key(gs.h[j]) != sl || gs.h[j].batch == 0) continue;
+          if (m == 0 || y_key(gs.h[j]) != sl || gs.h[j].batch == 0 || sl > kMixKey) continue;
           if (3 * h.tu.cb_y2 * (sl / 8) <= 512) key_of[i] = 32 * sl + m;
           break;
         }
@@ -614,7 +661,13 @@ hipError_t launch_eval(const GroupSet<T>& gs, const Epi<T>* epis, int mode, bool
         }
         if (!use[i]) continue;
         const int cols = 3 * (h.g.nz == 1 ? h.tu.cb_y2 : h.g.nz);  // fused launches
-        nt = std::max(nt, m > 0 ? std::min(512, cols * (keys[kk] / 32 / 8)) : h.tu.nt_y);
+        nt = std::max(nt, m > 0 ? std::min(512, cols * (keys[kk] / 32 / 8))
+                          : keys[kk] / 32 > kMixKey ? mix_threads(h) : h.tu.nt_y);
+      }
+      if (lb.total == 0) continue;
+      if (keys[kk] / 32 > kMixKey) {
+        y_launch_m<T>(false, keys[kk] / 32 - kMixKey, lb.L, lb.total, nt, lds, s);
+        continue;
       }
       if (m > 0) {
         yzy_launch<T>(m, keys[kk] / 32, lb.L, lb.total, nt, lds, s);
@@ -669,6 +722,7 @@ hipError_t launch_eval(const GroupSet<T>& gs, const Epi<T>* epis, int mode, bool
           // one XCD and its L2
           lb.set(j, use ? (nb + 7) / 8 * 8 : 0);
         }
+        if (lb.total == 0) continue;
         if (kind == 0) z_pair_dispatch<T>(hi.g.Pz, lb.L, lb.total, s);
         else if (kind == 3) zs_dispatch<T>(hi.g.Pz, lb.L, lb.total, s);
         else z_reg_dispatch<T>(hi.g.Pz, lb.L, lb.total, half, s);
@@ -685,7 +739,7 @@ hipError_t launch_eval(const GroupSet<T>& gs, const Epi<T>* epis, int mode, bool
           lds = std::max(lds, (size_t)3 * h.tu.qz * col_stride(h.g.Pz) * csz);
         }
       }
-      if (nt > 0 && on(2)) k_z3d<T><<<dim3((unsigned)lz.total), nt, lds, s>>>(lz.L);
+      if (nt > 0 && lz.total > 0 && on(2)) k_z3d<T><<<dim3((unsigned)lz.total), nt, lds, s>>>(lz.L);
       // y inverse (3-D groups), one launch per key as the forward pass
       mark();
       int keys[kMaxGroups], nkeys = 0;
@@ -706,9 +760,14 @@ hipError_t launch_eval(const GroupSet<T>& gs, const Epi<T>* epis, int mode, bool
         usey[j] = h.g.nz > 1 && yzy_m<T>(h) == 0 && y_key(h) == keys[kk];
         ly.set(j, usey[j] ? y3d_blocks(h.g, h.tu, h.batch) : 0);
         if (usey[j]) {
-          nty = std::max(nty, h.tu.nt_y);
+          nty = std::max(nty, keys[kk] > kMixKey ? mix_threads(h) : h.tu.nt_y);
           ldsy = std::max(ldsy, (size_t)h.tu.cb_y * col_stride(h.g.Py) * csz);
         }
+      }
+      if (ly.total == 0) continue;
+      if (keys[kk] > kMixKey) {
+        y_launch_m<T>(true, keys[kk] - kMixKey, ly.L, ly.total, nty, ldsy, s);
+        continue;
       }
       int nts = 0, ept = 16;
       const dim3 gridy((unsigned)ly.total);
@@ -747,6 +806,9 @@ hipError_t launch_eval(const GroupSet<T>& gs, const Epi<T>* epis, int mode, bool
     if (gen) {
       if (demag) inv_x_launch<T, true, true>(mode, cpt, fuse, lb.L, lb.total, nt, lds, s);
       else inv_x_launch<T, false, true>(mode, cpt, false, lb.L, lb.total, nt, 0, s);
+    } else if (const int len = demag ? inv_x_static(gs, nt, cpt, mode, fuse) : 0; len > 0) {
+      if (len < 256) inv_x_launch_s<T, false, false>(len, mode, cpt, fuse, lb.L, lb.total, nt, lds, s);
+      else inv_x_launch_s<T, false, true>(len, mode, cpt, fuse, lb.L, lb.total, nt, lds, s);
     } else {
       if (demag) inv_x_launch<T, true, false>(mode, cpt, fuse, lb.L, lb.total, nt, lds, s);
       else inv_x_launch<T, false, false>(mode, cpt, false, lb.L, lb.total, nt, 0, s);

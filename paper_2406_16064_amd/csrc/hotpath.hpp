@@ -176,8 +176,9 @@ struct XRowLoad {
 };
 
 // SLX: 0 for any group, else the one length Lx of every group, all with an
-// even nx = Lx (a kernel holding one static transform keeps fewer registers).
-template <typename T, int SLX>
+// even nx = Lx (a kernel holding one static transform keeps fewer registers);
+// MIX: any nx, the transform of fft_mix (sr_tpc(SLX) threads a row).
+template <typename T, int SLX, bool MIX = false>
 __global__ void __launch_bounds__(512) k_fwd_x(Launch<T> L) {
   extern __shared__ __align__(16) unsigned char smem[];
   Cx<T>* lds = reinterpret_cast<Cx<T>*>(smem);
@@ -199,7 +200,7 @@ __global__ void __launch_bounds__(512) k_fwd_x(Launch<T> L) {
   const int y0 = tile * TY;
   const int nrow = g.ny - y0 < TY ? g.ny - y0 : TY;
   const int cs = col_stride(g.Lx);
-  const int sh = hp.fd[0].psh;
+  const int sh = MIX ? sr_psh(SLX > 0 ? SLX : 32) : hp.fd[0].psh;
   // LDS: TY columns, then the twiddle table (Lx) and the post factors (Lx + 1)
   Cx<T>* const twl = lds + TY * cs;
   Cx<T>* const postl = twl + g.Lx;
@@ -214,6 +215,9 @@ __global__ void __launch_bounds__(512) k_fwd_x(Launch<T> L) {
   // all nx / 2 packed inputs present and the rest zero when nx = Lx (even)
   const bool hin = ld.pairs && g.nx == g.Lx;
   const NoStore<T> nst;
+  if constexpr (MIX) {
+    fft_mix<T, SLX, false, true, false, true, true, false, true>(lds, twl, cs, nrow, ld, nst, hook);
+  } else {
   // compiled for the power-of-two lengths (L/8 threads a row where the
   // workgroup has them, else L/16)
   const bool e8 = nrow * (g.Lx / 8) <= (int)blockDim.x;
@@ -233,6 +237,7 @@ __global__ void __launch_bounds__(512) k_fwd_x(Launch<T> L) {
                                              nst, hook);
   }
 #undef MMX_FS
+  }
   // real-to-complex post-processing: X[k] of row r
   auto post = [&](int r, int k) -> Cx<T> {
     const Cx<T> Zk = lds[r * cs + pidx(k == g.Lx ? 0 : k, sh)];
@@ -407,8 +412,9 @@ struct ColStoreS {
   }
 };
 
-// SL > 0: compiled for Py = SL = 2 ny (fft_static, SL/EPT threads a column).
-template <typename T, bool R16, int SL = 0, int EPT = 16>
+// SL > 0: compiled for Py = SL = 2 ny (fft_static, SL/EPT threads a column), or
+// with MIX for Py = SL of any ny (fft_mix, sr_tpc(SL) threads a column).
+template <typename T, bool R16, int SL = 0, int EPT = 16, bool MIX = false>
 __device__ __forceinline__ void y_fused2d(const HotPlan<T>& hp, const Epi<T>& ep, long long bid0, Cx<T>* lds) {
   const Geo& g = hp.g;
   const int CB = hp.tu.cb_y2;
@@ -428,7 +434,7 @@ __device__ __forceinline__ void y_fused2d(const HotPlan<T>& hp, const Epi<T>& ep
   const int cs = col_stride(g.Py);
   const int sh = hp.fd[1].psh;
   const int Xp = g.Xp, ny = g.ny;
-  const int tpc = SL > 0 ? SL / EPT : blockDim.x / (3 * CB);
+  const int tpc = MIX ? sr_tpc(SL) : SL > 0 ? SL / EPT : (int)blockDim.x / (3 * CB);
   // this thread's column, in Sx = [3][1][Xp][ny] of the instance
   const int mc = (int)threadIdx.x / tpc;
   const int cc = mc < ncol ? mc : 0;
@@ -459,7 +465,10 @@ __device__ __forceinline__ void y_fused2d(const HotPlan<T>& hp, const Epi<T>& ep
     if (ktlds && packed) ktabN.store(ktlN);
   };
   const bool half = g.Py == 2 * ny;  // ny inputs / outputs of Py points
-  if constexpr (SL > 0)
+  if constexpr (MIX)
+    fft_mix<T, SL, false, true, false, true, true, false, true>(lds, twl, cs, ncol, ColLoad2<T>{base, coff, coff2, ny},
+                                                                NoStore<T>{}, hook);
+  else if constexpr (SL > 0)
     fft_static<T, SL, (EPT > 8), false, true, false, true, true, false, EPT>(
         lds, twl, cs, ncol, ColLoad2<T>{base, coff, coff2, ny}, NoStore<T>{}, hook);
   else
@@ -474,7 +483,7 @@ __device__ __forceinline__ void y_fused2d(const HotPlan<T>& hp, const Epi<T>& ep
   const size_t kgs = (size_t)g.Kz * g.Xp * g.Ky;
   auto kent = [&](int a, int o) -> T { return ktlds ? ktl[a * seg + o] : gld(ktg + a * kgs + o); };
   const FDiv dpy = fdiv_of(g.Py);
-  const int psh = SL > 0 ? p2_psh(SL, EPT > 8) : sh;
+  const int psh = MIX ? sr_psh(SL) : SL > 0 ? p2_psh(SL, EPT > 8) : sh;
   for (int t = threadIdx.x; t < ncb * g.Py; t += blockDim.x) {
     const int jj = fdiv_q(t, dpy), ky = t - mul24(jj, g.Py);
     if (packed && jj == 0) continue;  // below
@@ -483,7 +492,7 @@ __device__ __forceinline__ void y_fused2d(const HotPlan<T>& hp, const Epi<T>& ep
     const int o = jj * g.Ky + kyf;
     const T kxx = kent(0, o) * s, kyy = kent(1, o) * s, kzz = kent(2, o) * s;
     const T kxy = kent(3, o) * (s * sy);
-    const int p = pidx(ky, SL > 0 ? p2_psh(SL, EPT > 8) : sh);
+    const int p = pidx(ky, psh);
     Cx<T>& m0 = spec[(0 * ncb + jj) * cs + p];
     Cx<T>& m1 = spec[(1 * ncb + jj) * cs + p];
     Cx<T>& m2 = spec[(2 * ncb + jj) * cs + p];
@@ -540,7 +549,10 @@ __device__ __forceinline__ void y_fused2d(const HotPlan<T>& hp, const Epi<T>& ep
     }
   }
   __syncthreads();
-  if constexpr (SL > 0)
+  if constexpr (MIX)
+    fft_mix<T, SL, true, false, true, true, false, true, true>(lds, twl, cs, ncol, NoLoad<T>{},
+                                                               ColStore2<T>{base, coff, coff2, ny}, NoHook{});
+  else if constexpr (SL > 0)
     fft_static<T, SL, (EPT > 8), true, false, true, true, false, true, EPT>(
         lds, twl, cs, ncol, NoLoad<T>{}, ColStore2<T>{base, coff, coff2, ny}, NoHook{});
   else
@@ -557,7 +569,8 @@ __device__ __forceinline__ void y_fused2d(const HotPlan<T>& hp, const Epi<T>& ep
 // transforms into LDS and copies the first ny entries of each column back the
 // same way).  Sy [3][nz][Xp][Py] is read and written
 // row by row by the transform itself.
-template <typename T, bool INV, bool R16, int SL = 0, int EPT = 16>
+// MIX as for y_fused2d (tiles inside one kx block only).
+template <typename T, bool INV, bool R16, int SL = 0, int EPT = 16, bool MIX = false>
 __device__ __forceinline__ void y_rows3d(const HotPlan<T>& hp, const Epi<T>& ep, long long bid0, Cx<T>* lds) {
   const Geo& g = hp.g;
   const int CB = hp.tu.cb_y;
@@ -575,11 +588,11 @@ __device__ __forceinline__ void y_rows3d(const HotPlan<T>& hp, const Epi<T>& ep,
   // Sx blocks kx0 / kSxB ... of this plane; Sy rows cz Xp + kx0 + i
   Cx<T>* const sx = hp.Sx + (size_t)b * g.sx + (size_t)cz * g.XB * kSxB * ny + (size_t)kx0 * ny;
   Cx<T>* const sy = hp.Sy + (size_t)b * g.sy + ((size_t)cz * g.Xp + kx0) * g.Py;
-  const int tpc = SL > 0 ? SL / EPT : (int)blockDim.x / CB;
+  const int tpc = MIX ? sr_tpc(SL) : SL > 0 ? SL / EPT : (int)blockDim.x / CB;
   const int c = (int)threadIdx.x / tpc;
   const int cc = c < ncol ? c : 0;
   const bool half = g.Py == 2 * ny;
-  if (CB <= kSxB) {
+  if (MIX || CB <= kSxB) {
     Cx<T>* const sxp = hp.Sx + (size_t)b * g.sx + (size_t)cz * g.XB * kSxB * ny;  // plane
     const int kxc = kx0 + cc;
     const uint32_t coff = (uint32_t)((kxc >> 2) * kSxB * ny + (kxc & 3)) * (uint32_t)sizeof(Cx<T>);
@@ -588,7 +601,9 @@ __device__ __forceinline__ void y_rows3d(const HotPlan<T>& hp, const Epi<T>& ep,
     if constexpr (!INV) {
       const ColLoadS<T> ld{sxp, coff, sb, ny};
       const ColStore<T> st{sy, yoff, g.Py};
-      if constexpr (SL > 0)
+      if constexpr (MIX)
+        fft_mix<T, SL, false, true, true, false, true, false, true>(lds, hp.fd[1].tw, cs, ncol, ld, st, NoHook{});
+      else if constexpr (SL > 0)
         fft_static<T, SL, (EPT > 8), false, true, true, false, true, false, EPT>(lds, hp.fd[1].tw, cs, ncol, ld, st, NoHook{});
       else
         fft_run<T, false, true, true, false, R16>(lds, hp.fd[1], hp.fd[1].tw, cs, ncol, tpc, half, false, ld, st,
@@ -596,7 +611,9 @@ __device__ __forceinline__ void y_rows3d(const HotPlan<T>& hp, const Epi<T>& ep,
     } else {
       const ColLoad<T> ld{sy, yoff, g.Py};
       const ColStoreS<T> st{sxp, coff, sb, ny};
-      if constexpr (SL > 0)
+      if constexpr (MIX)
+        fft_mix<T, SL, true, true, true, false, false, true, true>(lds, hp.fd[1].tw, cs, ncol, ld, st, NoHook{});
+      else if constexpr (SL > 0)
         fft_static<T, SL, (EPT > 8), true, true, true, false, false, true, EPT>(lds, hp.fd[1].tw, cs, ncol, ld, st, NoHook{});
       else
         fft_run<T, true, true, true, false, R16>(lds, hp.fd[1], hp.fd[1].tw, cs, ncol, tpc, false, half, ld, st,
@@ -604,6 +621,7 @@ __device__ __forceinline__ void y_rows3d(const HotPlan<T>& hp, const Epi<T>& ep,
     }
     return;
   }
+  if constexpr (!MIX) {
   // entry t of the staged blocks: column i = kSxB (t / (kSxB ny)) + t % kSxB, row
   // (t / kSxB) % ny; the tile's blocks (ncol rounded up) are contiguous from sx
   const int nblk = (ncol + kSxB - 1) / kSxB;
@@ -651,6 +669,7 @@ __device__ __forceinline__ void y_rows3d(const HotPlan<T>& hp, const Epi<T>& ep,
       if (i < ncol) gsto(sx, (uint32_t)t * (uint32_t)sizeof(Cx<T>), lds[i * cs + pidx(y, sh)]);
     }
   }
+  }  // !MIX
 }
 
 // ---------------------------------------------------------------------------
@@ -795,6 +814,37 @@ __global__ void __launch_bounds__(512) k_yinv_s(Launch<T> L) {
   const HotPlan<T> hp = hot_plan(L, gi);
   if (bid >= y3d_blocks(hp.g, hp.tu, hp.batch)) return;
   y_rows3d<T, true, false, SL, EPT>(hp, ldu(L.epis + gi), bid, lds);
+}
+
+// The y passes compiled for one 3-smooth length: every group of the launch has
+// Py = SL, any ny, and 3-D tiles inside one kx block.  The run-time engine holds
+// every radix and both predicates a butterfly in one kernel: 160 registers in
+// FP32 (three waves a SIMD) and three times the time a point of these.
+template <typename T, int SL>
+__global__ void __launch_bounds__(512) k_ypass_m(Launch<T> L) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  Cx<T>* lds = reinterpret_cast<Cx<T>*>(smem);
+  long long bid;
+  const int gi = group_of(L, bid);
+  const HotPlan<T> hp = hot_plan(L, gi);
+  if (hp.g.nz == 1) {
+    if (bid >= y2d_blocks(hp.g, hp.tu, hp.batch)) return;
+    y_fused2d<T, false, SL, 8, true>(hp, ldu(L.epis + gi), bid, lds);
+  } else {
+    if (bid >= y3d_blocks(hp.g, hp.tu, hp.batch)) return;
+    y_rows3d<T, false, false, SL, 8, true>(hp, ldu(L.epis + gi), bid, lds);
+  }
+}
+
+template <typename T, int SL>
+__global__ void __launch_bounds__(512) k_yinv_m(Launch<T> L) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  Cx<T>* lds = reinterpret_cast<Cx<T>*>(smem);
+  long long bid;
+  const int gi = group_of(L, bid);
+  const HotPlan<T> hp = hot_plan(L, gi);
+  if (bid >= y3d_blocks(hp.g, hp.tu, hp.batch)) return;
+  y_rows3d<T, true, false, SL, 8, true>(hp, ldu(L.epis + gi), bid, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -1605,13 +1655,18 @@ __device__ __forceinline__ V3<T> ll_rhs(V3<T> m, V3<T> H, T g1, T g2) {
 // launch shapes give every column that many), the general plan otherwise.
 // Inverse: only the first half of the output is kept; forward: hin as for
 // fft_run (the input's upper half is zero and not read).
-template <typename T, bool INV>
+// SLX > 0: every group of the launch has Lx = SLX and sr_tpc(SLX) threads a column.
+template <typename T, bool INV, int SLX = 0>
 __device__ __forceinline__ void x_columns(Cx<T>* lds, const FftDesc<T>& p, int cs, int ncol, const Cx<T>* twl,
                                           bool hin) {
   constexpr bool HIN = !INV, HOUT = INV;
   const NoLoad<T> nl;
   const NoStore<T> nst;
   const NoHook nh;
+  if constexpr (SLX > 0) {
+    fft_mix<T, SLX, INV, false, false, true, HIN, HOUT, false>(lds, twl, cs, ncol, nl, nst, nh);
+    return;
+  }
   if (INV || hin) {
     // 8 entries per thread where the workgroup has the threads (shorter stages)
     const bool e8 = ncol * (p.L / 8) <= (int)blockDim.x;
@@ -1860,7 +1915,7 @@ __device__ __forceinline__ void energy_pass_end(const double (&esum)[5], double*
 // Ms, A_ij, D_ij, an empty cell gets no demag field either, energies weight
 // each cell by its Ms, and with cell arrays the fused forward transform takes
 // Ms m.
-template <typename T, bool DEMAG, int MODE, int CPT, bool FUSE, bool CELLS>
+template <typename T, bool DEMAG, int MODE, int CPT, bool FUSE, bool CELLS, int SLX>
 __global__ void __launch_bounds__(512) k_inv_x(Launch<T> L) {
   constexpr bool PREF = CPT == 1;
   static_assert(!FUSE || (MODE == MODE_STAGE && DEMAG && CPT > 0), "fused forward pass needs a stage epilogue");
@@ -1885,7 +1940,7 @@ __global__ void __launch_bounds__(512) k_inv_x(Launch<T> L) {
   const int y0 = tile * TY;
   const int nrow = g.ny - y0 < TY ? g.ny - y0 : TY;
   const int cs = col_stride(g.Lx);
-  const int sh = hp.fd[0].psh;
+  const int sh = SLX > 0 ? sr_psh(SLX > 0 ? SLX : 32) : hp.fd[0].psh;
 
   // Spectrum tile: column c * TY + r holds component c of row y0 + r (rows past
   // the mesh are left out: only the epilogue's rows are read back).
@@ -2010,7 +2065,7 @@ __global__ void __launch_bounds__(512) k_inv_x(Launch<T> L) {
     }
     __syncthreads();
     // the epilogue reads complex entries below ceil(nx / 2) <= Lx / 2 only
-    x_columns<T, true>(lds, hp.fd[0], cs, ncol, twl, false);
+    x_columns<T, true, SLX>(lds, hp.fd[0], cs, ncol, twl, false);
   }
 
   // ----- epilogue ----- (its arguments are read only now, which keeps the
@@ -2161,7 +2216,7 @@ __global__ void __launch_bounds__(512) k_inv_x(Launch<T> L) {
     // half-length input end, else 2 Lx)
     T* const re = reinterpret_cast<T*>(lds);
     const int rcs = 2 * cs;
-    const bool hin = (hp.fd[0].code & kFftFirstEven) && hp.fd[0].nst > 1;
+    const bool hin = SLX > 0 ? mix_hin(SLX > 0 ? SLX : 32) : (hp.fd[0].code & kFftFirstEven) && hp.fd[0].nst > 1;
     const int nz0 = (hin ? g.Lx : 2 * g.Lx) - g.nx;
     if (nz0 > 0) {
       const FDiv dz = fdiv_of(nz0);
@@ -2182,7 +2237,7 @@ __global__ void __launch_bounds__(512) k_inv_x(Launch<T> L) {
       }
     }
     __syncthreads();
-    x_columns<T, false>(lds, hp.fd[0], cs, ncol, twl, hin);
+    x_columns<T, false, SLX>(lds, hp.fd[0], cs, ncol, twl, hin);
     // real-to-complex post-processing and transposed store (the rows this
     // workgroup read at the start)
     // layouts as for the load at the start
@@ -2228,24 +2283,24 @@ __global__ void __launch_bounds__(512) k_inv_x(Launch<T> L) {
   }
 }
 
-template <typename T, bool DEMAG, int CPT, bool CELLS>
+template <typename T, bool DEMAG, int CPT, bool CELLS, int SLX>
 void inv_x_launch_c(int mode, bool fuse, const Launch<T>& L, long long total, int nt, size_t lds, hipStream_t s) {
   const dim3 grid((unsigned)total);
   switch (mode) {
-    case MODE_FIELD: k_inv_x<T, DEMAG, MODE_FIELD, CPT, false, CELLS><<<grid, nt, lds, s>>>(L); break;
-    case MODE_RHS: k_inv_x<T, DEMAG, MODE_RHS, CPT, false, CELLS><<<grid, nt, lds, s>>>(L); break;
+    case MODE_FIELD: k_inv_x<T, DEMAG, MODE_FIELD, CPT, false, CELLS, SLX><<<grid, nt, lds, s>>>(L); break;
+    case MODE_RHS: k_inv_x<T, DEMAG, MODE_RHS, CPT, false, CELLS, SLX><<<grid, nt, lds, s>>>(L); break;
     case MODE_STAGE:
       if constexpr (DEMAG && CPT > 0) {
         if (fuse) {
-          k_inv_x<T, DEMAG, MODE_STAGE, CPT, true, CELLS><<<grid, nt, lds, s>>>(L);
+          k_inv_x<T, DEMAG, MODE_STAGE, CPT, true, CELLS, SLX><<<grid, nt, lds, s>>>(L);
           break;
         }
       }
-      k_inv_x<T, DEMAG, MODE_STAGE, CPT, false, CELLS><<<grid, nt, lds, s>>>(L);
+      if constexpr (SLX == 0) k_inv_x<T, DEMAG, MODE_STAGE, CPT, false, CELLS, SLX><<<grid, nt, lds, s>>>(L);
       break;
-    case MODE_ERROR: k_inv_x<T, DEMAG, MODE_ERROR, CPT, false, CELLS><<<grid, nt, lds, s>>>(L); break;
-    case MODE_ENERGY: k_inv_x<T, DEMAG, MODE_ENERGY, CPT, false, CELLS><<<grid, nt, lds, s>>>(L); break;
-    default: k_inv_x<T, DEMAG, MODE_FIELD_ENERGY, CPT, false, CELLS><<<grid, nt, lds, s>>>(L); break;
+    case MODE_ERROR: k_inv_x<T, DEMAG, MODE_ERROR, CPT, false, CELLS, SLX><<<grid, nt, lds, s>>>(L); break;
+    case MODE_ENERGY: k_inv_x<T, DEMAG, MODE_ENERGY, CPT, false, CELLS, SLX><<<grid, nt, lds, s>>>(L); break;
+    default: k_inv_x<T, DEMAG, MODE_FIELD_ENERGY, CPT, false, CELLS, SLX><<<grid, nt, lds, s>>>(L); break;
   }
 }
 
@@ -2255,14 +2310,25 @@ template <typename T, bool DEMAG, bool CELLS>
 void inv_x_launch(int mode, int cpt, bool fuse, const Launch<T>& L, long long total, int nt, size_t lds,
                   hipStream_t s) {
   switch (cpt) {
-    case 1: inv_x_launch_c<T, DEMAG, 1, CELLS>(mode, fuse, L, total, nt, lds, s); break;
-    case 2: inv_x_launch_c<T, DEMAG, 2, CELLS>(mode, fuse, L, total, nt, lds, s); break;
-    case 4: inv_x_launch_c<T, DEMAG, 4, CELLS>(mode, fuse, L, total, nt, lds, s); break;
-    case 8: inv_x_launch_c<T, DEMAG, 8, CELLS>(mode, fuse, L, total, nt, lds, s); break;
-    default: inv_x_launch_c<T, DEMAG, 0, CELLS>(mode, false, L, total, nt, lds, s); break;
+    case 1: inv_x_launch_c<T, DEMAG, 1, CELLS, 0>(mode, fuse, L, total, nt, lds, s); break;
+    case 2: inv_x_launch_c<T, DEMAG, 2, CELLS, 0>(mode, fuse, L, total, nt, lds, s); break;
+    case 4: inv_x_launch_c<T, DEMAG, 4, CELLS, 0>(mode, fuse, L, total, nt, lds, s); break;
+    case 8: inv_x_launch_c<T, DEMAG, 8, CELLS, 0>(mode, fuse, L, total, nt, lds, s); break;
+    default: inv_x_launch_c<T, DEMAG, 0, CELLS, 0>(mode, false, L, total, nt, lds, s); break;
   }
 }
 
+// The same compiled for Lx = SLX (1 or 2 cells a thread; inv_x_static() says
+// where it applies).  The kernel above holds the transforms of every length and
+// takes 121 registers whatever its epilogue; compiled for one length it takes 83
+// with one cell a thread (144 above; 104 for 166 with a stage epilogue) and 60 to
+// 93 with two (122), five to eight waves a SIMD instead of three or four.
+template <typename T, bool CELLS, int SLX>
+void inv_x_launch_l(int mode, int cpt, bool fuse, const Launch<T>& L, long long total, int nt, size_t lds,
+                    hipStream_t s) {
+  if (cpt == 1) inv_x_launch_c<T, true, 1, CELLS, SLX>(mode, fuse, L, total, nt, lds, s);
+  else inv_x_launch_c<T, true, 2, CELLS, SLX>(mode, fuse, L, total, nt, lds, s);
+}
 
 template <typename T, int M>
 void yzy_launch_m(int sl, const Launch<T>& L, long long total, int nt, size_t lds, hipStream_t s) {
@@ -2282,6 +2348,44 @@ void yzy_launch(int m, int sl, const Launch<T>& L, long long total, int nt, size
     case 3: yzy_launch_m<T, 3>(sl, L, total, nt, lds, s); break;
     default: yzy_launch_m<T, 4>(sl, L, total, nt, lds, s); break;
   }
+}
+
+// One case for every compiled length.
+#define MMX_SR_LENGTHS(X) \
+  X(32) X(48) X(64) X(72) X(96) X(108) X(128) X(144) X(162) X(192) X(216) X(256) X(288) X(324) X(384) X(432) X(512) \
+  X(576) X(648) X(768)
+
+template <typename T>
+void fwd_x_launch_m(int len, const Launch<T>& L, long long total, int nt, size_t lds, hipStream_t s) {
+#define MMX_CASE(LL) \
+  case LL: k_fwd_x<T, LL, true><<<dim3((unsigned)total), nt, lds, s>>>(L); break;
+  switch (len) { MMX_SR_LENGTHS(MMX_CASE) default: break; }
+#undef MMX_CASE
+}
+
+template <typename T>
+void y_launch_m(bool inv, int len, const Launch<T>& L, long long total, int nt, size_t lds, hipStream_t s) {
+#define MMX_CASE(LL)                                                        \
+  case LL:                                                                  \
+    if (inv) k_yinv_m<T, LL><<<dim3((unsigned)total), nt, lds, s>>>(L);     \
+    else k_ypass_m<T, LL><<<dim3((unsigned)total), nt, lds, s>>>(L);        \
+    break;
+  switch (len) { MMX_SR_LENGTHS(MMX_CASE) default: break; }
+#undef MMX_CASE
+}
+
+// Powers of two (two translation units: below 256, and from there).
+template <typename T, bool CELLS, bool LONG>
+void inv_x_launch_s(int len, int mode, int cpt, bool fuse, const Launch<T>& L, long long total, int nt, size_t lds,
+                    hipStream_t s) {
+#define MMX_CASE(LL) \
+  case LL: inv_x_launch_l<T, CELLS, LL>(mode, cpt, fuse, L, total, nt, lds, s); break;
+  if constexpr (LONG) {
+    switch (len) { MMX_CASE(256) MMX_CASE(512) MMX_CASE(1024) default: break; }
+  } else {
+    switch (len) { MMX_CASE(32) MMX_CASE(64) MMX_CASE(128) default: break; }
+  }
+#undef MMX_CASE
 }
 
 }  // namespace mmx

@@ -1,0 +1,7 @@
+// Inverse-x pass compiled for the powers of two below 256 (double, uniform material).
+#include "hotpath.hpp"
+
+namespace mmx {
+template void inv_x_launch_s<double, false, false>(int, int, int, bool, const Launch<double>&, long long, int, size_t,
+                                          hipStream_t);
+}  // namespace mmx

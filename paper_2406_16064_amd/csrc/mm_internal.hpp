@@ -85,6 +85,69 @@ __host__ __device__ constexpr int p2_psh(int L, bool a16) {
   return lin ? 3 : 31;
 }
 
+// Plan of the kernels compiled for one 3-smooth length L (at most 6 stages of
+// radix 2, 3, 4, 6, 8, 9): the power-of-two plan above, or with threes in L the
+// split into 6s, 9s and at most one 3 that takes the fewest stages, among those
+// the one with an even radix at both ends, then the one with the most 6s.  The
+// odd radices stand after the first stage.
+struct SrPlan {
+  int nst;
+  int rad[6];
+};
+__host__ __device__ constexpr SrPlan sr_plan(int L) {
+  int a = 0, b = 0;
+  while (L % 2 == 0) { L /= 2; ++a; }
+  while (L % 3 == 0) { L /= 3; ++b; }
+  int best = 1 << 20, n6 = 0;
+  for (int k = 0; k <= a && k <= b; ++k) {
+    const int evens = k + p2_nst(a - k, false), odds = (b - k) / 2 + (b - k) % 2;
+    const int score = 4 * (evens + odds) + (odds == 0 || evens >= 2 ? 0 : evens == 1 ? 1 : 2);
+    if (score <= best) { best = score; n6 = k; }
+  }
+  const int np = p2_nst(a - n6, false), n9 = (b - n6) / 2, n3 = (b - n6) % 2;
+  SrPlan p{0, {0, 0, 0, 0, 0, 0}};
+  int ev[8] = {0, 0, 0, 0, 0, 0, 0, 0}, ne = 0;
+  for (int s = 0; s < np; ++s) ev[ne++] = p2_radix(a - n6, false, s);
+  for (int s = 0; s < n6; ++s) ev[ne++] = 6;
+  if (ne > 0) p.rad[p.nst++] = ev[0];
+  for (int s = 0; s < n9; ++s) p.rad[p.nst++] = 9;
+  if (n3 > 0) p.rad[p.nst++] = 3;
+  for (int s = 1; s < ne; ++s) p.rad[p.nst++] = ev[s];
+  return p;
+}
+// Threads a column: 8 entries each for a power of two, else as many as give
+// every stage at most 9 entries a thread.
+__host__ __device__ constexpr int sr_tpc(int L) {
+  const SrPlan p = sr_plan(L);
+  bool p2 = true;
+  for (int s = 0; s < p.nst; ++s) p2 = p2 && p.rad[s] % 3 != 0;
+  if (p2) return L / 8;
+  int t = 1;
+  for (int s = 0; s < p.nst; ++s) {
+    const int R = p.rad[s], cap = R == 2 ? 4 : R == 3 ? 3 : R == 4 ? 2 : 1;
+    const int n = (L / R + cap - 1) / cap;
+    t = n > t ? n : t;
+  }
+  return t;
+}
+// LDS padding shift of that plan (the rule of describe() below)
+__host__ __device__ constexpr int sr_psh(int L) {
+  const SrPlan p = sr_plan(L);
+  int ns = 1;
+  for (int s = 0; s < p.nst; ++s) {
+    if ((L / p.rad[s]) % 8 != 0) return 31;
+    if (s == 0 ? p.rad[s] % 3 == 0 : ns % 8 != 0) return 31;
+    ns *= p.rad[s];
+  }
+  return 3;
+}
+// The lengths with kernels compiled so (y columns, and x rows by Lx = Px / 2).
+__host__ __device__ constexpr bool sr_compiled(int L) {
+  return L == 32 || L == 48 || L == 64 || L == 72 || L == 96 || L == 108 || L == 128 || L == 144 || L == 162 ||
+         L == 192 || L == 216 || L == 256 || L == 288 || L == 324 || L == 384 || L == 432 || L == 512 || L == 576 ||
+         L == 648 || L == 768;
+}
+
 constexpr uint32_t kFftFirstEven = 1u << 30;
 constexpr uint32_t kFftLastEven = 1u << 31;
 

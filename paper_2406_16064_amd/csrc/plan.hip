@@ -457,6 +457,8 @@ mm_status choose_tuning(Group& G, mm_precision prec, size_t csz, long long launc
     while (ty >= 4 && ty < 16 && ty * g.Lx < 512 && rows / (2 * ty) >= want) ty *= 2;
     while (ty > g.ny) ty /= 2;  // a power of two (the kernels split rows by shifts)
     if ((size_t)ty * rowb + xtab > 160 * 1024 || ty * tpx > 512) return fail(MM_E_ARG, "mesh too long along x");
+    // one kernel for a compiled length, whatever the rows (sr_compiled)
+    while (sr_compiled(g.Lx) && ty > 1 && ty * sr_tpc(g.Lx) > 512) ty /= 2;
     t.ty_f = ty;
     const int cap = ty <= 4 && rows / ty > want ? 256 : 512;
     t.nt_f = std::min(512, std::max(64, pow2ceil(std::max(ty * tpx, std::min(cap, ty * g.Lx / 4)))));
@@ -504,6 +506,7 @@ mm_status choose_tuning(Group& G, mm_precision prec, size_t csz, long long launc
     int cb = 8;
     // packed: the tile of slot 0 also holds the tensor rows of kx = Lx
     const int pk = y2d_packed(g);
+    while (sr_compiled(g.Py) && cb > 1 && 3 * cb * sr_tpc(g.Py) > 512) cb /= 2;
     while (cb > 1 && (cb * colb + (cb + pk) * ktab2 + ytab > budget || 3 * cb * tpc > 512 || g.Xp / cb < want)) cb /= 2;
     if (cb * colb + (cb + pk) * ktab2 + ytab > 160 * 1024 || 3 * cb * tpc > 512)
       return fail(MM_E_ARG, "mesh too long along y");
@@ -525,8 +528,8 @@ mm_status choose_tuning(Group& G, mm_precision prec, size_t csz, long long launc
       cb = 2;
       tpc *= 2;
     }
-    while (cb < 16 && cb * tpc < 64 && 3LL * g.nz * g.Xp / (2 * cb) >= want) cb *= 2;
-    while (cb > 1 && (cb * colb > budget || cb * tpc > 512)) cb /= 2;
+    while (!sr_compiled(g.Py) && cb < 16 && cb * tpc < 64 && 3LL * g.nz * g.Xp / (2 * cb) >= want) cb *= 2;
+    while (cb > 1 && (cb * colb > budget || cb * tpc > 512 || (sr_compiled(g.Py) && cb * sr_tpc(g.Py) > 512))) cb /= 2;
     if (cb * colb > 160 * 1024 || cb * tpc > 512) return fail(MM_E_ARG, "mesh too long along y");
     t.cb_y = cb;
     t.tpc_y = tpc;
