@@ -14,8 +14,9 @@ OUT = os.path.join(HERE, "libmmx.so")
 SOURCES = ("hotpath.hip", "invx_f32_demag.hip", "invx_f32_local.hip", "invx_f64_demag.hip",
            "invx_f64_local.hip", "invx_f32_demag_cells.hip", "invx_f32_local_cells.hip",
            "invx_f64_demag_cells.hip", "invx_f64_local_cells.hip", "yzy_f32.hip", "yzy_f64.hip",
-           "lengths_f32.hip", "lengths_f64.hip", "invx_f32_lengths_a.hip", "invx_f32_lengths_b.hip",
-           "invx_f64_lengths_a.hip", "invx_f64_lengths_b.hip", "potential.hip", "setup.hip", "plan.hip")
+           "lengths_f32.hip", "lengths_f64.hip", "invx_f32_any_cells.hip", "invx_f64_any_cells.hip",
+           "invx_f32_any1.hip", "invx_f32_any2.hip", "invx_f32_any4.hip", "invx_f64_any1.hip", "invx_f64_any2.hip",
+           "invx_f64_any4.hip", "potential.hip", "setup.hip", "plan.hip")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 

@@ -26,18 +26,22 @@ extern template void inv_x_launch<double, false, false>(int, int, bool, const La
                                                        hipStream_t);
 extern template void inv_x_launch<double, false, true>(int, int, bool, const Launch<double>&, long long, int, size_t,
                                                        hipStream_t);
-extern template void fwd_x_launch_m<float>(int, const Launch<float>&, long long, int, size_t, hipStream_t);
-extern template void y_launch_m<float>(bool, int, const Launch<float>&, long long, int, size_t, hipStream_t);
-extern template void inv_x_launch_s<float, false, false>(int, int, int, bool, const Launch<float>&, long long, int,
-                                                         size_t, hipStream_t);
-extern template void inv_x_launch_s<float, false, true>(int, int, int, bool, const Launch<float>&, long long, int,
-                                                         size_t, hipStream_t);
-extern template void fwd_x_launch_m<double>(int, const Launch<double>&, long long, int, size_t, hipStream_t);
-extern template void y_launch_m<double>(bool, int, const Launch<double>&, long long, int, size_t, hipStream_t);
-extern template void inv_x_launch_s<double, false, false>(int, int, int, bool, const Launch<double>&, long long, int,
-                                                         size_t, hipStream_t);
-extern template void inv_x_launch_s<double, false, true>(int, int, int, bool, const Launch<double>&, long long, int,
-                                                         size_t, hipStream_t);
+extern template void fwd_x_launch_m<float>(const Launch<float>&, long long, int, size_t, hipStream_t);
+extern template void y_launch_m<float>(int, const Launch<float>&, long long, int, size_t, hipStream_t);
+extern template void yinv_launch_m<float>(const Launch<float>&, long long, int, size_t, hipStream_t);
+extern template void inv_x_launch_any<float, false, 1>(int, bool, const Launch<float>&, long long, int, size_t, hipStream_t);
+extern template void inv_x_launch_any<float, false, 2>(int, bool, const Launch<float>&, long long, int, size_t, hipStream_t);
+extern template void inv_x_launch_any<float, false, 4>(int, bool, const Launch<float>&, long long, int, size_t, hipStream_t);
+extern template void inv_x_launch_any<float, true, 1>(int, bool, const Launch<float>&, long long, int, size_t, hipStream_t);
+extern template void inv_x_launch_any<float, true, 2>(int, bool, const Launch<float>&, long long, int, size_t, hipStream_t);
+extern template void fwd_x_launch_m<double>(const Launch<double>&, long long, int, size_t, hipStream_t);
+extern template void y_launch_m<double>(int, const Launch<double>&, long long, int, size_t, hipStream_t);
+extern template void yinv_launch_m<double>(const Launch<double>&, long long, int, size_t, hipStream_t);
+extern template void inv_x_launch_any<double, false, 1>(int, bool, const Launch<double>&, long long, int, size_t, hipStream_t);
+extern template void inv_x_launch_any<double, false, 2>(int, bool, const Launch<double>&, long long, int, size_t, hipStream_t);
+extern template void inv_x_launch_any<double, false, 4>(int, bool, const Launch<double>&, long long, int, size_t, hipStream_t);
+extern template void inv_x_launch_any<double, true, 1>(int, bool, const Launch<double>&, long long, int, size_t, hipStream_t);
+extern template void inv_x_launch_any<double, true, 2>(int, bool, const Launch<double>&, long long, int, size_t, hipStream_t);
 extern template void yzy_launch<float>(int, int, const Launch<float>&, long long, int, size_t, hipStream_t);
 extern template void yzy_launch<double>(int, int, const Launch<double>&, long long, int, size_t, hipStream_t);
 
@@ -465,20 +469,15 @@ int inv_cpt(const GroupSet<T>& gs, int nt) {
   return 0;
 }
 
-// Length of the inverse-x kernel compiled for one Lx (inv_x_launch_s), 0 for the
-// general one: every group has that Lx, a power of two (whose plan is the general
-// kernel's, so that a mesh gives the same bits alone and in a batch of others),
-// the workgroup holds its columns' threads, one or two cells a thread, and the
-// mode is one it is compiled for (a stage without the next forward pass is not).
+// Whether a group's inverse-x pass takes the kernels compiled for the lengths of
+// the list and 1024 (inv_x_launch_any): it has such an Lx and its workgroup holds
+// its columns' threads.  The other groups of a launch take the general kernel in
+// a launch of their own, so that a mesh has one plan, and the same bits, alone and
+// in a batch of others.
 template <typename T>
-int inv_x_static(const GroupSet<T>& gs, int nt, int cpt, int mode, bool fuse) {
-  if (cpt != 1 && cpt != 2) return 0;
-  if (mode == MODE_STAGE && !fuse) return 0;
-  const int L = gs.h[0].g.Lx;
-  if ((L & (L - 1)) != 0 || (!sr_compiled(L) && L != 1024)) return 0;
-  for (int i = 0; i < gs.n; ++i)
-    if (gs.h[i].g.Lx != L || 3 * gs.h[i].tu.ty_x * sr_tpc(L) > nt) return 0;
-  return L;
+bool inv_x_any(const HotPlan<T>& h) {
+  const int L = h.g.Lx;
+  return (sr_compiled(L) || L == 1024) && 3 * h.tu.ty_x * sr_tpc(L) <= h.tu.nt_i;
 }
 
 template <typename T>
@@ -517,25 +516,6 @@ int static_y(const GroupSet<T>& gs, bool inv, int& nt, int& ept, const bool* use
   return sl;
 }
 
-// The y passes launch once per length with a compiled transform (Py = 2 ny of
-// 256 to 2048, or kMixKey + Py for the other lengths of fft_mix) among the
-// groups, and once for the rest (the general transform): key of group i, 0 for
-// the general kernels.
-constexpr int kMixKey = 4096;
-template <typename T>
-int y_key(const HotPlan<T>& h) {
-  const int L = h.g.Py;
-  if (L == 2 * h.g.ny && (L == 256 || L == 512 || L == 1024 || L == 2048)) return L;
-  if (!sr_compiled(L)) return 0;
-  const int cols = h.g.nz == 1 ? 3 * h.tu.cb_y2 : h.tu.cb_y;
-  return cols * sr_tpc(L) <= 512 && (h.g.nz == 1 || h.tu.cb_y <= kSxB) ? kMixKey + L : 0;
-}
-template <typename T>
-int mix_threads(const HotPlan<T>& h) {
-  const int cols = h.g.nz == 1 ? 3 * h.tu.cb_y2 : h.tu.cb_y;
-  return (cols * sr_tpc(h.g.Py) + 63) / 64 * 64;
-}
-
 // Pz / 2 where a 3-D group takes the fused y and z passes (k_yzy), 0 where it
 // takes the separate ones.  Fused: nz = 2 to 4 (FP64 to 3), Py = 2 ny of 256, 512
 // or 1024, and the columns of a kx in 64 KB of LDS, so that two workgroups and
@@ -548,11 +528,33 @@ int mix_threads(const HotPlan<T>& h) {
 template <typename T>
 int yzy_m(const Geo& g) {
   if (g.nz < 2 || g.nz > (sizeof(T) == 8 ? 3 : 4) || g.Pz != 2 * g.nz) return 0;
-  if (g.Py != 2 * g.ny || (g.Py != 256 && g.Py != 512 && g.Py != 1024)) return 0;
+  if (!sr_compiled(g.Py) && !(g.Py == 2 * g.ny && g.Py == 1024)) return 0;
   return yzy_lds(g, sizeof(Cx<T>)) <= 64 * 1024 ? g.nz : 0;
 }
 template <typename T>
 int yzy_m(const HotPlan<T>& h) { return h.kt ? yzy_m<T>(h.g) : 0; }  // no tensor: the scalar-potential route
+
+// The y passes launch once per length of the kernels compiled for one (Py = 2 ny
+// of 256 to 2048), once for all the other compiled lengths (kMixKey; in a launch
+// of several meshes, `several`, those of the list among the former too), and
+// once for the rest (the general transform): key of a group, 0 for the general
+// kernels.
+constexpr int kMixKey = 4096;
+template <typename T>
+int y_key(const HotPlan<T>& h, bool several) {
+  const int L = h.g.Py;
+  const int cols = h.g.nz == 1 ? 3 * h.tu.cb_y2 : h.tu.cb_y;
+  // (a fused group's tile is its kx, whatever the launch shapes: Sy is not there)
+  const bool mix = sr_compiled(L) && (yzy_m<T>(h) > 0 || (cols * sr_tpc(L) <= 512 &&
+                                                         (h.g.nz == 1 || h.tu.cb_y <= kSxB)));
+  if (L == 2 * h.g.ny && (L == 256 || L == 512 || L == 1024 || L == 2048) && !(several && mix)) return L;
+  return mix ? kMixKey : 0;
+}
+template <typename T>
+int mix_threads(const HotPlan<T>& h) {
+  const int cols = h.g.nz == 1 ? 3 * h.tu.cb_y2 : h.tu.cb_y;
+  return (cols * sr_tpc(h.g.Py) + 63) / 64 * 64;
+}
 
 template <typename T>
 bool eval_needs_sy(const Geo& g) { return g.nz > 1 && yzy_m<T>(g) == 0; }
@@ -576,13 +578,15 @@ hipError_t launch_eval(const GroupSet<T>& gs, const Epi<T>* epis, int mode, bool
   if (demag) {
     if (!skip_fwd && on(0)) {  // x forward (skipped when the previous stage's inverse-x pass did it)
       // one launch per static length (every group with an even nx = Lx of
-      // 128 to 1024 shares the kernel compiled for its Lx; other row lengths of
-      // the list share the one of fft_mix, key 4096 + Lx, where the workgroup
-      // holds its threads), one for the rest
+      // 128 to 1024 shares the kernel compiled for its Lx), one for all the other
+      // compiled lengths (key kMixKey; in a launch of several meshes these
+      // static lengths too), one for the rest
       auto x_key = [&](const HotPlan<T>& h) {
         const Geo& g = h.g;
-        if (g.nx == g.Lx && (g.Lx == 128 || g.Lx == 256 || g.Lx == 512 || g.Lx == 1024)) return g.Lx;
-        return sr_compiled(g.Lx) && h.tu.ty_f * sr_tpc(g.Lx) <= 512 ? 4096 + g.Lx : 0;
+        const bool mix = sr_compiled(g.Lx) && h.tu.ty_f * sr_tpc(g.Lx) <= 512;
+        if (g.nx == g.Lx && (g.Lx == 128 || g.Lx == 256 || g.Lx == 512 || g.Lx == 1024) && (gs.n == 1 || !mix))
+          return g.Lx;
+        return mix ? kMixKey : 0;
       };
       mark();
       int keys[kMaxGroups], nkeys = 0;
@@ -601,13 +605,13 @@ hipError_t launch_eval(const GroupSet<T>& gs, const Epi<T>* epis, int mode, bool
           const bool use = x_key(h) == keys[kk];
           lb.set(i, use ? fwd_blocks(h.g, h.tu, h.batch) : 0);
           if (!use) continue;
-          nt = std::max(nt, keys[kk] > 4096 ? (h.tu.ty_f * sr_tpc(h.g.Lx) + 63) / 64 * 64 : h.tu.nt_f);
+          nt = std::max(nt, keys[kk] == kMixKey ? (h.tu.ty_f * sr_tpc(h.g.Lx) + 63) / 64 * 64 : h.tu.nt_f);
           lds = std::max(lds, ((size_t)h.tu.ty_f * col_stride(h.g.Lx) + 2 * h.g.Lx + 1) * csz);
         }
         if (lb.total == 0) continue;  // no instance of these meshes in this launch
         const dim3 grid((unsigned)lb.total);
-        if (keys[kk] > 4096) {
-          fwd_x_launch_m<T>(keys[kk] - 4096, lb.L, lb.total, nt, lds, s);
+        if (keys[kk] == kMixKey) {
+          fwd_x_launch_m<T>(lb.L, lb.total, nt, lds, s);
           continue;
         }
         switch (keys[kk]) {
@@ -626,11 +630,11 @@ hipError_t launch_eval(const GroupSet<T>& gs, const Epi<T>* epis, int mode, bool
       int key_of[kMaxGroups], keys[kMaxGroups], nkeys = 0;
       for (int i = 0; i < gs.n; ++i) {
         const HotPlan<T>& h = gs.h[i];
-        key_of[i] = 32 * y_key(h) + yzy_m<T>(h);
+        key_of[i] = 32 * y_key(h, gs.n > 1) + yzy_m<T>(h);
         for (int j = 0; j < gs.n && h.g.nz == 1; ++j) {
-          const int m = yzy_m<T>(gs.h[j]), sl = y_key(h);
-          if (m == 0 || y_key(gs.h[j]) != sl || gs.h[j].batch == 0 || sl > kMixKey) continue;
-          if (3 * h.tu.cb_y2 * (sl / 8) <= 512) key_of[i] = 32 * sl + m;
+          const int m = yzy_m<T>(gs.h[j]), sl = y_key(h, gs.n > 1);
+          if (m == 0 || y_key(gs.h[j], gs.n > 1) != sl || gs.h[j].batch == 0 ) continue;
+          if (sl == kMixKey || 3 * h.tu.cb_y2 * (sl / 8) <= 512) key_of[i] = 32 * sl + m;
           break;
         }
         bool seen = false;
@@ -660,13 +664,14 @@ hipError_t launch_eval(const GroupSet<T>& gs, const Epi<T>* epis, int mode, bool
           lds = std::max(lds, (size_t)h.tu.cb_y * col_stride(h.g.Py) * csz);
         }
         if (!use[i]) continue;
-        const int cols = 3 * (h.g.nz == 1 ? h.tu.cb_y2 : h.g.nz);  // fused launches
-        nt = std::max(nt, m > 0 ? std::min(512, cols * (keys[kk] / 32 / 8))
-                          : keys[kk] / 32 > kMixKey ? mix_threads(h) : h.tu.nt_y);
+        const bool mix = keys[kk] / 32 == kMixKey;
+        if (m > 0 && h.g.nz > 1) nt = std::max(nt, std::min(512, (3 * h.g.nz * sr_tpc(h.g.Py) + 63) / 64 * 64));
+        else if (m > 0 && !mix) nt = std::max(nt, 3 * h.tu.cb_y2 * (h.g.Py / 8));
+        else nt = std::max(nt, mix ? mix_threads(h) : h.tu.nt_y);
       }
       if (lb.total == 0) continue;
-      if (keys[kk] / 32 > kMixKey) {
-        y_launch_m<T>(false, keys[kk] / 32 - kMixKey, lb.L, lb.total, nt, lds, s);
+      if (keys[kk] / 32 == kMixKey) {
+        y_launch_m<T>(m, lb.L, lb.total, nt, lds, s);
         continue;
       }
       if (m > 0) {
@@ -745,7 +750,7 @@ hipError_t launch_eval(const GroupSet<T>& gs, const Epi<T>* epis, int mode, bool
       int keys[kMaxGroups], nkeys = 0;
       for (int i = 0; i < gs.n && on(3); ++i) {
         if (gs.h[i].g.nz == 1 || yzy_m<T>(gs.h[i]) > 0) continue;
-        const int k = y_key(gs.h[i]);
+        const int k = y_key(gs.h[i], gs.n > 1);
         bool seen = false;
         for (int j = 0; j < nkeys; ++j) seen = seen || keys[j] == k;
         if (!seen) keys[nkeys++] = k;
@@ -757,16 +762,16 @@ hipError_t launch_eval(const GroupSet<T>& gs, const Epi<T>* epis, int mode, bool
       size_t ldsy = 0;
       for (int j = 0; j < gs.n; ++j) {
         const HotPlan<T>& h = gs.h[j];
-        usey[j] = h.g.nz > 1 && yzy_m<T>(h) == 0 && y_key(h) == keys[kk];
+        usey[j] = h.g.nz > 1 && yzy_m<T>(h) == 0 && y_key(h, gs.n > 1) == keys[kk];
         ly.set(j, usey[j] ? y3d_blocks(h.g, h.tu, h.batch) : 0);
         if (usey[j]) {
-          nty = std::max(nty, keys[kk] > kMixKey ? mix_threads(h) : h.tu.nt_y);
+          nty = std::max(nty, keys[kk] == kMixKey ? mix_threads(h) : h.tu.nt_y);
           ldsy = std::max(ldsy, (size_t)h.tu.cb_y * col_stride(h.g.Py) * csz);
         }
       }
       if (ly.total == 0) continue;
-      if (keys[kk] > kMixKey) {
-        y_launch_m<T>(true, keys[kk] - kMixKey, ly.L, ly.total, nty, ldsy, s);
+      if (keys[kk] == kMixKey) {
+        yinv_launch_m<T>(ly.L, ly.total, nty, ldsy, s);
         continue;
       }
       int nts = 0, ept = 16;
@@ -789,29 +794,48 @@ hipError_t launch_eval(const GroupSet<T>& gs, const Epi<T>* epis, int mode, bool
     }
   }
   if (on(p_inv)) {  // x inverse + epilogue
-    LaunchBuilder<T> lb(gs, epis);
     int nt = 64;
-    size_t lds = 0;
-    for (int i = 0; i < gs.n; ++i) {
-      const HotPlan<T>& h = gs.h[i];
-      lb.set(i, inv_blocks(h.g, h.tu, h.batch));
-      nt = std::max(nt, h.tu.nt_i);
-      if (demag) lds = std::max(lds, ((size_t)3 * h.tu.ty_x * col_stride(h.g.Lx) + 2 * h.g.Lx + 1) * csz);
-    }
-    const int cpt = inv_cpt(gs, nt);
-    const bool fuse = fuse_next && demag && mode == MODE_STAGE && cpt > 0;
-    mark();
+    for (int i = 0; i < gs.n; ++i) nt = std::max(nt, gs.h[i].tu.nt_i);
+    const bool fuse = fuse_next && demag && mode == MODE_STAGE && inv_cpt(gs, nt) > 0;
     // general-material form (cell arrays, interlayer coupling, spin torques): plans only
     const bool gen = gs.n == 1 && gs.h[0].gen != 0;
-    if (gen) {
-      if (demag) inv_x_launch<T, true, true>(mode, cpt, fuse, lb.L, lb.total, nt, lds, s);
-      else inv_x_launch<T, false, true>(mode, cpt, false, lb.L, lb.total, nt, 0, s);
-    } else if (const int len = demag ? inv_x_static(gs, nt, cpt, mode, fuse) : 0; len > 0) {
-      if (len < 256) inv_x_launch_s<T, false, false>(len, mode, cpt, fuse, lb.L, lb.total, nt, lds, s);
-      else inv_x_launch_s<T, false, true>(len, mode, cpt, fuse, lb.L, lb.total, nt, lds, s);
-    } else {
-      if (demag) inv_x_launch<T, true, false>(mode, cpt, fuse, lb.L, lb.total, nt, lds, s);
-      else inv_x_launch<T, false, false>(mode, cpt, false, lb.L, lb.total, nt, 0, s);
+    mark();
+    bool listed[kMaxGroups];
+    int cpt_listed = 1;
+    for (int i = 0; i < gs.n; ++i) {
+      listed[i] = demag && (mode != MODE_STAGE || fuse) && inv_x_any(gs.h[i]);
+      if (listed[i]) cpt_listed = std::max(cpt_listed, (gs.h[i].tu.ty_x * gs.h[i].g.nx + nt - 1) / nt);
+    }
+    if (cpt_listed > (gen ? 2 : 4))  // compiled for one, two and four cells a thread (general material: to two)
+      for (int i = 0; i < gs.n; ++i) listed[i] = false;
+    for (int part = 0; part < 2; ++part) {  // 0: compiled lengths, 1: the rest
+      LaunchBuilder<T> lb(gs, epis);
+      size_t lds = 0;
+      int need = 1;
+      for (int i = 0; i < gs.n; ++i) {
+        const HotPlan<T>& h = gs.h[i];
+        const bool use = listed[i] == (part == 0);
+        lb.set(i, use ? inv_blocks(h.g, h.tu, h.batch) : 0);
+        if (!use) continue;
+        need = std::max(need, (h.tu.ty_x * h.g.nx + nt - 1) / nt);
+        if (demag) lds = std::max(lds, ((size_t)3 * h.tu.ty_x * col_stride(h.g.Lx) + 2 * h.g.Lx + 1) * csz);
+      }
+      if (lb.total == 0) continue;
+      const int cpt = need > 8 ? 0 : need > 4 ? 8 : need > 2 ? 4 : need;
+      if (part == 0 && gen) {
+        if (cpt == 1) inv_x_launch_any<T, true, 1>(mode, fuse, lb.L, lb.total, nt, lds, s);
+        else inv_x_launch_any<T, true, 2>(mode, fuse, lb.L, lb.total, nt, lds, s);
+      } else if (part == 0) {
+        if (cpt == 1) inv_x_launch_any<T, false, 1>(mode, fuse, lb.L, lb.total, nt, lds, s);
+        else if (cpt == 2) inv_x_launch_any<T, false, 2>(mode, fuse, lb.L, lb.total, nt, lds, s);
+        else inv_x_launch_any<T, false, 4>(mode, fuse, lb.L, lb.total, nt, lds, s);
+      } else if (gen) {
+        if (demag) inv_x_launch<T, true, true>(mode, cpt, fuse, lb.L, lb.total, nt, lds, s);
+        else inv_x_launch<T, false, true>(mode, cpt, false, lb.L, lb.total, nt, 0, s);
+      } else {
+        if (demag) inv_x_launch<T, true, false>(mode, cpt, fuse, lb.L, lb.total, nt, lds, s);
+        else inv_x_launch<T, false, false>(mode, cpt, false, lb.L, lb.total, nt, 0, s);
+      }
     }
   }
   mark();

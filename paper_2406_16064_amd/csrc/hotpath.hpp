@@ -175,9 +175,15 @@ struct XRowLoad {
   }
 };
 
+// One case for every compiled length.
+#define MMX_SR_LENGTHS(X) \
+  X(16) X(24) X(32) X(36) X(48) X(54) X(64) X(72) X(96) X(108) X(128) X(144) X(162) X(192) X(216) X(256) X(288) \
+  X(324) X(384) X(432) X(512) X(576) X(648) X(768) X(864) X(972)
+
 // SLX: 0 for any group, else the one length Lx of every group, all with an
 // even nx = Lx (a kernel holding one static transform keeps fewer registers);
-// MIX: any nx, the transform of fft_mix (sr_tpc(SLX) threads a row).
+// MIX: every group has a compiled Lx and any nx, the transform of fft_mix
+// (sr_tpc(Lx) threads a row).
 template <typename T, int SLX, bool MIX = false>
 __global__ void __launch_bounds__(512) k_fwd_x(Launch<T> L) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -200,7 +206,7 @@ __global__ void __launch_bounds__(512) k_fwd_x(Launch<T> L) {
   const int y0 = tile * TY;
   const int nrow = g.ny - y0 < TY ? g.ny - y0 : TY;
   const int cs = col_stride(g.Lx);
-  const int sh = MIX ? sr_psh(SLX > 0 ? SLX : 32) : hp.fd[0].psh;
+  const int sh = MIX ? hp.shx : hp.fd[0].psh;
   // LDS: TY columns, then the twiddle table (Lx) and the post factors (Lx + 1)
   Cx<T>* const twl = lds + TY * cs;
   Cx<T>* const postl = twl + g.Lx;
@@ -216,7 +222,13 @@ __global__ void __launch_bounds__(512) k_fwd_x(Launch<T> L) {
   const bool hin = ld.pairs && g.nx == g.Lx;
   const NoStore<T> nst;
   if constexpr (MIX) {
-    fft_mix<T, SLX, false, true, false, true, true, false, true>(lds, twl, cs, nrow, ld, nst, hook);
+    switch (g.Lx) {
+#define MMX_CASE(LL) \
+  case LL: fft_mix<T, LL, false, true, false, true, true, false, true>(lds, twl, cs, nrow, ld, nst, hook); break;
+      MMX_SR_LENGTHS(MMX_CASE)
+#undef MMX_CASE
+      default: break;
+    }
   } else {
   // compiled for the power-of-two lengths (L/8 threads a row where the
   // workgroup has them, else L/16)
@@ -695,8 +707,9 @@ __host__ __device__ inline long long yzy_blocks(const Geo& g, int batch) { retur
 template <typename T, int M>
 __device__ __forceinline__ void yzy_point(const HotPlan<T>& hp, Cx<T>* lds, int cs, int o, int kx, int ky, int p, T s);
 
-// Compiled for Py = SL = 2 ny, 8 entries a thread.
-template <typename T, int M, int SL>
+// Compiled for Py = SL = 2 ny, 8 entries a thread, or with MIX for Py = SL of any
+// ny (fft_mix).
+template <typename T, int M, int SL, bool MIX = false>
 __device__ __forceinline__ void yzy3d(const HotPlan<T>& hp, const Epi<T>& ep, long long bid0, Cx<T>* lds) {
   const Geo& g = hp.g;
   const unsigned bid = (unsigned)bid0;
@@ -705,8 +718,8 @@ __device__ __forceinline__ void yzy3d(const HotPlan<T>& hp, const Epi<T>& ep, lo
   if (ep.ctl && ldu(&ep.ctl[b].done)) return;
   const int nz = g.nz, ny = g.ny, ncol = 3 * nz;
   const int cs = col_stride(g.Py);
-  constexpr int sh = p2_psh(SL, false);
-  constexpr int tpc = SL / 8;
+  constexpr int sh = sr_psh(SL);
+  constexpr int tpc = sr_tpc(SL);
   const int many = (int)blockDim.x / tpc;  // columns transformed at a time
   const int mc = (int)threadIdx.x / tpc;
   Cx<T>* const twl = lds + ncol * cs;
@@ -724,8 +737,11 @@ __device__ __forceinline__ void yzy3d(const HotPlan<T>& hp, const Epi<T>& ep, lo
     auto hook = [&]() {
       if (c0 == 0) tab.store(twl);
     };
-    fft_static<T, SL, false, false, true, false, true, true, false, 8>(lds + c0 * cs, twl, cs, nc, ld, NoStore<T>{},
-                                                                      hook);
+    if constexpr (MIX)
+      fft_mix<T, SL, false, true, false, true, true, false, true>(lds + c0 * cs, twl, cs, nc, ld, NoStore<T>{}, hook);
+    else
+      fft_static<T, SL, false, false, true, false, true, true, false, 8>(lds + c0 * cs, twl, cs, nc, ld, NoStore<T>{},
+                                                                        hook);
   }
   const T s = T(ldu(&hp.prm[b].demag_scale));
   for (int ky = (int)threadIdx.x >> 1; ky < g.Py; ky += (int)blockDim.x >> 1)
@@ -735,8 +751,11 @@ __device__ __forceinline__ void yzy3d(const HotPlan<T>& hp, const Epi<T>& ep, lo
     const int nc = ncol - c0 < many ? ncol - c0 : many;
     const uint32_t coff = ((uint32_t)(c0 + (mc < nc ? mc : 0)) * plane + k0) * (uint32_t)sizeof(Cx<T>);
     const ColStoreS<T> st{base, coff, sb, ny};
-    fft_static<T, SL, false, true, false, true, true, false, true, 8>(lds + c0 * cs, twl, cs, nc, NoLoad<T>{}, st,
-                                                                     NoHook{});
+    if constexpr (MIX)
+      fft_mix<T, SL, true, false, true, true, false, true, true>(lds + c0 * cs, twl, cs, nc, NoLoad<T>{}, st, NoHook{});
+    else
+      fft_static<T, SL, false, true, false, true, true, false, true, 8>(lds + c0 * cs, twl, cs, nc, NoLoad<T>{}, st,
+                                                                       NoHook{});
   }
 }
 
@@ -816,27 +835,37 @@ __global__ void __launch_bounds__(512) k_yinv_s(Launch<T> L) {
   y_rows3d<T, true, false, SL, EPT>(hp, ldu(L.epis + gi), bid, lds);
 }
 
-// The y passes compiled for one 3-smooth length: every group of the launch has
-// Py = SL, any ny, and 3-D tiles inside one kx block.  The run-time engine holds
-// every radix and both predicates a butterfly in one kernel: 160 registers in
-// FP32 (three waves a SIMD) and three times the time a point of these.
-template <typename T, int SL>
+// The y passes of groups with a compiled 3-smooth Py and any ny, each group by
+// its own length (3-D tiles inside one kx block).  M > 0: the launch's 3-D
+// groups take the fused y and z passes with Pz = 2 M.  The run-time engine holds
+// every radix with a predicate a butterfly: 160 registers in FP32, three waves a
+// SIMD, and three times the time a point of these.
+template <typename T, int M>
 __global__ void __launch_bounds__(512) k_ypass_m(Launch<T> L) {
   extern __shared__ __align__(16) unsigned char smem[];
   Cx<T>* lds = reinterpret_cast<Cx<T>*>(smem);
   long long bid;
   const int gi = group_of(L, bid);
   const HotPlan<T> hp = hot_plan(L, gi);
-  if (hp.g.nz == 1) {
-    if (bid >= y2d_blocks(hp.g, hp.tu, hp.batch)) return;
-    y_fused2d<T, false, SL, 8, true>(hp, ldu(L.epis + gi), bid, lds);
-  } else {
-    if (bid >= y3d_blocks(hp.g, hp.tu, hp.batch)) return;
-    y_rows3d<T, false, false, SL, 8, true>(hp, ldu(L.epis + gi), bid, lds);
+  const Geo& g = hp.g;
+  if (bid >= (g.nz == 1 ? y2d_blocks(g, hp.tu, hp.batch) : M > 0 ? yzy_blocks(g, hp.batch)
+                                                                : y3d_blocks(g, hp.tu, hp.batch)))
+    return;
+  const Epi<T> ep = ldu(L.epis + gi);
+  switch (g.Py) {
+#define MMX_CASE(LL)                                                            \
+  case LL:                                                                      \
+    if (g.nz == 1) y_fused2d<T, false, LL, 8, true>(hp, ep, bid, lds);          \
+    else if constexpr (M > 0) yzy3d<T, M, LL, true>(hp, ep, bid, lds);          \
+    else y_rows3d<T, false, false, LL, 8, true>(hp, ep, bid, lds);              \
+    break;
+    MMX_SR_LENGTHS(MMX_CASE)
+#undef MMX_CASE
+    default: break;
   }
 }
 
-template <typename T, int SL>
+template <typename T>
 __global__ void __launch_bounds__(512) k_yinv_m(Launch<T> L) {
   extern __shared__ __align__(16) unsigned char smem[];
   Cx<T>* lds = reinterpret_cast<Cx<T>*>(smem);
@@ -844,7 +873,14 @@ __global__ void __launch_bounds__(512) k_yinv_m(Launch<T> L) {
   const int gi = group_of(L, bid);
   const HotPlan<T> hp = hot_plan(L, gi);
   if (bid >= y3d_blocks(hp.g, hp.tu, hp.batch)) return;
-  y_rows3d<T, true, false, SL, 8, true>(hp, ldu(L.epis + gi), bid, lds);
+  const Epi<T> ep = ldu(L.epis + gi);
+  switch (hp.g.Py) {
+#define MMX_CASE(LL) \
+  case LL: y_rows3d<T, true, false, LL, 8, true>(hp, ep, bid, lds); break;
+    MMX_SR_LENGTHS(MMX_CASE)
+#undef MMX_CASE
+    default: break;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1655,16 +1691,22 @@ __device__ __forceinline__ V3<T> ll_rhs(V3<T> m, V3<T> H, T g1, T g2) {
 // launch shapes give every column that many), the general plan otherwise.
 // Inverse: only the first half of the output is kept; forward: hin as for
 // fft_run (the input's upper half is zero and not read).
-// SLX > 0: every group of the launch has Lx = SLX and sr_tpc(SLX) threads a column.
-template <typename T, bool INV, int SLX = 0>
+// ANY: the length is one of the list or 1024, sr_tpc(L) threads a column.
+template <typename T, bool INV, bool ANY = false>
 __device__ __forceinline__ void x_columns(Cx<T>* lds, const FftDesc<T>& p, int cs, int ncol, const Cx<T>* twl,
                                           bool hin) {
   constexpr bool HIN = !INV, HOUT = INV;
   const NoLoad<T> nl;
   const NoStore<T> nst;
   const NoHook nh;
-  if constexpr (SLX > 0) {
-    fft_mix<T, SLX, INV, false, false, true, HIN, HOUT, false>(lds, twl, cs, ncol, nl, nst, nh);
+  if constexpr (ANY) {
+    switch (p.L) {
+#define MMX_CASE(LL) \
+  case LL: fft_mix<T, LL, INV, false, false, true, HIN, HOUT, false>(lds, twl, cs, ncol, nl, nst, nh); break;
+      MMX_SR_LENGTHS(MMX_CASE) MMX_CASE(1024)
+#undef MMX_CASE
+      default: break;
+    }
     return;
   }
   if (INV || hin) {
@@ -1915,7 +1957,7 @@ __device__ __forceinline__ void energy_pass_end(const double (&esum)[5], double*
 // Ms, A_ij, D_ij, an empty cell gets no demag field either, energies weight
 // each cell by its Ms, and with cell arrays the fused forward transform takes
 // Ms m.
-template <typename T, bool DEMAG, int MODE, int CPT, bool FUSE, bool CELLS, int SLX>
+template <typename T, bool DEMAG, int MODE, int CPT, bool FUSE, bool CELLS, bool ANY>
 __global__ void __launch_bounds__(512) k_inv_x(Launch<T> L) {
   constexpr bool PREF = CPT == 1;
   static_assert(!FUSE || (MODE == MODE_STAGE && DEMAG && CPT > 0), "fused forward pass needs a stage epilogue");
@@ -1940,7 +1982,7 @@ __global__ void __launch_bounds__(512) k_inv_x(Launch<T> L) {
   const int y0 = tile * TY;
   const int nrow = g.ny - y0 < TY ? g.ny - y0 : TY;
   const int cs = col_stride(g.Lx);
-  const int sh = SLX > 0 ? sr_psh(SLX > 0 ? SLX : 32) : hp.fd[0].psh;
+  const int sh = ANY ? hp.shx : hp.fd[0].psh;
 
   // Spectrum tile: column c * TY + r holds component c of row y0 + r (rows past
   // the mesh are left out: only the epilogue's rows are read back).
@@ -2065,7 +2107,7 @@ __global__ void __launch_bounds__(512) k_inv_x(Launch<T> L) {
     }
     __syncthreads();
     // the epilogue reads complex entries below ceil(nx / 2) <= Lx / 2 only
-    x_columns<T, true, SLX>(lds, hp.fd[0], cs, ncol, twl, false);
+    x_columns<T, true, ANY>(lds, hp.fd[0], cs, ncol, twl, false);
   }
 
   // ----- epilogue ----- (its arguments are read only now, which keeps the
@@ -2216,7 +2258,7 @@ __global__ void __launch_bounds__(512) k_inv_x(Launch<T> L) {
     // half-length input end, else 2 Lx)
     T* const re = reinterpret_cast<T*>(lds);
     const int rcs = 2 * cs;
-    const bool hin = SLX > 0 ? mix_hin(SLX > 0 ? SLX : 32) : (hp.fd[0].code & kFftFirstEven) && hp.fd[0].nst > 1;
+    const bool hin = ANY || ((hp.fd[0].code & kFftFirstEven) && hp.fd[0].nst > 1);
     const int nz0 = (hin ? g.Lx : 2 * g.Lx) - g.nx;
     if (nz0 > 0) {
       const FDiv dz = fdiv_of(nz0);
@@ -2237,7 +2279,7 @@ __global__ void __launch_bounds__(512) k_inv_x(Launch<T> L) {
       }
     }
     __syncthreads();
-    x_columns<T, false, SLX>(lds, hp.fd[0], cs, ncol, twl, hin);
+    x_columns<T, false, ANY>(lds, hp.fd[0], cs, ncol, twl, hin);
     // real-to-complex post-processing and transposed store (the rows this
     // workgroup read at the start)
     // layouts as for the load at the start
@@ -2283,24 +2325,24 @@ __global__ void __launch_bounds__(512) k_inv_x(Launch<T> L) {
   }
 }
 
-template <typename T, bool DEMAG, int CPT, bool CELLS, int SLX>
+template <typename T, bool DEMAG, int CPT, bool CELLS, bool ANY>
 void inv_x_launch_c(int mode, bool fuse, const Launch<T>& L, long long total, int nt, size_t lds, hipStream_t s) {
   const dim3 grid((unsigned)total);
   switch (mode) {
-    case MODE_FIELD: k_inv_x<T, DEMAG, MODE_FIELD, CPT, false, CELLS, SLX><<<grid, nt, lds, s>>>(L); break;
-    case MODE_RHS: k_inv_x<T, DEMAG, MODE_RHS, CPT, false, CELLS, SLX><<<grid, nt, lds, s>>>(L); break;
+    case MODE_FIELD: k_inv_x<T, DEMAG, MODE_FIELD, CPT, false, CELLS, ANY><<<grid, nt, lds, s>>>(L); break;
+    case MODE_RHS: k_inv_x<T, DEMAG, MODE_RHS, CPT, false, CELLS, ANY><<<grid, nt, lds, s>>>(L); break;
     case MODE_STAGE:
       if constexpr (DEMAG && CPT > 0) {
         if (fuse) {
-          k_inv_x<T, DEMAG, MODE_STAGE, CPT, true, CELLS, SLX><<<grid, nt, lds, s>>>(L);
+          k_inv_x<T, DEMAG, MODE_STAGE, CPT, true, CELLS, ANY><<<grid, nt, lds, s>>>(L);
           break;
         }
       }
-      if constexpr (SLX == 0) k_inv_x<T, DEMAG, MODE_STAGE, CPT, false, CELLS, SLX><<<grid, nt, lds, s>>>(L);
+      if constexpr (!ANY) k_inv_x<T, DEMAG, MODE_STAGE, CPT, false, CELLS, ANY><<<grid, nt, lds, s>>>(L);
       break;
-    case MODE_ERROR: k_inv_x<T, DEMAG, MODE_ERROR, CPT, false, CELLS, SLX><<<grid, nt, lds, s>>>(L); break;
-    case MODE_ENERGY: k_inv_x<T, DEMAG, MODE_ENERGY, CPT, false, CELLS, SLX><<<grid, nt, lds, s>>>(L); break;
-    default: k_inv_x<T, DEMAG, MODE_FIELD_ENERGY, CPT, false, CELLS, SLX><<<grid, nt, lds, s>>>(L); break;
+    case MODE_ERROR: k_inv_x<T, DEMAG, MODE_ERROR, CPT, false, CELLS, ANY><<<grid, nt, lds, s>>>(L); break;
+    case MODE_ENERGY: k_inv_x<T, DEMAG, MODE_ENERGY, CPT, false, CELLS, ANY><<<grid, nt, lds, s>>>(L); break;
+    default: k_inv_x<T, DEMAG, MODE_FIELD_ENERGY, CPT, false, CELLS, ANY><<<grid, nt, lds, s>>>(L); break;
   }
 }
 
@@ -2310,24 +2352,12 @@ template <typename T, bool DEMAG, bool CELLS>
 void inv_x_launch(int mode, int cpt, bool fuse, const Launch<T>& L, long long total, int nt, size_t lds,
                   hipStream_t s) {
   switch (cpt) {
-    case 1: inv_x_launch_c<T, DEMAG, 1, CELLS, 0>(mode, fuse, L, total, nt, lds, s); break;
-    case 2: inv_x_launch_c<T, DEMAG, 2, CELLS, 0>(mode, fuse, L, total, nt, lds, s); break;
-    case 4: inv_x_launch_c<T, DEMAG, 4, CELLS, 0>(mode, fuse, L, total, nt, lds, s); break;
-    case 8: inv_x_launch_c<T, DEMAG, 8, CELLS, 0>(mode, fuse, L, total, nt, lds, s); break;
-    default: inv_x_launch_c<T, DEMAG, 0, CELLS, 0>(mode, false, L, total, nt, lds, s); break;
+    case 1: inv_x_launch_c<T, DEMAG, 1, CELLS, false>(mode, fuse, L, total, nt, lds, s); break;
+    case 2: inv_x_launch_c<T, DEMAG, 2, CELLS, false>(mode, fuse, L, total, nt, lds, s); break;
+    case 4: inv_x_launch_c<T, DEMAG, 4, CELLS, false>(mode, fuse, L, total, nt, lds, s); break;
+    case 8: inv_x_launch_c<T, DEMAG, 8, CELLS, false>(mode, fuse, L, total, nt, lds, s); break;
+    default: inv_x_launch_c<T, DEMAG, 0, CELLS, false>(mode, false, L, total, nt, lds, s); break;
   }
-}
-
-// The same compiled for Lx = SLX (1 or 2 cells a thread; inv_x_static() says
-// where it applies).  The kernel above holds the transforms of every length and
-// takes 121 registers whatever its epilogue; compiled for one length it takes 83
-// with one cell a thread (144 above; 104 for 166 with a stage epilogue) and 60 to
-// 93 with two (122), five to eight waves a SIMD instead of three or four.
-template <typename T, bool CELLS, int SLX>
-void inv_x_launch_l(int mode, int cpt, bool fuse, const Launch<T>& L, long long total, int nt, size_t lds,
-                    hipStream_t s) {
-  if (cpt == 1) inv_x_launch_c<T, true, 1, CELLS, SLX>(mode, fuse, L, total, nt, lds, s);
-  else inv_x_launch_c<T, true, 2, CELLS, SLX>(mode, fuse, L, total, nt, lds, s);
 }
 
 template <typename T, int M>
@@ -2356,36 +2386,34 @@ void yzy_launch(int m, int sl, const Launch<T>& L, long long total, int nt, size
   X(576) X(648) X(768)
 
 template <typename T>
-void fwd_x_launch_m(int len, const Launch<T>& L, long long total, int nt, size_t lds, hipStream_t s) {
-#define MMX_CASE(LL) \
-  case LL: k_fwd_x<T, LL, true><<<dim3((unsigned)total), nt, lds, s>>>(L); break;
-  switch (len) { MMX_SR_LENGTHS(MMX_CASE) default: break; }
-#undef MMX_CASE
+void fwd_x_launch_m(const Launch<T>& L, long long total, int nt, size_t lds, hipStream_t s) {
+  k_fwd_x<T, -1, true><<<dim3((unsigned)total), nt, lds, s>>>(L);
 }
 
+// m: Pz / 2 of the launch's fused 3-D groups, 0 none
 template <typename T>
-void y_launch_m(bool inv, int len, const Launch<T>& L, long long total, int nt, size_t lds, hipStream_t s) {
-#define MMX_CASE(LL)                                                        \
-  case LL:                                                                  \
-    if (inv) k_yinv_m<T, LL><<<dim3((unsigned)total), nt, lds, s>>>(L);     \
-    else k_ypass_m<T, LL><<<dim3((unsigned)total), nt, lds, s>>>(L);        \
-    break;
-  switch (len) { MMX_SR_LENGTHS(MMX_CASE) default: break; }
-#undef MMX_CASE
+void y_launch_m(int m, const Launch<T>& L, long long total, int nt, size_t lds, hipStream_t s) {
+  const dim3 grid((unsigned)total);
+  switch (m) {
+    case 2: k_ypass_m<T, 2><<<grid, nt, lds, s>>>(L); break;
+    case 3: k_ypass_m<T, 3><<<grid, nt, lds, s>>>(L); break;
+    case 4: k_ypass_m<T, 4><<<grid, nt, lds, s>>>(L); break;
+    default: k_ypass_m<T, 0><<<grid, nt, lds, s>>>(L); break;
+  }
+}
+template <typename T>
+void yinv_launch_m(const Launch<T>& L, long long total, int nt, size_t lds, hipStream_t s) {
+  k_yinv_m<T><<<dim3((unsigned)total), nt, lds, s>>>(L);
 }
 
-// Powers of two (two translation units: below 256, and from there).
-template <typename T, bool CELLS, bool LONG>
-void inv_x_launch_s(int len, int mode, int cpt, bool fuse, const Launch<T>& L, long long total, int nt, size_t lds,
-                    hipStream_t s) {
-#define MMX_CASE(LL) \
-  case LL: inv_x_launch_l<T, CELLS, LL>(mode, cpt, fuse, L, total, nt, lds, s); break;
-  if constexpr (LONG) {
-    switch (len) { MMX_CASE(256) MMX_CASE(512) MMX_CASE(1024) default: break; }
-  } else {
-    switch (len) { MMX_CASE(32) MMX_CASE(64) MMX_CASE(128) default: break; }
-  }
-#undef MMX_CASE
+// The inverse-x pass compiled for the lengths of the list and 1024, each group by
+// its own; inv_x_any() says where it applies.  inv_x_launch()'s kernels hold the
+// run-time engine and take 121 registers whatever their epilogue; these take 83
+// with one cell a thread (144 there; 103 for 166 with a stage epilogue) and 60 to
+// 97 with two (122), four to eight waves a SIMD instead of three or four.
+template <typename T, bool CELLS, int CPT>
+void inv_x_launch_any(int mode, bool fuse, const Launch<T>& L, long long total, int nt, size_t lds, hipStream_t s) {
+  inv_x_launch_c<T, true, CPT, CELLS, true>(mode, fuse, L, total, nt, lds, s);
 }
 
 }  // namespace mmx

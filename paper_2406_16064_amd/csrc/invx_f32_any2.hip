@@ -1,0 +1,6 @@
+// Inverse-x pass of the compiled lengths, each group by its own (float, 2 cells a thread).
+#include "hotpath.hpp"
+
+namespace mmx {
+template void inv_x_launch_any<float, false, 2>(int, bool, const Launch<float>&, long long, int, size_t, hipStream_t);
+}  // namespace mmx

@@ -107,7 +107,7 @@ template <typename T> struct HotPlan {
   const DevParams* prm;    // [batch]
   const T* cells;          // cell-based material [batch][3][N] (Ms, A, D per cell) or null
   int gen;                 // launch the general-material form of the inverse-x epilogue
-  int pad_;
+  int shx;                 // LDS padding shift of the compiled x plan (sr_psh(Lx)) where Lx is compiled or 1024
 };
 
 constexpr int kMaxGroups = 16;

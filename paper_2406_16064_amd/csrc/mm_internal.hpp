@@ -143,9 +143,9 @@ __host__ __device__ constexpr int sr_psh(int L) {
 }
 // The lengths with kernels compiled so (y columns, and x rows by Lx = Px / 2).
 __host__ __device__ constexpr bool sr_compiled(int L) {
-  return L == 32 || L == 48 || L == 64 || L == 72 || L == 96 || L == 108 || L == 128 || L == 144 || L == 162 ||
-         L == 192 || L == 216 || L == 256 || L == 288 || L == 324 || L == 384 || L == 432 || L == 512 || L == 576 ||
-         L == 648 || L == 768;
+  return L == 16 || L == 24 || L == 32 || L == 36 || L == 48 || L == 54 || L == 64 || L == 72 || L == 96 ||
+         L == 108 || L == 128 || L == 144 || L == 162 || L == 192 || L == 216 || L == 256 || L == 288 || L == 324 ||
+         L == 384 || L == 432 || L == 512 || L == 576 || L == 648 || L == 768 || L == 864 || L == 972;
 }
 
 constexpr uint32_t kFftFirstEven = 1u << 30;

@@ -477,6 +477,10 @@ mm_status choose_tuning(Group& G, mm_precision prec, size_t csz, long long launc
     while (ty > g.ny) ty /= 2;  // a power of two (the kernels split rows by shifts)
     if ((size_t)3 * ty * rowb + xtab > 160 * 1024 || 3 * ty * tpx > 512)
       return fail(MM_E_ARG, "mesh too long along x");
+    // compiled lengths keep one plan whatever the launch: at most four cells a
+    // thread and a column's threads in the workgroup
+    const bool list = sr_compiled(g.Lx);
+    while (list && ty > 1 && (3 * ty * sr_tpc(g.Lx) > 512 || ty * g.nx > 2048)) ty /= 2;
     t.ty_x = ty;
     // Threads.  One cell a thread is the shortest chain but takes 145-166
     // registers (three waves a SIMD, and one workgroup of 512 threads a CU):
@@ -493,7 +497,8 @@ mm_status choose_tuning(Group& G, mm_precision prec, size_t csz, long long launc
     else if (wgs <= 512) nt = pow2ceil((int)std::min<long long>(std::max<long long>(3LL * ty * g.Lx / 8, cells / 2), 512));
     else if (2 * ((size_t)3 * ty * rowb + xtab) > 160 * 1024) nt = 512;
     else nt = cells <= 1024 ? pow2ceil((int)std::min<long long>(std::max<long long>(cells / 2, 64), 256)) : 512;
-    t.nt_i = std::min(512, std::max(64, pow2ceil(std::max(3 * ty * tpx, nt))));
+    const int columns = list && (g.Lx & (g.Lx - 1)) != 0 ? 3 * ty * sr_tpc(g.Lx) : 3 * ty * tpx;
+    t.nt_i = std::min(512, std::max(64, pow2ceil(std::max(columns, nt))));
     t.tpc_x = t.nt_i / (3 * ty);
   }
   const int tmin = tpc_for(g.Py, true);
@@ -953,6 +958,7 @@ mm_status make_set(Engine& E, const std::vector<int>& nb, GroupSet<T>& gs, std::
     h.prm = E.prm + acc;
     h.cells = E.use_general ? (const T*)G.cells : nullptr;
     h.gen = E.use_general ? 1 : 0;
+    h.shx = sr_compiled(G.g.Lx) || G.g.Lx == 1024 ? sr_psh(G.g.Lx) : 31;
     inst0[i] = acc;
     acc += nb[i];
   }

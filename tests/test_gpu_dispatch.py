@@ -134,3 +134,65 @@ def test_parameter_tables_follow_every_call(mm, n):
             got = plan.llg_rhs(p, m[k][:nb])
         torch.cuda.synchronize()
         assert torch.equal(got, fresh)
+
+
+LENGTHS = (16, 24, 32, 36, 48, 54, 64, 72, 96, 108, 128, 144, 162, 192, 216, 256, 288, 324, 384, 432, 512, 576, 648,
+           768, 864, 972)
+
+
+def _smooth(n):
+    for q in (2, 3):
+        while n % q == 0:
+            n //= q
+    return n == 1
+
+
+def _short_rows(L):
+    """The smallest n whose padded length is L (2n where that is 3-smooth, else the smallest 3-smooth >= 2n - 1)."""
+    def padded(n):
+        return 2 * n if _smooth(2 * n) else next(P for P in range(2 * n - 1, 4 * n) if _smooth(P))
+    return next(n for n in range(2, L // 2 + 1) if padded(n) == L)
+
+
+@pytest.mark.parametrize("prec,tol", [("f32", 1e-5), ("f64", 1e-11)])
+@pytest.mark.parametrize("L", LENGTHS)
+def test_compiled_lengths(mm, L, prec, tol):
+    """Every compiled transform length against the oracle: rows with Lx = L
+    (whole, and one cell short of it where the row still pads to 2 L), columns
+    with Py = L (half of it, and the shortest that pads to it), as films, fused
+    planes (nz = 2) and separate passes (nz = 5)."""
+    gp, op = gpu_params(mm, PAR, F.ALL_TERMS), oracle_params(PAR, F.ALL_TERMS)
+    sizes = [(L, 5, 1), (L - 1, 3, 1), (6, L // 2, 1), (6, _short_rows(L), 1), (5, L // 2, 2), (4, _short_rows(L), 5)]
+    for k, n in enumerate(sizes):
+        mesh = n + (3e-9, 2e-9, 2.5e-9)
+        plan = mm.Plan(mesh, prec, terms=F.ALL_TERMS)
+        if k in (2, 3, 4, 5):
+            assert plan.padded()[1] == L
+        m = representable(_m(mesh, 60 + k), plan.dtype)
+        H = plan.effective_field(gp, to_dev(m, plan.dtype)).double().cpu().numpy()
+        kern = F.DemagKernel(F.Mesh(*mesh))
+        assert field_err(H, F.effective_field(m, F.Mesh(*mesh), op, kern)) <= tol, n
+
+
+@pytest.mark.parametrize("n", [24, 81, 100, 128, 162, 200])
+def test_compiled_rows_in_stages_fp64(mm, n):
+    """Dormand-Prince attempts (stage kernels with the next forward x pass, the
+    error pass) on rows of compiled and other lengths, in the default launch shape
+    and with one to four cells a thread: every trajectory against the oracle's."""
+    mesh = (n, 6, 1, 2e-9, 2e-9, 2e-9)
+    gp, op = gpu_params(mm, PAR, F.ALL_TERMS), oracle_params(PAR, F.ALL_TERMS)
+    kern = F.DemagKernel(F.Mesh(*mesh))
+    m0 = [_m(mesh, 70 + i) for i in range(2)]
+    mo = [dp45.run(lambda y: F.llg_rhs(y, F.Mesh(*mesh), op, kern), m, dp45.State(h=1e-14, h_max=1e-14), t_end=3e-14)
+          for m in m0]
+    for nt, ty in ((None, None), (64, 1), (128, 2), (256, 4)):
+        plan = mm.Plan(mesh, "f64", terms=F.ALL_TERMS, max_batch=2)
+        if ty:
+            try:
+                plan.set_shapes(dict(ty_x=ty, nt_i=nt))
+            except mm.MMError:
+                continue
+        md = to_dev(np.stack(m0), torch.float64)
+        st = mm.new_states(2, h=1e-14, h_max=1e-14)
+        plan.rk45_run([gp, gp], md, st, t_end=3e-14)
+        assert np.max(np.abs(md.cpu().numpy() - np.stack(mo))) <= 1e-9
