@@ -42,6 +42,12 @@ extern template void inv_x_launch_any<double, false, 2>(int, bool, const Launch<
 extern template void inv_x_launch_any<double, false, 4>(int, bool, const Launch<double>&, long long, int, size_t, hipStream_t);
 extern template void inv_x_launch_any<double, true, 1>(int, bool, const Launch<double>&, long long, int, size_t, hipStream_t);
 extern template void inv_x_launch_any<double, true, 2>(int, bool, const Launch<double>&, long long, int, size_t, hipStream_t);
+extern template void len_launch<float>(int, int, const Launch<float>&, long long, int, size_t, hipStream_t);
+extern template void inv_x_launch_len<float, 1>(int, int, const Launch<float>&, long long, int, size_t, hipStream_t);
+extern template void inv_x_launch_len<float, 2>(int, int, const Launch<float>&, long long, int, size_t, hipStream_t);
+extern template void len_launch<double>(int, int, const Launch<double>&, long long, int, size_t, hipStream_t);
+extern template void inv_x_launch_len<double, 1>(int, int, const Launch<double>&, long long, int, size_t, hipStream_t);
+extern template void inv_x_launch_len<double, 2>(int, int, const Launch<double>&, long long, int, size_t, hipStream_t);
 extern template void yzy_launch<float>(int, int, const Launch<float>&, long long, int, size_t, hipStream_t);
 extern template void yzy_launch<double>(int, int, const Launch<double>&, long long, int, size_t, hipStream_t);
 
@@ -611,7 +617,8 @@ hipError_t launch_eval(const GroupSet<T>& gs, const Epi<T>* epis, int mode, bool
         if (lb.total == 0) continue;  // no instance of these meshes in this launch
         const dim3 grid((unsigned)lb.total);
         if (keys[kk] == kMixKey) {
-          fwd_x_launch_m<T>(lb.L, lb.total, nt, lds, s);
+          if (gs.n == 1) len_launch<T>(0, gs.h[0].g.Lx, lb.L, lb.total, nt, lds, s);
+          else fwd_x_launch_m<T>(lb.L, lb.total, nt, lds, s);
           continue;
         }
         switch (keys[kk]) {
@@ -671,7 +678,8 @@ hipError_t launch_eval(const GroupSet<T>& gs, const Epi<T>* epis, int mode, bool
       }
       if (lb.total == 0) continue;
       if (keys[kk] / 32 == kMixKey) {
-        y_launch_m<T>(m, lb.L, lb.total, nt, lds, s);
+        if (gs.n == 1 && m == 0) len_launch<T>(1, gs.h[0].g.Py, lb.L, lb.total, nt, lds, s);
+        else y_launch_m<T>(m, lb.L, lb.total, nt, lds, s);
         continue;
       }
       if (m > 0) {
@@ -771,7 +779,8 @@ hipError_t launch_eval(const GroupSet<T>& gs, const Epi<T>* epis, int mode, bool
       }
       if (ly.total == 0) continue;
       if (keys[kk] == kMixKey) {
-        yinv_launch_m<T>(ly.L, ly.total, nty, ldsy, s);
+        if (gs.n == 1) len_launch<T>(2, gs.h[0].g.Py, ly.L, ly.total, nty, ldsy, s);
+        else yinv_launch_m<T>(ly.L, ly.total, nty, ldsy, s);
         continue;
       }
       int nts = 0, ept = 16;
@@ -825,6 +834,9 @@ hipError_t launch_eval(const GroupSet<T>& gs, const Epi<T>* epis, int mode, bool
       if (part == 0 && gen) {
         if (cpt == 1) inv_x_launch_any<T, true, 1>(mode, fuse, lb.L, lb.total, nt, lds, s);
         else inv_x_launch_any<T, true, 2>(mode, fuse, lb.L, lb.total, nt, lds, s);
+      } else if (part == 0 && gs.n == 1 && cpt <= 2 && mode != MODE_ENERGY && mode != MODE_FIELD_ENERGY) {
+        if (cpt == 1) inv_x_launch_len<T, 1>(mode, gs.h[0].g.Lx, lb.L, lb.total, nt, lds, s);
+        else inv_x_launch_len<T, 2>(mode, gs.h[0].g.Lx, lb.L, lb.total, nt, lds, s);
       } else if (part == 0) {
         if (cpt == 1) inv_x_launch_any<T, false, 1>(mode, fuse, lb.L, lb.total, nt, lds, s);
         else if (cpt == 2) inv_x_launch_any<T, false, 2>(mode, fuse, lb.L, lb.total, nt, lds, s);

@@ -175,15 +175,10 @@ struct XRowLoad {
   }
 };
 
-// One case for every compiled length.
-#define MMX_SR_LENGTHS(X) \
-  X(16) X(24) X(32) X(36) X(48) X(54) X(64) X(72) X(96) X(108) X(128) X(144) X(162) X(192) X(216) X(256) X(288) \
-  X(324) X(384) X(432) X(512) X(576) X(648) X(768) X(864) X(972)
-
 // SLX: 0 for any group, else the one length Lx of every group, all with an
 // even nx = Lx (a kernel holding one static transform keeps fewer registers);
-// MIX: every group has a compiled Lx and any nx, the transform of fft_mix
-// (sr_tpc(Lx) threads a row).
+// MIX: every group has a compiled Lx (SLX = -1: its own) and any nx, the
+// transform of fft_mix (sr_tpc(Lx) threads a row).
 template <typename T, int SLX, bool MIX = false>
 __global__ void __launch_bounds__(512) k_fwd_x(Launch<T> L) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -222,9 +217,12 @@ __global__ void __launch_bounds__(512) k_fwd_x(Launch<T> L) {
   const bool hin = ld.pairs && g.nx == g.Lx;
   const NoStore<T> nst;
   if constexpr (MIX) {
-    switch (g.Lx) {
-#define MMX_CASE(LL) \
-  case LL: fft_mix<T, LL, false, true, false, true, true, false, true>(lds, twl, cs, nrow, ld, nst, hook); break;
+    switch (SLX > 0 ? SLX : g.Lx) {
+#define MMX_CASE(LL)                                                                                  \
+  case LL:                                                                                            \
+    if constexpr (SLX <= 0 || SLX == LL)                                                              \
+      fft_mix<T, LL, false, true, false, true, true, false, true>(lds, twl, cs, nrow, ld, nst, hook); \
+    break;
       MMX_SR_LENGTHS(MMX_CASE)
 #undef MMX_CASE
       default: break;
@@ -840,7 +838,9 @@ __global__ void __launch_bounds__(512) k_yinv_s(Launch<T> L) {
 // groups take the fused y and z passes with Pz = 2 M.  The run-time engine holds
 // every radix with a predicate a butterfly: 160 registers in FP32, three waves a
 // SIMD, and three times the time a point of these.
-template <typename T, int M>
+// SL > 0: all have Py = SL (a kernel of its own is 2 to 4% faster where a launch is
+// one short chain: no switch to fetch).
+template <typename T, int M, int SL>
 __global__ void __launch_bounds__(512) k_ypass_m(Launch<T> L) {
   extern __shared__ __align__(16) unsigned char smem[];
   Cx<T>* lds = reinterpret_cast<Cx<T>*>(smem);
@@ -852,12 +852,14 @@ __global__ void __launch_bounds__(512) k_ypass_m(Launch<T> L) {
                                                                 : y3d_blocks(g, hp.tu, hp.batch)))
     return;
   const Epi<T> ep = ldu(L.epis + gi);
-  switch (g.Py) {
+  switch (SL > 0 ? SL : g.Py) {
 #define MMX_CASE(LL)                                                            \
   case LL:                                                                      \
-    if (g.nz == 1) y_fused2d<T, false, LL, 8, true>(hp, ep, bid, lds);          \
-    else if constexpr (M > 0) yzy3d<T, M, LL, true>(hp, ep, bid, lds);          \
-    else y_rows3d<T, false, false, LL, 8, true>(hp, ep, bid, lds);              \
+    if constexpr (SL == 0 || SL == LL) {                                        \
+      if (g.nz == 1) y_fused2d<T, false, LL, 8, true>(hp, ep, bid, lds);        \
+      else if constexpr (M > 0) yzy3d<T, M, LL, true>(hp, ep, bid, lds);        \
+      else y_rows3d<T, false, false, LL, 8, true>(hp, ep, bid, lds);            \
+    }                                                                           \
     break;
     MMX_SR_LENGTHS(MMX_CASE)
 #undef MMX_CASE
@@ -865,7 +867,7 @@ __global__ void __launch_bounds__(512) k_ypass_m(Launch<T> L) {
   }
 }
 
-template <typename T>
+template <typename T, int SL>
 __global__ void __launch_bounds__(512) k_yinv_m(Launch<T> L) {
   extern __shared__ __align__(16) unsigned char smem[];
   Cx<T>* lds = reinterpret_cast<Cx<T>*>(smem);
@@ -874,9 +876,9 @@ __global__ void __launch_bounds__(512) k_yinv_m(Launch<T> L) {
   const HotPlan<T> hp = hot_plan(L, gi);
   if (bid >= y3d_blocks(hp.g, hp.tu, hp.batch)) return;
   const Epi<T> ep = ldu(L.epis + gi);
-  switch (hp.g.Py) {
+  switch (SL > 0 ? SL : hp.g.Py) {
 #define MMX_CASE(LL) \
-  case LL: y_rows3d<T, true, false, LL, 8, true>(hp, ep, bid, lds); break;
+  case LL: if constexpr (SL == 0 || SL == LL) y_rows3d<T, true, false, LL, 8, true>(hp, ep, bid, lds); break;
     MMX_SR_LENGTHS(MMX_CASE)
 #undef MMX_CASE
     default: break;
@@ -1691,18 +1693,21 @@ __device__ __forceinline__ V3<T> ll_rhs(V3<T> m, V3<T> H, T g1, T g2) {
 // launch shapes give every column that many), the general plan otherwise.
 // Inverse: only the first half of the output is kept; forward: hin as for
 // fft_run (the input's upper half is zero and not read).
-// ANY: the length is one of the list or 1024, sr_tpc(L) threads a column.
-template <typename T, bool INV, bool ANY = false>
+// LEN: the length, or -1 for one of the list or 1024; sr_tpc(L) threads a column.
+template <typename T, bool INV, int LEN = 0>
 __device__ __forceinline__ void x_columns(Cx<T>* lds, const FftDesc<T>& p, int cs, int ncol, const Cx<T>* twl,
                                           bool hin) {
   constexpr bool HIN = !INV, HOUT = INV;
   const NoLoad<T> nl;
   const NoStore<T> nst;
   const NoHook nh;
-  if constexpr (ANY) {
-    switch (p.L) {
-#define MMX_CASE(LL) \
-  case LL: fft_mix<T, LL, INV, false, false, true, HIN, HOUT, false>(lds, twl, cs, ncol, nl, nst, nh); break;
+  if constexpr (LEN != 0) {
+    switch (LEN > 0 ? LEN : p.L) {
+#define MMX_CASE(LL)                                                                                 \
+  case LL:                                                                                           \
+    if constexpr (LEN < 0 || LEN == LL)                                                              \
+      fft_mix<T, LL, INV, false, false, true, HIN, HOUT, false>(lds, twl, cs, ncol, nl, nst, nh);    \
+    break;
       MMX_SR_LENGTHS(MMX_CASE) MMX_CASE(1024)
 #undef MMX_CASE
       default: break;
@@ -1957,7 +1962,7 @@ __device__ __forceinline__ void energy_pass_end(const double (&esum)[5], double*
 // Ms, A_ij, D_ij, an empty cell gets no demag field either, energies weight
 // each cell by its Ms, and with cell arrays the fused forward transform takes
 // Ms m.
-template <typename T, bool DEMAG, int MODE, int CPT, bool FUSE, bool CELLS, bool ANY>
+template <typename T, bool DEMAG, int MODE, int CPT, bool FUSE, bool CELLS, int LEN>
 __global__ void __launch_bounds__(512) k_inv_x(Launch<T> L) {
   constexpr bool PREF = CPT == 1;
   static_assert(!FUSE || (MODE == MODE_STAGE && DEMAG && CPT > 0), "fused forward pass needs a stage epilogue");
@@ -1982,7 +1987,7 @@ __global__ void __launch_bounds__(512) k_inv_x(Launch<T> L) {
   const int y0 = tile * TY;
   const int nrow = g.ny - y0 < TY ? g.ny - y0 : TY;
   const int cs = col_stride(g.Lx);
-  const int sh = ANY ? hp.shx : hp.fd[0].psh;
+  const int sh = LEN > 0 ? sr_psh(LEN > 0 ? LEN : 32) : LEN < 0 ? hp.shx : hp.fd[0].psh;
 
   // Spectrum tile: column c * TY + r holds component c of row y0 + r (rows past
   // the mesh are left out: only the epilogue's rows are read back).
@@ -2107,7 +2112,7 @@ __global__ void __launch_bounds__(512) k_inv_x(Launch<T> L) {
     }
     __syncthreads();
     // the epilogue reads complex entries below ceil(nx / 2) <= Lx / 2 only
-    x_columns<T, true, ANY>(lds, hp.fd[0], cs, ncol, twl, false);
+    x_columns<T, true, LEN>(lds, hp.fd[0], cs, ncol, twl, false);
   }
 
   // ----- epilogue ----- (its arguments are read only now, which keeps the
@@ -2258,7 +2263,7 @@ __global__ void __launch_bounds__(512) k_inv_x(Launch<T> L) {
     // half-length input end, else 2 Lx)
     T* const re = reinterpret_cast<T*>(lds);
     const int rcs = 2 * cs;
-    const bool hin = ANY || ((hp.fd[0].code & kFftFirstEven) && hp.fd[0].nst > 1);
+    const bool hin = LEN != 0 || ((hp.fd[0].code & kFftFirstEven) && hp.fd[0].nst > 1);
     const int nz0 = (hin ? g.Lx : 2 * g.Lx) - g.nx;
     if (nz0 > 0) {
       const FDiv dz = fdiv_of(nz0);
@@ -2279,7 +2284,7 @@ __global__ void __launch_bounds__(512) k_inv_x(Launch<T> L) {
       }
     }
     __syncthreads();
-    x_columns<T, false, ANY>(lds, hp.fd[0], cs, ncol, twl, hin);
+    x_columns<T, false, LEN>(lds, hp.fd[0], cs, ncol, twl, hin);
     // real-to-complex post-processing and transposed store (the rows this
     // workgroup read at the start)
     // layouts as for the load at the start
@@ -2325,24 +2330,24 @@ __global__ void __launch_bounds__(512) k_inv_x(Launch<T> L) {
   }
 }
 
-template <typename T, bool DEMAG, int CPT, bool CELLS, bool ANY>
+template <typename T, bool DEMAG, int CPT, bool CELLS, int LEN>
 void inv_x_launch_c(int mode, bool fuse, const Launch<T>& L, long long total, int nt, size_t lds, hipStream_t s) {
   const dim3 grid((unsigned)total);
   switch (mode) {
-    case MODE_FIELD: k_inv_x<T, DEMAG, MODE_FIELD, CPT, false, CELLS, ANY><<<grid, nt, lds, s>>>(L); break;
-    case MODE_RHS: k_inv_x<T, DEMAG, MODE_RHS, CPT, false, CELLS, ANY><<<grid, nt, lds, s>>>(L); break;
+    case MODE_FIELD: k_inv_x<T, DEMAG, MODE_FIELD, CPT, false, CELLS, LEN><<<grid, nt, lds, s>>>(L); break;
+    case MODE_RHS: k_inv_x<T, DEMAG, MODE_RHS, CPT, false, CELLS, LEN><<<grid, nt, lds, s>>>(L); break;
     case MODE_STAGE:
       if constexpr (DEMAG && CPT > 0) {
         if (fuse) {
-          k_inv_x<T, DEMAG, MODE_STAGE, CPT, true, CELLS, ANY><<<grid, nt, lds, s>>>(L);
+          k_inv_x<T, DEMAG, MODE_STAGE, CPT, true, CELLS, LEN><<<grid, nt, lds, s>>>(L);
           break;
         }
       }
-      if constexpr (!ANY) k_inv_x<T, DEMAG, MODE_STAGE, CPT, false, CELLS, ANY><<<grid, nt, lds, s>>>(L);
+      if constexpr (LEN == 0) k_inv_x<T, DEMAG, MODE_STAGE, CPT, false, CELLS, LEN><<<grid, nt, lds, s>>>(L);
       break;
-    case MODE_ERROR: k_inv_x<T, DEMAG, MODE_ERROR, CPT, false, CELLS, ANY><<<grid, nt, lds, s>>>(L); break;
-    case MODE_ENERGY: k_inv_x<T, DEMAG, MODE_ENERGY, CPT, false, CELLS, ANY><<<grid, nt, lds, s>>>(L); break;
-    default: k_inv_x<T, DEMAG, MODE_FIELD_ENERGY, CPT, false, CELLS, ANY><<<grid, nt, lds, s>>>(L); break;
+    case MODE_ERROR: k_inv_x<T, DEMAG, MODE_ERROR, CPT, false, CELLS, LEN><<<grid, nt, lds, s>>>(L); break;
+    case MODE_ENERGY: k_inv_x<T, DEMAG, MODE_ENERGY, CPT, false, CELLS, LEN><<<grid, nt, lds, s>>>(L); break;
+    default: k_inv_x<T, DEMAG, MODE_FIELD_ENERGY, CPT, false, CELLS, LEN><<<grid, nt, lds, s>>>(L); break;
   }
 }
 
@@ -2352,11 +2357,11 @@ template <typename T, bool DEMAG, bool CELLS>
 void inv_x_launch(int mode, int cpt, bool fuse, const Launch<T>& L, long long total, int nt, size_t lds,
                   hipStream_t s) {
   switch (cpt) {
-    case 1: inv_x_launch_c<T, DEMAG, 1, CELLS, false>(mode, fuse, L, total, nt, lds, s); break;
-    case 2: inv_x_launch_c<T, DEMAG, 2, CELLS, false>(mode, fuse, L, total, nt, lds, s); break;
-    case 4: inv_x_launch_c<T, DEMAG, 4, CELLS, false>(mode, fuse, L, total, nt, lds, s); break;
-    case 8: inv_x_launch_c<T, DEMAG, 8, CELLS, false>(mode, fuse, L, total, nt, lds, s); break;
-    default: inv_x_launch_c<T, DEMAG, 0, CELLS, false>(mode, false, L, total, nt, lds, s); break;
+    case 1: inv_x_launch_c<T, DEMAG, 1, CELLS, 0>(mode, fuse, L, total, nt, lds, s); break;
+    case 2: inv_x_launch_c<T, DEMAG, 2, CELLS, 0>(mode, fuse, L, total, nt, lds, s); break;
+    case 4: inv_x_launch_c<T, DEMAG, 4, CELLS, 0>(mode, fuse, L, total, nt, lds, s); break;
+    case 8: inv_x_launch_c<T, DEMAG, 8, CELLS, 0>(mode, fuse, L, total, nt, lds, s); break;
+    default: inv_x_launch_c<T, DEMAG, 0, CELLS, 0>(mode, false, L, total, nt, lds, s); break;
   }
 }
 
@@ -2380,10 +2385,6 @@ void yzy_launch(int m, int sl, const Launch<T>& L, long long total, int nt, size
   }
 }
 
-// One case for every compiled length.
-#define MMX_SR_LENGTHS(X) \
-  X(32) X(48) X(64) X(72) X(96) X(108) X(128) X(144) X(162) X(192) X(216) X(256) X(288) X(324) X(384) X(432) X(512) \
-  X(576) X(648) X(768)
 
 template <typename T>
 void fwd_x_launch_m(const Launch<T>& L, long long total, int nt, size_t lds, hipStream_t s) {
@@ -2395,15 +2396,52 @@ template <typename T>
 void y_launch_m(int m, const Launch<T>& L, long long total, int nt, size_t lds, hipStream_t s) {
   const dim3 grid((unsigned)total);
   switch (m) {
-    case 2: k_ypass_m<T, 2><<<grid, nt, lds, s>>>(L); break;
-    case 3: k_ypass_m<T, 3><<<grid, nt, lds, s>>>(L); break;
-    case 4: k_ypass_m<T, 4><<<grid, nt, lds, s>>>(L); break;
-    default: k_ypass_m<T, 0><<<grid, nt, lds, s>>>(L); break;
+    case 2: k_ypass_m<T, 2, 0><<<grid, nt, lds, s>>>(L); break;
+    case 3: k_ypass_m<T, 3, 0><<<grid, nt, lds, s>>>(L); break;
+    case 4: k_ypass_m<T, 4, 0><<<grid, nt, lds, s>>>(L); break;
+    default: k_ypass_m<T, 0, 0><<<grid, nt, lds, s>>>(L); break;
   }
 }
 template <typename T>
 void yinv_launch_m(const Launch<T>& L, long long total, int nt, size_t lds, hipStream_t s) {
-  k_yinv_m<T><<<dim3((unsigned)total), nt, lds, s>>>(L);
+  k_yinv_m<T, 0><<<dim3((unsigned)total), nt, lds, s>>>(L);
+}
+
+// The same for launches of one length, which have kernels of their own: pass 0
+// forward x, 1 y (films and separate 3-D passes), 2 inverse y.
+template <typename T>
+void len_launch(int pass, int len, const Launch<T>& L, long long total, int nt, size_t lds, hipStream_t s) {
+  const dim3 grid((unsigned)total);
+  switch (len) {
+#define MMX_CASE(LL)                                                        \
+  case LL:                                                                  \
+    if (pass == 0) k_fwd_x<T, LL, true><<<grid, nt, lds, s>>>(L);           \
+    else if (pass == 1) k_ypass_m<T, 0, LL><<<grid, nt, lds, s>>>(L);       \
+    else k_yinv_m<T, LL><<<grid, nt, lds, s>>>(L);                          \
+    break;
+    MMX_SR_LENGTHS(MMX_CASE)
+#undef MMX_CASE
+    default: break;
+  }
+}
+// Inverse x of one length, one or two cells a thread, uniform material: field,
+// dm/dt, stage (with the next forward pass) and error epilogues.
+template <typename T, int CPT>
+void inv_x_launch_len(int mode, int len, const Launch<T>& L, long long total, int nt, size_t lds, hipStream_t s) {
+  const dim3 grid((unsigned)total);
+  switch (len) {
+#define MMX_CASE(LL)                                                                                              \
+  case LL:                                                                                                        \
+    if (mode == MODE_FIELD) k_inv_x<T, true, MODE_FIELD, CPT, false, false, LL><<<grid, nt, lds, s>>>(L);         \
+    else if (mode == MODE_RHS) k_inv_x<T, true, MODE_RHS, CPT, false, false, LL><<<grid, nt, lds, s>>>(L);        \
+    else if (mode == MODE_STAGE) k_inv_x<T, true, MODE_STAGE, CPT, true, false, LL><<<grid, nt, lds, s>>>(L);     \
+    else k_inv_x<T, true, MODE_ERROR, CPT, false, false, LL><<<grid, nt, lds, s>>>(L);                            \
+    break;
+    MMX_SR_LENGTHS(MMX_CASE)
+    MMX_CASE(1024)
+#undef MMX_CASE
+    default: break;
+  }
 }
 
 // The inverse-x pass compiled for the lengths of the list and 1024, each group by
@@ -2413,7 +2451,7 @@ void yinv_launch_m(const Launch<T>& L, long long total, int nt, size_t lds, hipS
 // 97 with two (122), four to eight waves a SIMD instead of three or four.
 template <typename T, bool CELLS, int CPT>
 void inv_x_launch_any(int mode, bool fuse, const Launch<T>& L, long long total, int nt, size_t lds, hipStream_t s) {
-  inv_x_launch_c<T, true, CPT, CELLS, true>(mode, fuse, L, total, nt, lds, s);
+  inv_x_launch_c<T, true, CPT, CELLS, -1>(mode, fuse, L, total, nt, lds, s);
 }
 
 }  // namespace mmx

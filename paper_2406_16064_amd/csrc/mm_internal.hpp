@@ -142,10 +142,13 @@ __host__ __device__ constexpr int sr_psh(int L) {
   return 3;
 }
 // The lengths with kernels compiled so (y columns, and x rows by Lx = Px / 2).
+#define MMX_SR_LENGTHS(X) \
+  X(16) X(24) X(32) X(36) X(48) X(54) X(64) X(72) X(96) X(108) X(128) X(144) X(162) X(192) X(216) X(256) X(288) \
+  X(324) X(384) X(432) X(512) X(576) X(648) X(768) X(864) X(972)
 __host__ __device__ constexpr bool sr_compiled(int L) {
-  return L == 16 || L == 24 || L == 32 || L == 36 || L == 48 || L == 54 || L == 64 || L == 72 || L == 96 ||
-         L == 108 || L == 128 || L == 144 || L == 162 || L == 192 || L == 216 || L == 256 || L == 288 || L == 324 ||
-         L == 384 || L == 432 || L == 512 || L == 576 || L == 648 || L == 768 || L == 864 || L == 972;
+#define MMX_CASE(LL) || L == LL
+  return false MMX_SR_LENGTHS(MMX_CASE);
+#undef MMX_CASE
 }
 
 constexpr uint32_t kFftFirstEven = 1u << 30;
