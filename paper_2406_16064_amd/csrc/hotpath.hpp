@@ -13,8 +13,8 @@
 //
 // Demag data flow for one evaluation (all FP32 or all FP64):
 //   x pass   m[3][nz][ny][nx] -> real-to-complex along x (two reals packed per
-//            complex, half-length transform) -> Sx[3][nz][Xp][ny] (transposed,
-//            so the y transform reads contiguous rows)
+//            complex, half-length transform) -> Sx[3][nz][XB][ny][4] (kx in
+//            blocks of 4)
 //   y pass   3-D: Sx -> Sy[3][nz][Xp][Py];  2-D: forward y, tensor product,
 //            inverse y fused, in place in Sx
 //   z pass   3-D: forward z (zero padded in registers or LDS), tensor product,
@@ -257,23 +257,14 @@ __global__ void __launch_bounds__(512) k_fwd_x(Launch<T> L) {
     const Cx<T> O = {D.y, -D.x};  // D / i
     return cadd(E, cmul(postl[k], O));
   };
-  if (g.nz > 1) {  // 3-D: Sx [3][nz][XB][ny][kSxB], kSxB TY contiguous entries per block
-    const int lq = lty + 2;  // kSxB = 4
-    Cx<T>* dst = hp.Sx + (size_t)b * g.sx + ((size_t)c * g.nz + z) * g.XB * kSxB * g.ny + kSxB * y0;
-    for (int t = threadIdx.x; t < (g.XB << lq); t += blockDim.x) {
-      const int kb = t >> lq, q = t & ((1 << lq) - 1);
-      const int r = q >> 2, k = kb * kSxB + (q & 3);
-      if (r < nrow && k < g.Xp)
-        gsto(dst, (uint32_t)(kb * kSxB * g.ny + q) * (uint32_t)sizeof(Cx<T>), post(r, k));
-    }
-  } else {  // 2-D: Sx transposed [3][Xp][ny] (the fused y pass reads columns)
-    Cx<T>* dst = hp.Sx + (size_t)b * g.sx + (size_t)c * g.Xp * g.ny + y0;
-    const int tot2 = g.Xp << lty;
-    for (int t = threadIdx.x; t < tot2; t += blockDim.x) {
-      const int k = t >> lty, r = t & (TY - 1);
-      if (r >= nrow) continue;
-      gsto(dst, (uint32_t)(k * g.ny + r) * (uint32_t)sizeof(Cx<T>), post(r, k));
-    }
+  // Sx [3][nz][XB][ny][kSxB], kSxB TY contiguous entries per block
+  const int lq = lty + 2;  // kSxB = 4
+  Cx<T>* dst = hp.Sx + (size_t)b * g.sx + ((size_t)c * g.nz + z) * g.XB * kSxB * g.ny + kSxB * y0;
+  for (int t = threadIdx.x; t < (g.XB << lq); t += blockDim.x) {
+    const int kb = t >> lq, q = t & ((1 << lq) - 1);
+    const int r = q >> 2, k = kb * kSxB + (q & 3);
+    if (r < nrow && k < g.Xp)
+      gsto(dst, (uint32_t)(kb * kSxB * g.ny + q) * (uint32_t)sizeof(Cx<T>), post(r, k));
   }
 }
 
@@ -364,7 +355,8 @@ struct ColStore {
 // A column of the 2-D y pass.  The kx = 0 and kx = Lx (Nyquist) columns of a
 // real field's x spectrum are real in y; the pass carries them as one complex
 // column (kx = 0 in the real part, kx = Lx in the imaginary part): coff2 is
-// the kx = Lx column for that packed column, ~0u for every other one.
+// the kx = Lx column for that packed column, ~0u for every other one.  Entries
+// kSxB apart (a column inside the kx blocks).
 template <typename T>
 struct ColLoad2 {
   const Cx<T>* base;
@@ -373,7 +365,7 @@ struct ColLoad2 {
   template <bool CHK>
   __device__ __forceinline__ Cx<T> get(int, int e) const {
     if (CHK && e >= n) return Cx<T>{T(0), T(0)};
-    const uint32_t eo = (uint32_t)e * (uint32_t)sizeof(Cx<T>);
+    const uint32_t eo = (uint32_t)e * (uint32_t)(kSxB * sizeof(Cx<T>));
     const Cx<T> v = gldo(base, coff + eo);
     if (coff2 == ~0u) return v;
     return Cx<T>{v.x, gldo(base, coff2 + eo).x};
@@ -387,7 +379,7 @@ struct ColStore2 {
   template <bool CHK>
   __device__ __forceinline__ void put(int, int e, Cx<T> v) const {
     if (CHK && e >= n) return;
-    const uint32_t eo = (uint32_t)e * (uint32_t)sizeof(Cx<T>);
+    const uint32_t eo = (uint32_t)e * (uint32_t)(kSxB * sizeof(Cx<T>));
     if (coff2 == ~0u) {
       gsto(base, coff + eo, v);
     } else {
@@ -443,14 +435,17 @@ __device__ __forceinline__ void y_fused2d(const HotPlan<T>& hp, const Epi<T>& ep
   const int ncol = 3 * ncb;                     // column c * ncb + j: component c of slot kx0 + j
   const int cs = col_stride(g.Py);
   const int sh = hp.fd[1].psh;
-  const int Xp = g.Xp, ny = g.ny;
+  const int ny = g.ny;
   const int tpc = MIX ? sr_tpc(SL) : SL > 0 ? SL / EPT : (int)blockDim.x / (3 * CB);
-  // this thread's column, in Sx = [3][1][Xp][ny] of the instance
+  // this thread's column, in Sx = [3][1][XB][ny][kSxB] of the instance
+  const auto col_off = [&](int comp, int kx) -> uint32_t {
+    return (uint32_t)((comp * g.XB + (kx >> 2)) * ny * kSxB + (kx & 3)) * (uint32_t)sizeof(Cx<T>);
+  };
   const int mc = (int)threadIdx.x / tpc;
   const int cc = mc < ncol ? mc : 0;
   const int c = cc / ncb, j = cc - c * ncb;
-  const uint32_t coff = (uint32_t)((c * Xp + kx0 + j) * ny) * (uint32_t)sizeof(Cx<T>);
-  const uint32_t coff2 = pk && kx0 + j == 0 ? (uint32_t)((c * Xp + L) * ny) * (uint32_t)sizeof(Cx<T>) : ~0u;
+  const uint32_t coff = col_off(c, kx0 + j);
+  const uint32_t coff2 = pk && kx0 + j == 0 ? col_off(c, L) : ~0u;
   Cx<T>* base = hp.Sx + (size_t)b * g.sx;
   // LDS after the columns: the twiddle table (Py) and the tensor rows of this
   // tile, kt[a][j][ky] for the components a = xx, yy, zz, xy and the ncb kx
@@ -1991,28 +1986,21 @@ __global__ void __launch_bounds__(512) k_inv_x(Launch<T> L) {
 
   // Spectrum tile: column c * TY + r holds component c of row y0 + r (rows past
   // the mesh are left out: only the epilogue's rows are read back).
-  // 3-D groups: Sx [3][nz][XB][ny][kSxB], the tile of a component is XB runs
-  // of kSxB TY entries; 2-D groups: Sx [3][Xp][ny], TY entries of each kx
-  // column.  Its first batch of loads is issued before anything else waits
+  // Sx [3][nz][XB][ny][kSxB]: the tile of a component is XB runs of kSxB TY
+  // entries.  Its first batch of loads is issued before anything else waits
   // (the controller flag, the epilogue's arguments and prefetch).
   const int ncol = 3 * TY;
-  const bool blk = g.nz > 1;
-  const size_t plane = blk ? (size_t)g.XB * kSxB * g.ny : (size_t)g.Xp * g.ny;
+  const size_t plane = (size_t)g.XB * kSxB * g.ny;
   const size_t cstride = (size_t)g.nz * plane;
-  const Cx<T>* src0 = hp.Sx + (size_t)b * g.sx + (size_t)z * plane + (blk ? kSxB * y0 : y0);
+  const Cx<T>* src0 = hp.Sx + (size_t)b * g.sx + (size_t)z * plane + kSxB * y0;
   const int lq = lty + 2;  // kSxB = 4
-  const int tot = DEMAG ? (blk ? g.XB << lq : g.Xp << lty) : 0;
+  const int tot = DEMAG ? g.XB << lq : 0;
   // entry t of a component's tile: row r, kx k; returns its offset from src0
   auto tile_ent = [&](int t, int& r, int& k) -> uint32_t {
-    if (blk) {
-      const int kb = t >> lq, q = t & ((1 << lq) - 1);
-      r = q >> 2;
-      k = kb * kSxB + (q & 3);
-      return (uint32_t)(kb * kSxB * g.ny + q);
-    }
-    r = t & (TY - 1);
-    k = t >> lty;
-    return (uint32_t)(k * g.ny + r);
+    const int kb = t >> lq, q = t & ((1 << lq) - 1);
+    r = q >> 2;
+    k = kb * kSxB + (q & 3);
+    return (uint32_t)(kb * kSxB * g.ny + q);
   };
   constexpr int U = 4;
   auto load_batch = [&](int t0, Cx<T> (&v)[U][3]) {
@@ -2287,26 +2275,16 @@ __global__ void __launch_bounds__(512) k_inv_x(Launch<T> L) {
     x_columns<T, false, LEN>(lds, hp.fd[0], cs, ncol, twl, hin);
     // real-to-complex post-processing and transposed store (the rows this
     // workgroup read at the start)
-    // layouts as for the load at the start
-    const bool blk = g.nz > 1;
-    const size_t plane = blk ? (size_t)g.XB * kSxB * g.ny : (size_t)g.Xp * g.ny;
+    // layout as for the load at the start
+    const size_t plane = (size_t)g.XB * kSxB * g.ny;
     const size_t cstride = (size_t)g.nz * plane;
-    Cx<T>* dst0 = hp.Sx + (size_t)b * g.sx + (size_t)z * plane + (blk ? kSxB * y0 : y0);
+    Cx<T>* dst0 = hp.Sx + (size_t)b * g.sx + (size_t)z * plane + kSxB * y0;
     const int lq = lty + 2;
-    const int tot = blk ? g.XB << lq : g.Xp << lty;
+    const int tot = g.XB << lq;
     for (int t = threadIdx.x; t < tot; t += blockDim.x) {
-      int r, k;
-      uint32_t o;
-      if (blk) {
-        const int kb = t >> lq, q = t & ((1 << lq) - 1);
-        r = q >> 2;
-        k = kb * kSxB + (q & 3);
-        o = (uint32_t)(kb * kSxB * g.ny + q);
-      } else {
-        r = t & (TY - 1);
-        k = t >> lty;
-        o = (uint32_t)(k * g.ny + r);
-      }
+      const int kblk = t >> lq, q = t & ((1 << lq) - 1);
+      const int r = q >> 2, k = kblk * kSxB + (q & 3);
+      const uint32_t o = (uint32_t)(kblk * kSxB * g.ny + q);
       if (r >= nrow || k >= g.Xp) continue;
       const uint32_t off = o * (uint32_t)sizeof(Cx<T>);
       const Cx<T> pk = postl[k];

@@ -477,9 +477,10 @@ mm_status choose_tuning(Group& G, mm_precision prec, size_t csz, long long launc
     while (ty > g.ny) ty /= 2;  // a power of two (the kernels split rows by shifts)
     if ((size_t)3 * ty * rowb + xtab > 160 * 1024 || 3 * ty * tpx > 512)
       return fail(MM_E_ARG, "mesh too long along x");
-    // compiled lengths keep one plan whatever the launch: at most four cells a
-    // thread and a column's threads in the workgroup
-    const bool list = sr_compiled(g.Lx);
+    // compiled lengths with threes keep one plan whatever the launch: at most four
+    // cells a thread and a column's threads in the workgroup (powers of two have
+    // the general kernel's plan)
+    const bool list = sr_compiled(g.Lx) && (g.Lx & (g.Lx - 1)) != 0;
     while (list && ty > 1 && (3 * ty * sr_tpc(g.Lx) > 512 || ty * g.nx > 2048)) ty /= 2;
     t.ty_x = ty;
     // Threads.  One cell a thread is the shortest chain but takes 145-166
@@ -497,7 +498,7 @@ mm_status choose_tuning(Group& G, mm_precision prec, size_t csz, long long launc
     else if (wgs <= 512) nt = pow2ceil((int)std::min<long long>(std::max<long long>(3LL * ty * g.Lx / 8, cells / 2), 512));
     else if (2 * ((size_t)3 * ty * rowb + xtab) > 160 * 1024) nt = 512;
     else nt = cells <= 1024 ? pow2ceil((int)std::min<long long>(std::max<long long>(cells / 2, 64), 256)) : 512;
-    const int columns = list && (g.Lx & (g.Lx - 1)) != 0 ? 3 * ty * sr_tpc(g.Lx) : 3 * ty * tpx;
+    const int columns = list ? 3 * ty * sr_tpc(g.Lx) : 3 * ty * tpx;
     t.nt_i = std::min(512, std::max(64, pow2ceil(std::max(columns, nt))));
     t.tpc_x = t.nt_i / (3 * ty);
   }
@@ -755,7 +756,7 @@ mm_status build_padded(Engine& E, Group& G, int Px, int Py, int Pz, hipStream_t 
   g.Kz = g.Pz / 2 + 1;
   g.N = (long long)g.nx * g.ny * g.nz;
   g.XB = (g.Xp + kSxB - 1) / kSxB;
-  g.sx = g.nz == 1 ? 3LL * g.Xp * g.ny : 3LL * g.nz * g.XB * kSxB * g.ny;
+  g.sx = 3LL * g.nz * g.XB * kSxB * g.ny;
   g.sy = 3LL * g.nz * g.Xp * g.Py;
   g.dV = G.mesh.dx * G.mesh.dy * G.mesh.dz;
   MMCHK(choose_tuning(G, E.prec, E.csz));
