@@ -364,11 +364,16 @@ void z_pair_launch(const Launch<T>& L, long long total, hipStream_t s) {
   k_z3d_pair<T, M><<<dim3((unsigned)total), kNT, 0, s>>>(L);
 }
 
-// Lane-pair register z pass: even Pz with Pz / 2 in {1,2,3,4,6,8,9,12,16}.
+// Lane-pair register z pass: even Pz with Pz / 2 in {1,2,3,4,6,8,9,12,16}, in FP32
+// also 18 and 24 (z pass of 100x100x20 21 us against 41 through LDS, 300x300x19 117
+// against 209; in FP64 24 spills its columns, 107 against 60).
+template <typename T>
 bool z_pair_supported(int Pz) {
   switch (Pz) {
     case 2: case 4: case 6: case 8: case 12: case 16: case 18: case 24: case 32:
       return true;
+    case 36: case 48:
+      return sizeof(T) == 4;
     default:
       return false;
   }
@@ -386,6 +391,12 @@ void z_pair_dispatch(int Pz, const Launch<T>& L, long long total, hipStream_t s)
     case 18: z_pair_launch<T, 9>(L, total, s); break;
     case 24: z_pair_launch<T, 12>(L, total, s); break;
     case 32: z_pair_launch<T, 16>(L, total, s); break;
+    case 36:
+      if constexpr (sizeof(T) == 4) z_pair_launch<T, 18>(L, total, s);
+      break;
+    case 48:
+      if constexpr (sizeof(T) == 4) z_pair_launch<T, 24>(L, total, s);
+      break;
     default: break;
   }
 }
@@ -434,7 +445,7 @@ int z_kind(const Geo& g) {
   const bool fits = (double)g.sy * sizeof(Cx<T>) < 4294967296.0;
   if (half && fits && (Pz == 16 || Pz == 32 || Pz == 64) && (sizeof(T) == 8 || Pz == 64)) return 3;
   if (z_reg_supported<T>(Pz)) return 1;
-  if (z_pair_supported(Pz)) return 0;
+  if (z_pair_supported<T>(Pz)) return 0;
   return 2;
 }
 

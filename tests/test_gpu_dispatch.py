@@ -196,3 +196,17 @@ def test_compiled_rows_in_stages_fp64(mm, n):
         st = mm.new_states(2, h=1e-14, h_max=1e-14)
         plan.rk45_run([gp, gp], md, st, t_end=3e-14)
         assert np.max(np.abs(md.cpu().numpy() - np.stack(mo))) <= 1e-9
+
+
+@pytest.mark.parametrize("nz", [17, 18, 19, 24])
+def test_lane_pair_z_of_36_and_48_points(mm, nz):
+    """The FP32 lane-pair z transforms of 36 and 48 points (full and short
+    columns) and FP64's pass through LDS at the same lengths."""
+    for prec, tol in (("f32", 1e-5), ("f64", 1e-11)):
+        mesh = (10, 9, nz, 3e-9, 2e-9, 2.5e-9)
+        plan = mm.Plan(mesh, prec, terms=F.ALL_TERMS)
+        assert plan.padded()[2] == (36 if nz < 19 else 48)
+        gp, op = gpu_params(mm, PAR, F.ALL_TERMS), oracle_params(PAR, F.ALL_TERMS)
+        m = representable(_m(mesh, 80 + nz), plan.dtype)
+        H = plan.effective_field(gp, to_dev(m, plan.dtype)).double().cpu().numpy()
+        assert field_err(H, F.effective_field(m, F.Mesh(*mesh), op, F.DemagKernel(F.Mesh(*mesh)))) <= tol
