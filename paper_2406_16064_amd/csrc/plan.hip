@@ -482,6 +482,9 @@ mm_status choose_tuning(Group& G, mm_precision prec, size_t csz, long long launc
     // the general kernel's plan)
     const bool list = sr_compiled(g.Lx) && (g.Lx & (g.Lx - 1)) != 0;
     while (list && ty > 1 && (3 * ty * sr_tpc(g.Lx) > 512 || ty * g.nx > 2048)) ty /= 2;
+    // in a batch the rows of up to 256 points too, so that one launch of the
+    // compiled kernels takes every mesh
+    while (launch_rows > 0 && sr_compiled(g.Lx) && g.Lx <= 256 && ty > 1 && 3 * ty * sr_tpc(g.Lx) > 512) ty /= 2;
     t.ty_x = ty;
     // Threads.  One cell a thread is the shortest chain but takes 145-166
     // registers (three waves a SIMD, and one workgroup of 512 threads a CU):
@@ -513,7 +516,12 @@ mm_status choose_tuning(Group& G, mm_precision prec, size_t csz, long long launc
     // packed: the tile of slot 0 also holds the tensor rows of kx = Lx
     const int pk = y2d_packed(g);
     while (sr_compiled(g.Py) && cb > 1 && 3 * cb * sr_tpc(g.Py) > 512) cb /= 2;
-    while (cb > 1 && (cb * colb + (cb + pk) * ktab2 + ytab > budget || 3 * cb * tpc > 512 || g.Xp / cb < want)) cb /= 2;
+    // batch launches: columns for 256 threads (32 films of 128x128: 19.2 with two
+    // columns a workgroup, 21.7 with one, 20.7 with four)
+    const int tl = sr_compiled(g.Py) ? sr_tpc(g.Py) : tpc;
+    while (cb > 1 && (cb * colb + (cb + pk) * ktab2 + ytab > budget || 3 * cb * tpc > 512 ||
+                      (launch_rows > 0 ? 3 * cb * tl > 256 : g.Xp / cb < want)))
+      cb /= 2;
     if (cb * colb + (cb + pk) * ktab2 + ytab > 160 * 1024 || 3 * cb * tpc > 512)
       return fail(MM_E_ARG, "mesh too long along y");
     t.cb_y2 = cb;
