@@ -174,11 +174,14 @@ hipError_t launch_controller(DevCtl* ctl, int n, const double* replay_h, hipStre
 // and the update of m.  Arrays [batch][3][N].  With ctl (a relaxation; prm
 // gives the LL coefficients): first the stopping rule on the largest |dm/dt|
 // of m (ctl[b].stop_dmdt, rad/s), done instances skipped from then on; `last`
-// only checks (no update) and marks every instance done.
+// only checks (no update) and marks every instance done.  fold (no ctl): the
+// update's blocks take the step from the block sums themselves (up to 256 blocks
+// an instance: each reads them all); tau then holds 2 batch values, that of
+// iteration k at (k & 1) batch + b.
 template <typename T>
 hipError_t launch_sd_iteration(T* m, const T* H, T* g, T* mp, T* gp, double* part, double* tau, int batch,
                                long long N, long long k, double tau_min, double tau_max, const DevParams* prm,
-                               DevCtl* ctl, bool last, hipStream_t s);
+                               DevCtl* ctl, bool last, bool fold, hipStream_t s);
 
 hipError_t launch_energy_reduce(const double* partial, int batch, int blocks_per_inst, double* out,
                                 hipStream_t s);

@@ -3,7 +3,7 @@ launch shape, at the sizes on both sides of its line, against the oracle."""
 import numpy as np
 import pytest
 
-from oracle import dp45
+from oracle import dp45, sd
 from oracle import fields as F
 from paper_2406_16064_amd import inputs
 
@@ -210,3 +210,25 @@ def test_lane_pair_z_of_36_and_48_points(mm, nz):
         m = representable(_m(mesh, 80 + nz), plan.dtype)
         H = plan.effective_field(gp, to_dev(m, plan.dtype)).double().cpu().numpy()
         assert field_err(H, F.effective_field(m, F.Mesh(*mesh), op, F.DemagKernel(F.Mesh(*mesh)))) <= tol
+
+
+@pytest.mark.parametrize("n", [1, 2, 5])
+@pytest.mark.parametrize("nx", [8, 256, 257])
+def test_sd_step_inside_the_update_fp64(mm, nx, n):
+    """Steepest descent of two instances whose update takes the step itself (one
+    and 256 workgroups an instance) and of 257 workgroups, where a kernel of its
+    own does: the state and the last step, after odd and even iterations."""
+    mesh = (nx, 256, 1, 2e-9, 2e-9, 2e-9) if nx > 8 else (nx, 8, 1, 2e-9, 2e-9, 2e-9)
+    plan = mm.Plan(mesh, "f64", terms=F.ALL_TERMS, max_batch=2)
+    ps = [dict(PAR, alpha=0.5), dict(PAR, Ms=8e5, Ku=2e5, alpha=0.5)]
+    rng = np.random.default_rng(90)
+    m0 = np.array([0.0, 0.0, 1.0]).reshape(3, 1, 1, 1) + 0.3 * rng.normal(size=(2, 3, *mesh[2::-1]))
+    m0 /= np.linalg.norm(m0, axis=1, keepdims=True)
+    md = to_dev(m0, torch.float64)
+    tau = plan.sd_run([gpu_params(mm, p, F.ALL_TERMS) for p in ps], md, n, 1e-7, 1e-10, 1e-3)
+    kern = F.DemagKernel(F.Mesh(*mesh))
+    for b, p in enumerate(ps):
+        op = oracle_params(p, F.ALL_TERMS)
+        mo, taus = sd.run(lambda y: F.effective_field(y, F.Mesh(*mesh), op, kern), m0[b].copy(), n, 1e-7, 1e-10, 1e-3)
+        assert np.max(np.linalg.norm(md[b].cpu().numpy() - mo, axis=0)) <= 1e-9
+        assert abs(tau[b] - taus[-1]) <= 1e-9 * taus[-1]
