@@ -427,8 +427,9 @@ DevParams dev_params(const mm_params& r, const Group& G, bool general) {
 // launch_rows: rows (nz ny per instance) of every group of a batch launch, 0
 // for one instance of this group alone: the workgroup count aimed at counts
 // the whole launch, so that the meshes of a large batch take rows per
-// workgroup up to the LDS and thread limits.
-mm_status choose_tuning(Group& G, mm_precision prec, size_t csz, long long launch_rows = 0) {
+// workgroup up to the LDS and thread limits.  pot: the scalar-potential route,
+// whose inverse x has its own kernel.
+mm_status choose_tuning(Group& G, mm_precision prec, size_t csz, bool pot, long long launch_rows = 0) {
   const Geo& g = G.g;
   Tuning& t = G.tu;
   const size_t budget = 80 * 1024;
@@ -480,11 +481,16 @@ mm_status choose_tuning(Group& G, mm_precision prec, size_t csz, long long launc
     // compiled lengths with threes keep one plan whatever the launch: at most four
     // cells a thread and a column's threads in the workgroup (powers of two have
     // the general kernel's plan)
-    const bool list = sr_compiled(g.Lx) && (g.Lx & (g.Lx - 1)) != 0;
+    const bool list = !pot && sr_compiled(g.Lx) && (g.Lx & (g.Lx - 1)) != 0;
     while (list && ty > 1 && (3 * ty * sr_tpc(g.Lx) > 512 || ty * g.nx > 2048)) ty /= 2;
     // in a batch the rows of up to 256 points too, so that one launch of the
     // compiled kernels takes every mesh
-    while (launch_rows > 0 && sr_compiled(g.Lx) && g.Lx <= 256 && ty > 1 && 3 * ty * sr_tpc(g.Lx) > 512) ty /= 2;
+    while (!pot && launch_rows > 0 && sr_compiled(g.Lx) && g.Lx <= 256 && ty > 1 && 3 * ty * sr_tpc(g.Lx) > 512)
+      ty /= 2;
+    // potential route: long compiled rows run best in twos, three workgroups a CU
+    // (512x512x16 74.8 -> 67.2, FP64 161 -> 137; one row: 84); the general
+    // transform's keep the LDS limit (400x300x16 52 with four, 64 with two)
+    while (pot && g.Lx >= 512 && (g.Lx & (g.Lx - 1)) == 0 && ty > 2) ty /= 2;
     t.ty_x = ty;
     // Threads.  One cell a thread is the shortest chain but takes 145-166
     // registers (three waves a SIMD, and one workgroup of 512 threads a CU):
@@ -767,7 +773,7 @@ mm_status build_padded(Engine& E, Group& G, int Px, int Py, int Pz, hipStream_t 
   g.sx = 3LL * g.nz * g.XB * kSxB * g.ny;
   g.sy = 3LL * g.nz * g.Xp * g.Py;
   g.dV = G.mesh.dx * G.mesh.dy * G.mesh.dz;
-  MMCHK(choose_tuning(G, E.prec, E.csz));
+  MMCHK(choose_tuning(G, E.prec, E.csz, pot));
   if (E.terms & MM_DEMAG) {
     MMCHK(dev_alloc(&G.kt, E.rsz * G.ncomp * (size_t)g.Kz * g.Xp * g.Ky));
     MMCHK(E.prec == MM_F32 ? upload_tables<float>(G) : upload_tables<double>(G));
@@ -1773,7 +1779,7 @@ mm_status batch_run(mm_batch* bt, mm_instance* inst, int n, long long max_steps,
   for (int g = 0; g < ng; ++g) {
     Group& G = E.groups[g];
     if (nb[g] == 0 || launch_rows == G.tuned_for) continue;
-    MMCHK(choose_tuning(G, E.prec, E.csz, launch_rows));
+    MMCHK(choose_tuning(G, E.prec, E.csz, (E.terms & MM_DEMAG_POTENTIAL) != 0, launch_rows));
     G.tuned_for = launch_rows;
     if (E.gexec) { (void)hipGraphExecDestroy(E.gexec); E.gexec = nullptr; }
     E.k1_ok = false;
@@ -1833,7 +1839,7 @@ mm_status neb_impl(mm_plan* p, const mm_params* q, void* images, int n_img, doub
     Group& Gm = E.groups[0];
     const long long rows = (long long)Gm.g.nz * Gm.g.ny * n_img;
     if (!Gm.user_shapes && rows != Gm.tuned_for) {
-      MMCHK(choose_tuning(Gm, E.prec, E.csz, rows));
+      MMCHK(choose_tuning(Gm, E.prec, E.csz, (E.terms & MM_DEMAG_POTENTIAL) != 0, rows));
       Gm.tuned_for = rows;
       MMCHK(engine_reserve(E, std::vector<int>{p->maxb}));
       if (E.gexec) { (void)hipGraphExecDestroy(E.gexec); E.gexec = nullptr; }

@@ -230,8 +230,13 @@ __global__ void __launch_bounds__(512) k_pot_yinv_s(HotPlan<T> hp, int CB) {
 // vertex rows of vertex planes z and z + 1 are loaded (kSxB (TY + 1)
 // contiguous entries per kx block), transformed together, and each cell reads
 // its eight corners from LDS.
+// P2: only the compiled transforms of 128 to 1024 points (Lx / 16 threads a
+// column), without the run-time one, whose registers the other loops would pay
+// for: 60 to 93 in FP32 instead of 114, three workgroups of 512 threads a CU
+// (512x512x16 dm/dt, two rows: 76 -> 67 us, 2.2 TB/s of its 150 MB; LDS traffic
+// and the divisions of the tile's indices bound it).
 // ---------------------------------------------------------------------------
-template <typename T, int MODE, int CPT>
+template <typename T, int MODE, int CPT, bool P2>
 __global__ void __launch_bounds__(512) k_pot_x(HotPlan<T> hp, const Epi<T>* __restrict__ epis, int tpc, T gx, T gy,
                                               T gz) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -313,11 +318,8 @@ __global__ void __launch_bounds__(512) k_pot_x(HotPlan<T> hp, const Epi<T>* __re
       }
     }
     __syncthreads();
-    // the full inverse transform (vertex nx needs the entry Lx / 2); compiled
-    // for the power-of-two lengths when the workgroup has Lx / 16 threads a column
-    const bool st16 = (g.Lx == 128 || g.Lx == 256 || g.Lx == 512 || g.Lx == 1024) &&
-                      ncol * (g.Lx / 16) <= (int)blockDim.x;
-    if (st16) {
+    // the full inverse transform (vertex nx needs the entry Lx / 2)
+    if constexpr (P2) {
       switch (g.Lx) {
         case 128: fft_static<T, 128, false, true, false, false, true, false, false, 16>(lds, twl, cs, ncol, NoLoad<T>{}, NoStore<T>{}, NoHook{}); break;
         case 256: fft_static<T, 256, false, true, false, false, true, false, false, 16>(lds, twl, cs, ncol, NoLoad<T>{}, NoStore<T>{}, NoHook{}); break;
@@ -553,15 +555,22 @@ hipError_t launch_potential(const GroupSet<T>& gs, const Epi<T>* epis, const Pot
     const T cx = T(pt.gdx), cy = T(pt.gdy), cz = T(pt.gdz);
     const int cpt = p.cpt_x;
     const dim3 grid((unsigned)blocks);
-    auto go = [&](auto mode_c) {
+    auto go_p2 = [&](auto mode_c, auto p2_c) {
       constexpr int MD = decltype(mode_c)::value;
+      constexpr bool P2 = decltype(p2_c)::value;
       switch (cpt) {
-        case 1: k_pot_x<T, MD, 1><<<grid, p.nt_x, p.lds_x, s>>>(h, epis, p.tpc_x, cx, cy, cz); break;
-        case 2: k_pot_x<T, MD, 2><<<grid, p.nt_x, p.lds_x, s>>>(h, epis, p.tpc_x, cx, cy, cz); break;
-        case 4: k_pot_x<T, MD, 4><<<grid, p.nt_x, p.lds_x, s>>>(h, epis, p.tpc_x, cx, cy, cz); break;
-        case 8: k_pot_x<T, MD, 8><<<grid, p.nt_x, p.lds_x, s>>>(h, epis, p.tpc_x, cx, cy, cz); break;
-        default: k_pot_x<T, MD, 0><<<grid, p.nt_x, p.lds_x, s>>>(h, epis, p.tpc_x, cx, cy, cz); break;
+        case 1: k_pot_x<T, MD, 1, P2><<<grid, p.nt_x, p.lds_x, s>>>(h, epis, p.tpc_x, cx, cy, cz); break;
+        case 2: k_pot_x<T, MD, 2, P2><<<grid, p.nt_x, p.lds_x, s>>>(h, epis, p.tpc_x, cx, cy, cz); break;
+        case 4: k_pot_x<T, MD, 4, P2><<<grid, p.nt_x, p.lds_x, s>>>(h, epis, p.tpc_x, cx, cy, cz); break;
+        case 8: k_pot_x<T, MD, 8, P2><<<grid, p.nt_x, p.lds_x, s>>>(h, epis, p.tpc_x, cx, cy, cz); break;
+        default: k_pot_x<T, MD, 0, P2><<<grid, p.nt_x, p.lds_x, s>>>(h, epis, p.tpc_x, cx, cy, cz); break;
       }
+    };
+    const bool p2 = (g.Lx == 128 || g.Lx == 256 || g.Lx == 512 || g.Lx == 1024) &&
+                    2 * (h.tu.ty_x + 1) * (g.Lx / 16) <= p.nt_x;
+    auto go = [&](auto mode_c) {
+      if (p2) go_p2(mode_c, std::true_type{});
+      else go_p2(mode_c, std::false_type{});
     };
     switch (mode) {
       case MODE_FIELD: go(std::integral_constant<int, MODE_FIELD>{}); break;
