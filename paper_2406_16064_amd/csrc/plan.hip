@@ -449,7 +449,8 @@ mm_status choose_tuning(Group& G, mm_precision prec, size_t csz, bool pot, long 
      // block takes whole lines; 1 row only where 4 would leave CUs idle
      // (512x512x1 16.6 -> 12.2, 1024x1024x1 22.3 -> 19.3, 256x256x1 9.2 -> 8.9).
      // Long rows in many workgroups run best on 256 threads (512x512x16: 38.7
-     // against 42.5 with 8 rows on 512, 40.8 with 4 on 512).
+     // against 42.5 with 8 rows on 512, 40.8 with 4 on 512), the longest on 512
+    // (1024x512x8 47.8 -> 38.4, FP64 96 -> 84).
     const long long rows = 3 * all_rows;
     int ty = launch_rows > 0 ? 16 : 4;
     while (ty > 1 && ((size_t)ty * rowb + xtab > budget || ty * tpx > 512 || rows / ty < (ty > 4 ? want : 192))) ty /= 2;
@@ -461,7 +462,7 @@ mm_status choose_tuning(Group& G, mm_precision prec, size_t csz, bool pot, long 
     // one kernel for a compiled length, whatever the rows (sr_compiled)
     while (sr_compiled(g.Lx) && ty > 1 && ty * sr_tpc(g.Lx) > 512) ty /= 2;
     t.ty_f = ty;
-    const int cap = ty <= 4 && rows / ty > want ? 256 : 512;
+    const int cap = ty <= 4 && rows / ty > want && g.Lx < 1000 ? 256 : 512;
     t.nt_f = std::min(512, std::max(64, pow2ceil(std::max(ty * tpx, std::min(cap, ty * g.Lx / 4)))));
     t.tpc_f = t.nt_f / ty;
   }
