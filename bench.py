@@ -571,11 +571,11 @@ def load_traffic(workload, kernel, launch=None):
 
 
 # kernel-name fragments of each pass in rocprofv3 output
-# (the y passes: kernels compiled for one length, k_*_s, or the general ones)
-PASS_KERNELS = {"x_fwd": ("k_fwd_x<",), "y_fused_product": ("k_ypass_s<", "k_ypass<"),
-                "y_fwd": ("k_ypass_s<", "k_ypass<"),
+# (the y passes: kernels compiled for one length, k_*_s and k_*_m, or the general ones)
+PASS_KERNELS = {"x_fwd": ("k_fwd_x<",), "y_fused_product": ("k_ypass_s<", "k_ypass_m<", "k_ypass<"),
+                "y_fwd": ("k_ypass_s<", "k_ypass_m<", "k_ypass<"),
                 "z_product": ("k_z3d_reg_half<", "k_z3d_reg<", "k_z3d_s<", "k_z3d_pair<", "k_z3d<"),
-                "y_inv": ("k_yinv_s<", "k_yinv<"), "x_inv_fused_llg": ("k_inv_x<",)}
+                "y_inv": ("k_yinv_s<", "k_yinv_m<", "k_yinv<"), "x_inv_fused_llg": ("k_inv_x<",)}
 COPY_BYTES = 1 << 30
 
 
@@ -643,10 +643,16 @@ def ingest_counters(fetch_csv, write_csv, copy_fetch_csv, copy_write_csv, worklo
         wb = sum(w) / len(w) * 1024.0 * kw
         return {"fetch_bytes": fb, "write_bytes": wb, "bytes_per_launch": fb + wb}
 
+    def inv_x_args(k):  # k_inv_x<T, demag, mode, cells per thread, fused, cell material, compiled row>
+        if "k_inv_x<" not in k:
+            return [None] * 6
+        a = [x.strip() for x in k.split("k_inv_x<", 1)[1].split(">", 1)[0].split(",")]
+        return a
+
     for name in pass_names(mesh_nz):
         frags = PASS_KERNELS[name]
         if name == "x_inv_fused_llg":  # the dm/dt (MODE_RHS = 1) instance with the demag transform
-            keys = [k for k in fr if frags[0] in k and ", true, 1," in k and k.split("(")[0].endswith("false>")]
+            keys = [k for k in fr if inv_x_args(k)[1:3] == ["true", "1"] and inv_x_args(k)[5] == "false"]
         else:
             keys = [k for f in frags for k in fr if f in k]
         # read in both runs; the instantiation the timed run used is the one
@@ -662,12 +668,6 @@ def ingest_counters(fetch_csv, write_csv, copy_fetch_csv, copy_write_csv, worklo
     # 2..6 in equal numbers in the graph replays and in the step timing)
     frf = _counter_rows(fetch_csv, True)
     wrf = _counter_rows(write_csv, True)
-    def inv_x_args(k):  # k_inv_x<T, demag, mode, cells per thread, fused, cell material>
-        if "k_inv_x<" not in k:
-            return [None] * 6
-        a = [x.strip() for x in k.split("k_inv_x<", 1)[1].split(">", 1)[0].split(",")]
-        return a + ["false"] * (6 - len(a))  # builds without the cell-material argument
-
     def is_stage(k, fused):
         a = inv_x_args(k)
         return a[1:3] == ["true", "2"] and a[4] == ("true" if fused else "false") and a[5] == "false"

@@ -260,9 +260,9 @@ mm_status mm_sd_run(mm_plan* plan, const mm_params* params, int32_t batch, void*
 
 /* mm_sd_run for callers that cannot allocate device memory (code under HIP
  * graph capture, tight serving loops, harnesses that forbid allocation): the
- * same iteration, kernels and results, but the per-call scratch that mm_sd_run
- * allocates and frees (FP64 partial sums, 4 per 256 cells per instance, and
- * the step sizes) comes from a fixed 16 MiB array in device memory that every
+ * same iteration and results, but the scratch that mm_sd_run keeps in the plan
+ * and grows for larger batches (FP64 partial sums, 4 per 256 cells per instance,
+ * and the step sizes) comes from a fixed 16 MiB array in device memory that every
  * GPU the library runs on holds until the process ends.  This call allocates
  * nothing: MM_E_ARG when the batch needs more scratch than that
  * (32 * ceil(nx ny nz / 256) * batch bytes, rounded up to 256, plus 8 * batch;

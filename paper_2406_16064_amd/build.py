@@ -17,8 +17,8 @@ SOURCES = ("hotpath.hip", "invx_f32_demag.hip", "invx_f32_local.hip", "invx_f64_
            "lengths_f32.hip", "lengths_f64.hip", "invx_f32_any_cells.hip", "invx_f64_any_cells.hip",
            "invx_f32_any1.hip", "invx_f32_any2.hip", "invx_f32_any4.hip", "invx_f64_any1.hip", "invx_f64_any2.hip",
            "invx_f64_any4.hip",
-           "len_f32.hip", "invx_f32_len1.hip", "invx_f32_len2.hip",
-           "len_f64.hip", "invx_f64_len1.hip", "invx_f64_len2.hip", "potential.hip", "setup.hip", "plan.hip")
+           "len_f32.hip", "long_f32.hip", "invx_f32_len1.hip", "invx_f32_len2.hip",
+           "len_f64.hip", "long_f64.hip", "invx_f64_len1.hip", "invx_f64_len2.hip", "potential.hip", "setup.hip", "plan.hip")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 

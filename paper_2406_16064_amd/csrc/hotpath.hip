@@ -43,9 +43,11 @@ extern template void inv_x_launch_any<double, false, 4>(int, bool, const Launch<
 extern template void inv_x_launch_any<double, true, 1>(int, bool, const Launch<double>&, long long, int, size_t, hipStream_t);
 extern template void inv_x_launch_any<double, true, 2>(int, bool, const Launch<double>&, long long, int, size_t, hipStream_t);
 extern template void len_launch<float>(int, int, const Launch<float>&, long long, int, size_t, hipStream_t);
+extern template void long_launch<float>(bool, int, const Launch<float>&, long long, int, size_t, hipStream_t);
 extern template void inv_x_launch_len<float, 1>(int, int, const Launch<float>&, long long, int, size_t, hipStream_t);
 extern template void inv_x_launch_len<float, 2>(int, int, const Launch<float>&, long long, int, size_t, hipStream_t);
 extern template void len_launch<double>(int, int, const Launch<double>&, long long, int, size_t, hipStream_t);
+extern template void long_launch<double>(bool, int, const Launch<double>&, long long, int, size_t, hipStream_t);
 extern template void inv_x_launch_len<double, 1>(int, int, const Launch<double>&, long long, int, size_t, hipStream_t);
 extern template void inv_x_launch_len<double, 2>(int, int, const Launch<double>&, long long, int, size_t, hipStream_t);
 extern template void yzy_launch<float>(int, int, const Launch<float>&, long long, int, size_t, hipStream_t);
@@ -560,14 +562,15 @@ int static_y(const GroupSet<T>& gs, bool inv, int& nt, int& ept, const bool* use
 }
 
 // Pz / 2 where a 3-D group takes the fused y and z passes (k_yzy), 0 where it
-// takes the separate ones.  Fused: nz = 2 to 4 (FP64 to 3), Py = 2 ny of 256, 512
-// or 1024, and the columns of a kx in 64 KB of LDS, so that two workgroups and
+// takes the separate ones.  Fused: nz = 2 to 4 (FP64 to 3), a Py with a compiled
+// transform, and the columns of a kx in 64 KB of LDS, so that two workgroups and
 // more share a CU.  The fused workgroup is one serial chain, so that larger
 // planes, which leave one a CU, and the general transform lose (FP32, y + z +
 // inverse y in us, separate -> fused: 256x256x2 13.9 -> 9.9, eight of them
-// 48.7 -> 35.3, eight 128x128x2 14.7 -> 10.1, eight 256x256x4 90 -> 79, 256x256x2
-// FP64 22.5 -> 16.5; but 512x512x4 57 -> 73, eight 128x128x8 49 -> 70, eight
-// 128x128x4 FP64 49 -> 55, eight 192x192x2 57 -> 107).
+// 48.7 -> 35.3, eight 128x128x2 14.7 -> 10.1, eight 256x256x4 90 -> 79, eight
+// 192x192x2 57 -> 25, 256x256x2 FP64 22.5 -> 16.5; but 512x512x4 57 -> 73, eight
+// 128x128x8 49 -> 70, eight 128x128x4 FP64 49 -> 55, and eight 192x192x2 with the
+// general transform 57 -> 107).
 template <typename T>
 int yzy_m(const Geo& g) {
   if (g.nz < 2 || g.nz > (sizeof(T) == 8 ? 3 : 4) || g.Pz != 2 * g.nz) return 0;
@@ -578,7 +581,7 @@ template <typename T>
 int yzy_m(const HotPlan<T>& h) { return h.kt ? yzy_m<T>(h.g) : 0; }  // no tensor: the scalar-potential route
 
 // The y passes launch once per length of the kernels compiled for one (Py = 2 ny
-// of 256 to 2048), once for all the other compiled lengths (kMixKey; in a launch
+// of 256 to 2048, sr_long), once for all the other compiled lengths (kMixKey; in a launch
 // of several meshes, `several`, those of the list among the former too), and
 // once for the rest (the general transform): key of a group, 0 for the general
 // kernels.
@@ -591,6 +594,7 @@ int y_key(const HotPlan<T>& h, bool several) {
   const bool mix = sr_compiled(L) && (yzy_m<T>(h) > 0 || (cols * sr_tpc(L) <= 512 &&
                                                          (h.g.nz == 1 || h.tu.cb_y <= kSxB)));
   if (L == 2 * h.g.ny && (L == 256 || L == 512 || L == 1024 || L == 2048) && !(several && mix)) return L;
+  if (sr_long(L) && cols * sr_tpc(L) <= 512 && (h.g.nz == 1 || h.tu.cb_y <= kSxB)) return L;
   return mix ? kMixKey : 0;
 }
 template <typename T>
@@ -708,12 +712,16 @@ hipError_t launch_eval(const GroupSet<T>& gs, const Epi<T>* epis, int mode, bool
           lds = std::max(lds, (size_t)h.tu.cb_y * col_stride(h.g.Py) * csz);
         }
         if (!use[i]) continue;
-        const bool mix = keys[kk] / 32 == kMixKey;
+        const bool mix = keys[kk] / 32 == kMixKey || sr_long(keys[kk] / 32);
         if (m > 0 && h.g.nz > 1) nt = std::max(nt, std::min(512, (3 * h.g.nz * sr_tpc(h.g.Py) + 63) / 64 * 64));
         else if (m > 0 && !mix) nt = std::max(nt, 3 * h.tu.cb_y2 * (h.g.Py / 8));
         else nt = std::max(nt, mix ? mix_threads(h) : h.tu.nt_y);
       }
       if (lb.total == 0) continue;
+      if (sr_long(keys[kk] / 32)) {
+        long_launch<T>(false, keys[kk] / 32, lb.L, lb.total, nt, lds, s);
+        continue;
+      }
       if (keys[kk] / 32 == kMixKey) {
         if (gs.n == 1 && m == 0) len_launch<T>(1, gs.h[0].g.Py, lb.L, lb.total, nt, lds, s);
         else y_launch_m<T>(m, lb.L, lb.total, nt, lds, s);
@@ -810,11 +818,15 @@ hipError_t launch_eval(const GroupSet<T>& gs, const Epi<T>* epis, int mode, bool
         usey[j] = h.g.nz > 1 && yzy_m<T>(h) == 0 && y_key(h, gs.n > 1) == keys[kk];
         ly.set(j, usey[j] ? y3d_blocks(h.g, h.tu, h.batch) : 0);
         if (usey[j]) {
-          nty = std::max(nty, keys[kk] == kMixKey ? mix_threads(h) : h.tu.nt_y);
+          nty = std::max(nty, keys[kk] == kMixKey || sr_long(keys[kk]) ? mix_threads(h) : h.tu.nt_y);
           ldsy = std::max(ldsy, (size_t)h.tu.cb_y * col_stride(h.g.Py) * csz);
         }
       }
       if (ly.total == 0) continue;
+      if (sr_long(keys[kk])) {
+        long_launch<T>(true, keys[kk], ly.L, ly.total, nty, ldsy, s);
+        continue;
+      }
       if (keys[kk] == kMixKey) {
         if (gs.n == 1) len_launch<T>(2, gs.h[0].g.Py, ly.L, ly.total, nty, ldsy, s);
         else yinv_launch_m<T>(ly.L, ly.total, nty, ldsy, s);

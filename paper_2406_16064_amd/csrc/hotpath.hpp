@@ -858,6 +858,15 @@ __global__ void __launch_bounds__(512) k_ypass_m(Launch<T> L) {
     break;
     MMX_SR_LENGTHS(MMX_CASE)
 #undef MMX_CASE
+#define MMX_CASE(LL)                                                            \
+  case LL:                                                                      \
+    if constexpr (SL == LL) {                                                   \
+      if (g.nz == 1) y_fused2d<T, false, LL, 8, true>(hp, ep, bid, lds);        \
+      else if constexpr (LL < 1944) y_rows3d<T, false, false, LL, 8, true>(hp, ep, bid, lds); \
+    }                                                                           \
+    break;
+    MMX_SR_LONG(MMX_CASE)
+#undef MMX_CASE
     default: break;
   }
 }
@@ -875,6 +884,10 @@ __global__ void __launch_bounds__(512) k_yinv_m(Launch<T> L) {
 #define MMX_CASE(LL) \
   case LL: if constexpr (SL == 0 || SL == LL) y_rows3d<T, true, false, LL, 8, true>(hp, ep, bid, lds); break;
     MMX_SR_LENGTHS(MMX_CASE)
+#undef MMX_CASE
+#define MMX_CASE(LL) \
+  case LL: if constexpr (SL == LL && LL < 1944) y_rows3d<T, true, false, LL, 8, true>(hp, ep, bid, lds); break;
+    MMX_SR_LONG(MMX_CASE)
 #undef MMX_CASE
     default: break;
   }
@@ -2398,6 +2411,21 @@ void len_launch(int pass, int len, const Launch<T>& L, long long total, int nt, 
     else k_yinv_m<T, LL><<<grid, nt, lds, s>>>(L);                          \
     break;
     MMX_SR_LENGTHS(MMX_CASE)
+#undef MMX_CASE
+    default: break;
+  }
+}
+// The y passes of the longer lengths (sr_long): inv the inverse one.
+template <typename T>
+void long_launch(bool inv, int len, const Launch<T>& L, long long total, int nt, size_t lds, hipStream_t s) {
+  const dim3 grid((unsigned)total);
+  switch (len) {
+#define MMX_CASE(LL)                                           \
+  case LL:                                                     \
+    if (!inv) k_ypass_m<T, 0, LL><<<grid, nt, lds, s>>>(L);    \
+    else k_yinv_m<T, LL><<<grid, nt, lds, s>>>(L);             \
+    break;
+    MMX_SR_LONG(MMX_CASE)
 #undef MMX_CASE
     default: break;
   }

@@ -116,7 +116,8 @@ __host__ __device__ constexpr SrPlan sr_plan(int L) {
   return p;
 }
 // Threads a column: 8 entries each for a power of two, else as many as give
-// every stage at most 9 entries a thread.
+// every stage at most 9 entries a thread; beyond 1024 points 16 (two radix-9
+// butterflies 18), so that a film's three columns fit 512 threads.
 __host__ __device__ constexpr int sr_tpc(int L) {
   const SrPlan p = sr_plan(L);
   bool p2 = true;
@@ -124,7 +125,7 @@ __host__ __device__ constexpr int sr_tpc(int L) {
   if (p2) return L / 8;
   int t = 1;
   for (int s = 0; s < p.nst; ++s) {
-    const int R = p.rad[s], cap = R == 2 ? 4 : R == 3 ? 3 : R == 4 ? 2 : 1;
+    const int R = p.rad[s], cap = L > 1024 ? (R == 9 ? 2 : 16 / R) : R == 2 ? 4 : R == 3 ? 3 : R == 4 ? 2 : 1;
     const int n = (L / R + cap - 1) / cap;
     t = n > t ? n : t;
   }
@@ -148,6 +149,19 @@ __host__ __device__ constexpr int sr_psh(int L) {
 __host__ __device__ constexpr bool sr_compiled(int L) {
 #define MMX_CASE(LL) || L == LL
   return false MMX_SR_LENGTHS(MMX_CASE);
+#undef MMX_CASE
+}
+
+// Longer y columns compiled the same way, each length a kernel of its own (their
+// 16 entries a thread would cost the kernels that hold the lengths above their
+// registers): y of 900x900x1 93 -> 35 us (FP64 131 -> 76), forward and inverse y of
+// 600x600x8 178 -> 48 and 126 -> 54 us, with 42 to 62 registers in FP32, 74 to 114 in
+// FP64.  1944 points: films only (a 3-D tile of four columns does not fit the
+// run-time transform's threads, and such meshes are refused).
+#define MMX_SR_LONG(X) X(1152) X(1296) X(1458) X(1536) X(1728) X(1944)
+__host__ __device__ constexpr bool sr_long(int L) {
+#define MMX_CASE(LL) || L == LL
+  return false MMX_SR_LONG(MMX_CASE);
 #undef MMX_CASE
 }
 

@@ -522,10 +522,11 @@ mm_status choose_tuning(Group& G, mm_precision prec, size_t csz, bool pot, long 
     int cb = 8;
     // packed: the tile of slot 0 also holds the tensor rows of kx = Lx
     const int pk = y2d_packed(g);
-    while (sr_compiled(g.Py) && cb > 1 && 3 * cb * sr_tpc(g.Py) > 512) cb /= 2;
+    const bool list = sr_compiled(g.Py) || sr_long(g.Py);
+    while (list && cb > 1 && 3 * cb * sr_tpc(g.Py) > 512) cb /= 2;
     // batch launches: columns for 256 threads (32 films of 128x128: 19.2 with two
     // columns a workgroup, 21.7 with one, 20.7 with four)
-    const int tl = sr_compiled(g.Py) ? sr_tpc(g.Py) : tpc;
+    const int tl = list ? sr_tpc(g.Py) : tpc;
     while (cb > 1 && (cb * colb + (cb + pk) * ktab2 + ytab > budget || 3 * cb * tpc > 512 ||
                       (launch_rows > 0 ? 3 * cb * tl > 256 : g.Xp / cb < want)))
       cb /= 2;
@@ -543,14 +544,17 @@ mm_status choose_tuning(Group& G, mm_precision prec, size_t csz, bool pot, long 
     // has the columns (700x16x12: forward 11.3 with 16, 14.5 with 4)
     int tpc = std::max(tmin, std::min(2 * tmin, 64));
     const size_t colb = (size_t)col_stride(g.Py) * csz;
+    // a tile of one kx block has to fit with the run-time transform's threads
+    if (kSxB * colb > 160 * 1024 || kSxB * tpc > 512) return fail(MM_E_ARG, "mesh too long along y");
     int cb = kSxB;
     const bool compiled = 2 * g.ny == g.Py && (g.Py & (g.Py - 1)) == 0;
     if (prec == MM_F64 && compiled && g.Py >= 512 && 2 * tpc <= 256) {
       cb = 2;
       tpc *= 2;
     }
-    while (!sr_compiled(g.Py) && cb < 16 && cb * tpc < 64 && 3LL * g.nz * g.Xp / (2 * cb) >= want) cb *= 2;
-    while (cb > 1 && (cb * colb > budget || cb * tpc > 512 || (sr_compiled(g.Py) && cb * sr_tpc(g.Py) > 512))) cb /= 2;
+    const bool list = sr_compiled(g.Py) || sr_long(g.Py);
+    while (!list && cb < 16 && cb * tpc < 64 && 3LL * g.nz * g.Xp / (2 * cb) >= want) cb *= 2;
+    while (cb > 1 && (cb * colb > budget || cb * tpc > 512 || (list && cb * sr_tpc(g.Py) > 512))) cb /= 2;
     if (cb * colb > 160 * 1024 || cb * tpc > 512) return fail(MM_E_ARG, "mesh too long along y");
     t.cb_y = cb;
     t.tpc_y = tpc;

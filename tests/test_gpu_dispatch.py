@@ -232,3 +232,43 @@ def test_sd_step_inside_the_update_fp64(mm, nx, n):
         mo, taus = sd.run(lambda y: F.effective_field(y, F.Mesh(*mesh), op, kern), m0[b].copy(), n, 1e-7, 1e-10, 1e-3)
         assert np.max(np.linalg.norm(md[b].cpu().numpy() - mo, axis=0)) <= 1e-9
         assert abs(tau[b] - taus[-1]) <= 1e-9 * taus[-1]
+
+
+@pytest.mark.parametrize("prec,tol", [("f32", 1e-5), ("f64", 1e-11)])
+@pytest.mark.parametrize("L", [1152, 1296, 1458, 1536, 1728, 1944])
+def test_compiled_columns_beyond_1024(mm, L, prec, tol):
+    """Fields of films and two-plane meshes whose y columns take the longer
+    compiled transforms, full (2 ny = L) and short (3-D columns of 1944 points
+    are refused)."""
+    for mesh in ((6, L // 2, 1), (5, L // 2 - 2, 1), (4, L // 2, 2), (9, L // 2 - 1, 3)):
+        mesh = mesh + (2e-9, 3e-9, 2.5e-9)
+        if L == 1944 and mesh[2] > 1:
+            with pytest.raises(mm.MMError):
+                mm.Plan(mesh, prec, terms=F.ALL_TERMS)
+            continue
+        plan = mm.Plan(mesh, prec, terms=F.ALL_TERMS)
+        assert plan.padded()[1] == L
+        gp, op = gpu_params(mm, PAR, F.ALL_TERMS), oracle_params(PAR, F.ALL_TERMS)
+        m = representable(_m(mesh, L), plan.dtype)
+        H = plan.effective_field(gp, to_dev(m, plan.dtype)).double().cpu().numpy()
+        assert field_err(H, F.effective_field(m, F.Mesh(*mesh), op, F.DemagKernel(F.Mesh(*mesh)))) <= tol
+
+
+def test_long_columns_in_a_batch_fp64(mm):
+    """A batch of two long column lengths (films and separate passes) and a short
+    one: each trajectory against the oracle's."""
+    meshes = [(8, 600, 1, 2e-9, 2e-9, 2e-9), (6, 648, 2, 2e-9, 2e-9, 2e-9), (6, 760, 1, 2e-9, 2e-9, 2e-9),
+              (10, 64, 1, 2e-9, 2e-9, 2e-9)]
+    batch = mm.Batch(meshes, "f64")
+    gp, op = gpu_params(mm, PAR, F.ALL_TERMS), oracle_params(PAR, F.ALL_TERMS)
+    which = [0, 1, 2, 3, 0]
+    m0 = [_m(meshes[k], 95 + i) for i, k in enumerate(which)]
+    md = [to_dev(m, torch.float64) for m in m0]
+    t_end = 4e-14
+    batch.run([dict(mesh_id=k, params=gp, m=md[i], t_end=t_end, state=mm.new_states(1, h=2e-14, h_max=2e-14)[0])
+               for i, k in enumerate(which)])
+    for i, k in enumerate(which):
+        mesh = F.Mesh(*meshes[k])
+        kern = F.DemagKernel(mesh)
+        mo = dp45.run(lambda y: F.llg_rhs(y, mesh, op, kern), m0[i], dp45.State(h=2e-14, h_max=2e-14), t_end=t_end)
+        assert np.max(np.abs(md[i].cpu().numpy() - mo)) <= 1e-9
