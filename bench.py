@@ -459,10 +459,6 @@ def potential_bench(mm, inputs, torch, newell=None, reps=30):
     plan = mm.Plan(mesh, "f32", terms=terms)
     params = mm.make_params(terms=terms, **w["params"])
     m = torch.tensor(inputs.initial_state(2, mesh), dtype=torch.float32, device="cuda")
-    from paper_2406_16064_amd import tuned
-    sh = tuned.lookup(mesh, "f32")  # the slab's shapes of the forward passes and tiles
-    if sh is not None:
-        plan.set_shapes(sh)
     us_b2b, us = plan.profile_passes(params, m, reps=reps, in_order=True)
     pb = pot_pass_bytes(mesh, plan.padded(), 4)
     passes = [{"kernel": n, "us": round(t, 3), "alg_bytes": b, "gbs": round(b / (t * 1e-6) / 1e9, 1),
