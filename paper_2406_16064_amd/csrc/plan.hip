@@ -488,13 +488,10 @@ mm_status choose_tuning(Group& G, mm_precision prec, size_t csz, bool pot, long 
     // compiled kernels takes every mesh
     while (!pot && launch_rows > 0 && sr_compiled(g.Lx) && g.Lx <= 256 && ty > 1 && 3 * ty * sr_tpc(g.Lx) > 512)
       ty /= 2;
-    // potential route: long compiled rows run best in twos, three workgroups a CU
-    // (512x512x16 74.8 -> 67.2, FP64 161 -> 137; one row: 84); the general
-    // transform's keep the LDS limit (400x300x16 52 with four, 64 with two)
-    while (pot && g.Lx >= 512 && (g.Lx & (g.Lx - 1)) == 0 && ty > 2) ty /= 2;
     t.ty_x = ty;
     // Threads.  One cell a thread is the shortest chain but takes 145-166
-    // registers (three waves a SIMD, and one workgroup of 512 threads a CU):
+    // registers with the run-time transform, 83 in FP32 with compiled rows (three
+    // waves a SIMD of the former, and one workgroup of 512 threads a CU):
     // kept while the launch's waves all run at once, 12 a CU.  Beyond that two
     // or four cells a thread (122-126 registers) in workgroups of 256 threads,
     // 512 where a tile has more than 1024 cells (256x256x8 stage kernel 41.2 ->

@@ -551,23 +551,31 @@ hipError_t launch_potential(const GroupSet<T>& gs, const Epi<T>* epis, const Pot
     else k_pot_yinv<T, false><<<dim3((unsigned)blocks), nt, lds, s>>>(h, p.cb_y, p.tpc_y);
   }
   if (pass_mask & 16u) {
-    const long long blocks = ((long long)h.batch * g.nz * ((g.ny + h.tu.ty_x - 1) / h.tu.ty_x) + 7) / 8 * 8;
+    // Long compiled rows run best in twos where the epilogue reads no earlier
+    // slopes, three workgroups a CU (512x512x16 74.8 -> 67.2, FP64 161 -> 137; one
+    // row: 84); the Runge-Kutta epilogues keep the rows of the launch shape (an
+    // attempt 1.957 ms with two, 1.891 with four).
+    HotPlan<T> hx = h;
+    const bool p2l = g.Lx >= 512 && (g.Lx & (g.Lx - 1)) == 0;
+    if (p2l && mode != MODE_STAGE && mode != MODE_ERROR) hx.tu.ty_x = std::min(h.tu.ty_x, 2);
+    const PotShape px = pot_shape(hx);
+    const long long blocks = ((long long)h.batch * g.nz * ((g.ny + hx.tu.ty_x - 1) / hx.tu.ty_x) + 7) / 8 * 8;
     const T cx = T(pt.gdx), cy = T(pt.gdy), cz = T(pt.gdz);
-    const int cpt = p.cpt_x;
+    const int cpt = px.cpt_x;
     const dim3 grid((unsigned)blocks);
     auto go_p2 = [&](auto mode_c, auto p2_c) {
       constexpr int MD = decltype(mode_c)::value;
       constexpr bool P2 = decltype(p2_c)::value;
       switch (cpt) {
-        case 1: k_pot_x<T, MD, 1, P2><<<grid, p.nt_x, p.lds_x, s>>>(h, epis, p.tpc_x, cx, cy, cz); break;
-        case 2: k_pot_x<T, MD, 2, P2><<<grid, p.nt_x, p.lds_x, s>>>(h, epis, p.tpc_x, cx, cy, cz); break;
-        case 4: k_pot_x<T, MD, 4, P2><<<grid, p.nt_x, p.lds_x, s>>>(h, epis, p.tpc_x, cx, cy, cz); break;
-        case 8: k_pot_x<T, MD, 8, P2><<<grid, p.nt_x, p.lds_x, s>>>(h, epis, p.tpc_x, cx, cy, cz); break;
-        default: k_pot_x<T, MD, 0, P2><<<grid, p.nt_x, p.lds_x, s>>>(h, epis, p.tpc_x, cx, cy, cz); break;
+        case 1: k_pot_x<T, MD, 1, P2><<<grid, px.nt_x, px.lds_x, s>>>(hx, epis, px.tpc_x, cx, cy, cz); break;
+        case 2: k_pot_x<T, MD, 2, P2><<<grid, px.nt_x, px.lds_x, s>>>(hx, epis, px.tpc_x, cx, cy, cz); break;
+        case 4: k_pot_x<T, MD, 4, P2><<<grid, px.nt_x, px.lds_x, s>>>(hx, epis, px.tpc_x, cx, cy, cz); break;
+        case 8: k_pot_x<T, MD, 8, P2><<<grid, px.nt_x, px.lds_x, s>>>(hx, epis, px.tpc_x, cx, cy, cz); break;
+        default: k_pot_x<T, MD, 0, P2><<<grid, px.nt_x, px.lds_x, s>>>(hx, epis, px.tpc_x, cx, cy, cz); break;
       }
     };
     const bool p2 = (g.Lx == 128 || g.Lx == 256 || g.Lx == 512 || g.Lx == 1024) &&
-                    2 * (h.tu.ty_x + 1) * (g.Lx / 16) <= p.nt_x;
+                    2 * (hx.tu.ty_x + 1) * (g.Lx / 16) <= px.nt_x;
     auto go = [&](auto mode_c) {
       if (p2) go_p2(mode_c, std::true_type{});
       else go_p2(mode_c, std::false_type{});
