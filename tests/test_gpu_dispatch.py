@@ -5,6 +5,7 @@ import pytest
 
 from oracle import dp45, sd
 from oracle import fields as F
+from oracle import potential
 from paper_2406_16064_amd import inputs
 
 from _util import field_err, gpu_params, oracle_params, representable, to_dev
@@ -272,3 +273,35 @@ def test_long_columns_in_a_batch_fp64(mm):
         kern = F.DemagKernel(mesh)
         mo = dp45.run(lambda y: F.llg_rhs(y, mesh, op, kern), m0[i], dp45.State(h=2e-14, h_max=2e-14), t_end=t_end)
         assert np.max(np.abs(md[i].cpu().numpy() - mo)) <= 1e-9
+
+
+@pytest.mark.parametrize("prec,tol", [("f32", 1e-5), ("f64", 1e-11)])
+@pytest.mark.parametrize("nx,rows", [(128, 1), (127, 4), (256, 2), (512, 4), (512, 1), (509, 2), (1024, 2)])
+def test_potential_rows(mm, nx, rows, prec, tol):
+    """The scalar-potential route's inverse x of the compiled rows at the rows a
+    workgroup of the launch shape, which long rows take at most two of outside
+    the integrators, with a short last tile: field and dm/dt, and two attempts in
+    FP64 (the Runge-Kutta epilogues keep the shape's rows)."""
+    mesh = (nx, 9, 2, 3e-9, 2e-9, 2.5e-9)
+    local = F.EXCHANGE | F.DMI | F.ANIS | F.ZEEMAN
+    plan = mm.Plan(mesh, prec, terms=local | mm.DEMAG_POTENTIAL)
+    try:
+        plan.set_shapes(dict(ty_x=rows, nt_i=512, ty_f=1))
+    except mm.MMError:
+        pytest.skip("four FP64 rows of 512 points exceed LDS")
+    gp, op = gpu_params(mm, PAR, local | mm.DEMAG_POTENTIAL), oracle_params(PAR, local | F.DEMAG)
+    m = representable(_m(mesh, 97), plan.dtype)
+    kern = potential.PotentialKernel(F.Mesh(*mesh), P=tuple(plan.padded()[::-1]))
+    field = lambda y: potential.effective_field(y, F.Mesh(*mesh), op, kern)
+    md = to_dev(m, plan.dtype)
+    Href = field(m)
+    assert field_err(plan.effective_field(gp, md).double().cpu().numpy(), Href) <= tol
+    k = F.llg_rhs_from_field(m, Href, op)
+    assert field_err(plan.llg_rhs(gp, md).double().cpu().numpy(), k) <= tol
+    if prec == "f64":
+        st, ost, mo = mm.new_states(1, h=2e-14), dp45.State(h=2e-14), m
+        for _ in range(2):
+            plan.rk45_step([gp], md, st)
+            mo, acc = dp45.step(lambda y: F.llg_rhs_from_field(y, field(y), op), mo, ost)
+            assert bool(st[0].last_accepted) == acc
+        assert field_err(md.cpu().numpy(), mo) <= 1e-10
