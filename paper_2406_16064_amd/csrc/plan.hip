@@ -757,12 +757,12 @@ void free_engine(Engine& E) {
   if (E.cap) (void)hipStreamDestroy(E.cap);
 }
 
-// Geometry of the padded grid (Px, Py, Pz), default launch shapes, the
-// transform tables and the demag spectrum (Newell tensor or scalar-potential
-// kernel) of G's mesh.  The grid's buffers (G.Sx, G.Sy) follow in engine_reserve.
-mm_status build_padded(Engine& E, Group& G, int Px, int Py, int Pz, hipStream_t s) {
+// Geometry of G's mesh on the padded grid (Px, Py, Pz).
+void set_padded(Group& G, int Px, int Py, int Pz) {
   Geo& g = G.g;
-  const bool pot = (E.terms & MM_DEMAG_POTENTIAL) != 0;
+  g.nx = G.mesh.nx;
+  g.ny = G.mesh.ny;
+  g.nz = G.mesh.nz;
   g.Px = Px;
   g.Py = Py;
   g.Pz = Pz;
@@ -775,6 +775,15 @@ mm_status build_padded(Engine& E, Group& G, int Px, int Py, int Pz, hipStream_t 
   g.sx = 3LL * g.nz * g.XB * kSxB * g.ny;
   g.sy = 3LL * g.nz * g.Xp * g.Py;
   g.dV = G.mesh.dx * G.mesh.dy * G.mesh.dz;
+}
+
+// Geometry of the padded grid (Px, Py, Pz), default launch shapes, the
+// transform tables and the demag spectrum (Newell tensor or scalar-potential
+// kernel) of G's mesh.  The grid's buffers (G.Sx, G.Sy) follow in engine_reserve.
+mm_status build_padded(Engine& E, Group& G, int Px, int Py, int Pz, hipStream_t s) {
+  const Geo& g = G.g;
+  const bool pot = (E.terms & MM_DEMAG_POTENTIAL) != 0;
+  set_padded(G, Px, Py, Pz);
   MMCHK(choose_tuning(G, E.prec, E.csz, pot));
   if (E.terms & MM_DEMAG) {
     MMCHK(dev_alloc(&G.kt, E.rsz * G.ncomp * (size_t)g.Kz * g.Xp * g.Ky));
@@ -799,12 +808,10 @@ int min_padded(int n, bool pot) { return pot ? 2 * n : 2 * n - 1; }
 mm_status make_group(Engine& E, const mm_mesh& mesh, hipStream_t s, Group& G) {
   G.mesh = mesh;
   G.ncomp = mesh.nz == 1 ? 4 : 6;
-  Geo& g = G.g;
-  g.nx = mesh.nx; g.ny = mesh.ny; g.nz = mesh.nz;
   const bool pot = (E.terms & MM_DEMAG_POTENTIAL) != 0;
-  const int Px = pot ? pick_padded_pot(g.nx, true) : pick_padded(g.nx, true);
-  const int Py = pot ? pick_padded_pot(g.ny, false) : pick_padded(g.ny, false);
-  const int Pz = pot ? pick_padded_pot(g.nz, false) : pick_padded(g.nz, false);
+  const int Px = pot ? pick_padded_pot(mesh.nx, true) : pick_padded(mesh.nx, true);
+  const int Py = pot ? pick_padded_pot(mesh.ny, false) : pick_padded(mesh.ny, false);
+  const int Pz = pot ? pick_padded_pot(mesh.nz, false) : pick_padded(mesh.nz, false);
   return build_padded(E, G, Px, Py, Pz, s);
 }
 

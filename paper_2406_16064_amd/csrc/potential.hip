@@ -551,13 +551,8 @@ hipError_t launch_potential(const GroupSet<T>& gs, const Epi<T>* epis, const Pot
     else k_pot_yinv<T, false><<<dim3((unsigned)blocks), nt, lds, s>>>(h, p.cb_y, p.tpc_y);
   }
   if (pass_mask & 16u) {
-    // Long compiled rows run best in twos where the epilogue reads no earlier
-    // slopes, three workgroups a CU (512x512x16 74.8 -> 67.2, FP64 161 -> 137; one
-    // row: 84); the Runge-Kutta epilogues keep the rows of the launch shape (an
-    // attempt 1.957 ms with two, 1.891 with four).
     HotPlan<T> hx = h;
-    const bool p2l = g.Lx >= 512 && (g.Lx & (g.Lx - 1)) == 0;
-    if (p2l && mode != MODE_STAGE && mode != MODE_ERROR) hx.tu.ty_x = std::min(h.tu.ty_x, 2);
+    hx.tu.ty_x = pot_x_rows(g, h.tu, mode);
     const PotShape px = pot_shape(hx);
     const long long blocks = ((long long)h.batch * g.nz * ((g.ny + hx.tu.ty_x - 1) / hx.tu.ty_x) + 7) / 8 * 8;
     const T cx = T(pt.gdx), cy = T(pt.gdy), cz = T(pt.gdz);

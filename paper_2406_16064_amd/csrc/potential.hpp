@@ -30,6 +30,18 @@ struct PotShape {
 template <typename T>
 PotShape pot_shape(const HotPlan<T>& h);
 
+// Rows a workgroup of the inverse x pass takes for epilogue `mode`.  Long
+// compiled rows run best in twos where the epilogue reads no earlier slopes,
+// three workgroups a CU (512x512x16 field and dm/dt 74.8 -> 67.2 us, FP64 161 ->
+// 137; one row: 84); the Runge-Kutta epilogues keep the rows of the launch shape
+// (an attempt 1.957 ms with two, 1.891 with four).  The energy epilogues keep
+// them as well: they write one partial sum a workgroup, and the buffer and the
+// reduction count workgroups by the launch shape (eval_blocks_per_inst).
+inline int pot_x_rows(const Geo& g, const Tuning& tu, int mode) {
+  const bool two = g.Lx >= 512 && (g.Lx & (g.Lx - 1)) == 0 && (mode == MODE_FIELD || mode == MODE_RHS);
+  return two && tu.ty_x > 2 ? 2 : tu.ty_x;
+}
+
 // The route's launch shapes fit the group (nz >= 2, LDS, threads per transform
 // at least tpc_x_min).
 template <typename T>

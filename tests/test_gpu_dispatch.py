@@ -305,3 +305,50 @@ def test_potential_rows(mm, nx, rows, prec, tol):
             mo, acc = dp45.step(lambda y: F.llg_rhs_from_field(y, field(y), op), mo, ost)
             assert bool(st[0].last_accepted) == acc
         assert field_err(md.cpu().numpy(), mo) <= 1e-10
+
+
+@pytest.mark.parametrize("prec,tol", [("f32", 1e-5), ("f64", 1e-10)])
+@pytest.mark.parametrize("nx,rows", [(127, 4), (256, 8), (512, 1), (512, 2), (512, 4), (509, 4), (1024, 2)])
+def test_potential_energy_rows(mm, nx, rows, prec, tol):
+    """Energies of two instances on the scalar-potential route at the rows a
+    workgroup of the launch shape, long rows in fours among them (one partial sum
+    a workgroup, counted by the shape where they are summed), with a short last
+    tile: each instance against the oracle, to the field's bar of the sum of its
+    terms, and the same again after a field of the same plan (in twos)."""
+    mesh = (nx, 9, 2, 3e-9, 2e-9, 2.5e-9)
+    local = F.EXCHANGE | F.DMI | F.ANIS | F.ZEEMAN
+    plan = mm.Plan(mesh, prec, terms=local | mm.DEMAG_POTENTIAL, max_batch=2)
+    plan.set_shapes(dict(ty_x=rows, nt_i=512, ty_f=1))
+    gp, op = gpu_params(mm, PAR, local | mm.DEMAG_POTENTIAL), oracle_params(PAR, local | F.DEMAG)
+    m = [representable(_m(mesh, s), plan.dtype) for s in (98, 99)]
+    kern = potential.PotentialKernel(F.Mesh(*mesh), P=tuple(plan.padded()[::-1]))
+    md = to_dev(np.stack(m), plan.dtype)
+    E = plan.energy([gp, gp], md)
+    for b in range(2):
+        Eref = potential.energies(m[b], F.Mesh(*mesh), op, kern)
+        assert np.all(np.abs(E[b] - Eref) <= tol * np.sum(np.abs(Eref))), (E[b], Eref)
+    plan.effective_field([gp, gp], md)
+    assert np.array_equal(plan.energy([gp, gp], md), E)
+
+
+def test_potential_energy_default_rows_fp32(mm):
+    """A slab whose default shape takes four rows a workgroup: the demag energy of
+    two instances against the FP64 sum over the cells of m . H from the field call
+    (H to 1e-5 of its largest value), and no other term."""
+    mesh = (512, 256, 16, 5e-9, 5e-9, 5e-9)
+    plan = mm.Plan(mesh, "f32", terms=mm.DEMAG_POTENTIAL, max_batch=2)
+    assert plan.shapes()["ty_x"] == 4
+    gp = gpu_params(mm, PAR, mm.DEMAG_POTENTIAL)
+    md = to_dev(np.stack([_m(mesh, s) + np.array([0.0, 0.0, w]).reshape(3, 1, 1, 1) for s, w in ((1, 2.0), (2, -1.0))]),
+                plan.dtype)
+    md /= md.norm(dim=1, keepdim=True)
+    E = plan.energy([gp, gp], md)
+    H = plan.effective_field([gp, gp], md)
+    V = mesh[3] * mesh[4] * mesh[5]
+    c = -0.5 * 4e-7 * np.pi * PAR["Ms"] * V
+    for b in range(2):
+        mh = md[b].double() * H[b].double()
+        ref = c * float(mh.sum())
+        bar = 1e-5 * abs(c) * float(H[b].double().norm(dim=0).max()) * md[b, 0].numel()
+        assert abs(E[b][1] - ref) <= bar and abs(ref) > 100 * bar
+        assert np.all(E[b][[0, 2, 3, 4]] == 0.0)

@@ -1,0 +1,79 @@
+"""Host rules of the launch shapes, worked through on the CPU: a program that
+compiles the host runtime's own source with a main() of its own and links the
+built library, so that the rules checked are the ones that launch."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+PKG = os.path.join(ROOT, "paper_2406_16064_amd")
+
+HEAD = r"""
+#include "%s/csrc/plan.hip"
+
+Group group(int nx, int ny, int nz, bool pot) {
+  Group G;
+  G.mesh = mm_mesh{nx, ny, nz, 3e-9, 2e-9, 2.5e-9};
+  G.ncomp = nz == 1 ? 4 : 6;
+  if (pot) set_padded(G, pick_padded_pot(nx, true), pick_padded_pot(ny, false), pick_padded_pot(nz, false));
+  else set_padded(G, pick_padded(nx, true), pick_padded(ny, false), pick_padded(nz, false));
+  return G;
+}
+size_t csz_of(mm_precision prec) { return prec == MM_F32 ? sizeof(Cx<float>) : sizeof(Cx<double>); }
+""" % PKG
+
+
+def _run(tmp_path, main):
+    """Lines that the program with this main() prints, split into words."""
+    if not os.path.exists(os.path.join(PKG, "libmmx.so")):
+        pytest.fail("libmmx.so not built (run python -m paper_2406_16064_amd.build)")
+    from paper_2406_16064_amd.build import _hipcc
+    src, exe = str(tmp_path / "rules.hip"), str(tmp_path / "rules")
+    with open(src, "w") as f:
+        f.write(HEAD + main)
+    r = subprocess.run([_hipcc(), "--offload-arch=gfx950", "-O0", "-std=c++17", src, "-o", exe, "-L" + PKG,
+                        "-l:libmmx.so", "-Wl,-rpath," + PKG], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    r = subprocess.run([exe], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    return [line.split() for line in r.stdout.splitlines()]
+
+
+def test_potential_energy_partials_written_are_those_reserved(tmp_path):
+    """Scalar-potential route: the energy pass writes one partial sum a workgroup;
+    their number, by the rows the launch takes, is the one that the buffer and the
+    reduction count by the launch shape, for every shape that a plan accepts."""
+    lines = _run(tmp_path, r"""
+int main() {
+  for (mm_precision prec : {MM_F32, MM_F64})
+    for (int nx : {20, 128, 256, 400, 487, 509, 512, 700, 1000, 1024})
+      for (int ny : {1, 3, 9, 64, 512})
+        for (int nz : {2, 16}) {
+          Group G = group(nx, ny, nz, true);
+          if (choose_tuning(G, prec, csz_of(prec), true) != MM_OK) continue;
+          const Tuning def = G.tu;
+          for (int ty : {0, 1, 2, 4, 8, 16})  // 0: the default shape
+            for (int nt : {64, 128, 256, 512}) {
+              Tuning t = def;
+              if (ty > 0) {
+                t.ty_x = ty;
+                t.nt_i = nt;
+                t.tpc_x = nt / (3 * ty);
+                if (!tuning_ok(G, t, prec, csz_of(prec))) continue;
+              }
+              G.tu = t;
+              if (!(prec == MM_F32 ? pot_fits<float>(G) : pot_fits<double>(G))) continue;
+              const int rows = pot_x_rows(G.g, t, MODE_ENERGY);
+              printf("%d %d %d %d %d %d %d %d\n", (int)prec, nx, ny, nz, ty, t.ty_x,
+                     nz * ((ny + rows - 1) / rows), eval_blocks_per_inst(G.g, t));
+            }
+        }
+}
+""")
+    rows = [[int(v) for v in line] for line in lines]
+    for prec, nx, ny, nz, ty, ty_x, written, reserved in rows:
+        assert written == reserved, (prec, nx, ny, nz, ty_x)
+    # shapes of more than two rows on long compiled rows are among them, by default too
+    assert any(nx in (509, 512) and ty_x > 2 for _, nx, _, _, _, ty_x, _, _ in rows)
+    assert {ty_x for prec, nx, ny, nz, ty, ty_x, _, _ in rows if (prec, nx, ny, nz, ty) == (0, 512, 512, 16, 0)} == {4}
