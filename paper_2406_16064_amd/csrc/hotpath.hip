@@ -514,17 +514,6 @@ int inv_cpt(const GroupSet<T>& gs, int nt) {
   return 0;
 }
 
-// Whether a group's inverse-x pass takes the kernels compiled for the lengths of
-// the list and 1024 (inv_x_launch_any): it has such an Lx and its workgroup holds
-// its columns' threads.  The other groups of a launch take the general kernel in
-// a launch of their own, so that a mesh has one plan, and the same bits, alone and
-// in a batch of others.
-template <typename T>
-bool inv_x_any(const HotPlan<T>& h) {
-  const int L = h.g.Lx;
-  return (sr_compiled(L) || L == 1024) && 3 * h.tu.ty_x * sr_tpc(L) <= h.tu.nt_i;
-}
-
 template <typename T>
 bool eval_fusable(const GroupSet<T>& gs) {
   int nt = 64;
@@ -861,7 +850,7 @@ hipError_t launch_eval(const GroupSet<T>& gs, const Epi<T>* epis, int mode, bool
     bool listed[kMaxGroups];
     int cpt_listed = 1;
     for (int i = 0; i < gs.n; ++i) {
-      listed[i] = demag && (mode != MODE_STAGE || fuse) && inv_x_any(gs.h[i]);
+      listed[i] = demag && (mode != MODE_STAGE || fuse) && inv_x_any(gs.h[i].g, gs.h[i].tu, nt);
       if (listed[i]) cpt_listed = std::max(cpt_listed, (gs.h[i].tu.ty_x * gs.h[i].g.nx + nt - 1) / nt);
     }
     if (cpt_listed > (gen ? 2 : 4))  // compiled for one, two and four cells a thread (general material: to two)

@@ -94,6 +94,21 @@ struct Tuning {
   int tpc_z;
 };
 
+// Whether a group's inverse-x pass takes the kernels compiled for the lengths of
+// the list and 1024 (inv_x_launch_any): it has such an Lx and the launch's
+// workgroups, nt threads (the largest nt_i of its meshes), hold its columns'
+// threads.  The other groups of a launch take the general kernel in a launch of
+// their own.  Lengths with threes, whose compiled plan is another than the
+// general kernel's, always get the threads by choose_tuning's shapes, so that a
+// mesh has one plan, and the same bits, alone and in a batch of others; powers of
+// two have the same plan in both.  A batch of meshes all of one power of two
+// keeps the general kernel's 256 threads: with 512 for the compiled one 24 films
+// of 256x256 in FP64 take 12.35 ms for 11.65, eight 256x256x4 in FP32 8.72 for 8.51.
+inline bool inv_x_any(const Geo& g, const Tuning& tu, int nt) {
+  const int L = g.Lx;
+  return (sr_compiled(L) || L == 1024) && 3 * tu.ty_x * sr_tpc(L) <= nt;
+}
+
 // Static description of one group (device resident, one entry per group).
 template <typename T> struct HotPlan {
   Geo g;

@@ -352,3 +352,22 @@ def test_potential_energy_default_rows_fp32(mm):
         bar = 1e-5 * abs(c) * float(H[b].double().norm(dim=0).max()) * md[b, 0].numel()
         assert abs(E[b][1] - ref) <= bar and abs(ref) > 100 * bar
         assert np.all(E[b][[0, 2, 3, 4]] == 0.0)
+
+
+@pytest.mark.parametrize("prec", ["f32", "f64"])
+def test_mixed_batch_has_the_bits_of_each_mesh_alone(mm, prec):
+    """A batch whose launch has 512 threads, so that rows of a power of two take the
+    compiled inverse x with four rows a workgroup beside a length with threes:
+    three steps of every instance bit for bit those of a plan of its mesh."""
+    meshes = [(256, 256, 1, 2e-9, 2e-9, 2e-9), (96, 96, 1, 2e-9, 2e-9, 2e-9), (128, 64, 2, 2e-9, 2e-9, 2e-9)]
+    batch = mm.Batch(meshes, prec)
+    gp = gpu_params(mm, PAR, F.ALL_TERMS)
+    plans = [mm.Plan(m, prec, terms=F.ALL_TERMS) for m in meshes]
+    which = [i % 3 for i in range(48)]
+    m0 = [to_dev(_m(meshes[k], 200 + i), plans[k].dtype) for i, k in enumerate(which)]
+    md = [m.clone() for m in m0]
+    state = lambda: mm.new_states(1, h=1e-14, h_max=1e-14)
+    batch.run([dict(mesh_id=k, params=gp, m=md[i], t_end=3e-14, state=state()[0]) for i, k in enumerate(which)])
+    for i in (0, 1, 2, 45, 46, 47):
+        plans[which[i]].rk45_run(gp, m0[i], state(), t_end=3e-14)
+        assert torch.equal(m0[i], md[i]), i

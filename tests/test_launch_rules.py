@@ -77,3 +77,52 @@ int main() {
     # shapes of more than two rows on long compiled rows are among them, by default too
     assert any(nx in (509, 512) and ty_x > 2 for _, nx, _, _, _, ty_x, _, _ in rows)
     assert {ty_x for prec, nx, ny, nz, ty, ty_x, _, _ in rows if (prec, nx, ny, nz, ty) == (0, 512, 512, 16, 0)} == {4}
+
+
+def test_compiled_inverse_x_takes_every_mesh_of_a_mixed_batch(tmp_path):
+    """Batch launches: a mesh whose rows have a compiled length with threes takes the
+    compiled inverse-x kernels with its own threads, one of a power of two up to
+    256 points wherever the launch has 512, at most four cells a thread; the sweep's
+    meshes together have 512."""
+    lines = _run(tmp_path, r"""
+int main() {
+  for (mm_precision prec : {MM_F32, MM_F64})
+    for (int nx = 2; nx <= 1024; ++nx)
+      for (int ny : {1, 2, 5, 16, 64, 256})
+        for (int nz : {1, 4}) {
+          Group G = group(nx, ny, nz, false);
+          if (!sr_compiled(G.g.Lx)) continue;
+          for (int n : {1, 4, 32, 256, 4096}) {
+            if (choose_tuning(G, prec, csz_of(prec), false, (long long)n * ny * nz) != MM_OK) continue;
+            printf("%d %d %d %d %d %d %d %d %d\n", (int)prec, nx, ny, nz, n, G.g.Lx,
+                   inv_x_any(G.g, G.tu, G.tu.nt_i) ? 1 : 0, inv_x_any(G.g, G.tu, 512) ? 1 : 0,
+                   (G.tu.ty_x * nx + G.tu.nt_i - 1) / G.tu.nt_i);
+          }
+        }
+  // launches of the sweep's sizes, films and two planes, n instances of each
+  for (mm_precision prec : {MM_F32, MM_F64})
+    for (int n : {4, 32}) {
+      const int sizes[] = {32, 64, 96, 128, 192, 256};
+      long long rows = 0;
+      for (int a : sizes) rows += n * 3LL * a;
+      std::vector<Group> gs;
+      int nt = 64;
+      for (int a : sizes)
+        for (int nz : {1, 2}) {
+          gs.push_back(group(a, a, nz, false));
+          if (choose_tuning(gs.back(), prec, csz_of(prec), false, rows) != MM_OK) return 1;
+          nt = std::max(nt, gs.back().tu.nt_i);
+        }
+      for (const Group& G : gs) printf("sweep %d %d %d\n", nt, G.g.nx, inv_x_any(G.g, G.tu, nt) ? 1 : 0);
+    }
+}
+""")
+    rows = [[int(v) for v in line] for line in lines if line[0] != "sweep"]
+    assert len(rows) > 10000
+    for prec, nx, ny, nz, n, Lx, own, with512, cells in rows:
+        if Lx & (Lx - 1) or Lx <= 256:
+            assert with512 and cells <= 4, (prec, nx, ny, nz, n, Lx, cells)
+        if Lx & (Lx - 1):
+            assert own, (prec, nx, ny, nz, n, Lx)
+    sweep = [line[1:] for line in lines if line[0] == "sweep"]
+    assert len(sweep) == 48 and all(takes == "1" for _, _, takes in sweep)
