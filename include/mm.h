@@ -20,7 +20,9 @@
  *   (float for MM_F32, double for MM_F64).  The caller owns them.
  * - Compute calls are ordered on the given HIP stream (hipStream_t passed as
  *   void*; NULL = the default stream) and return before the work finishes,
- *   except where a call says it synchronises.
+ *   except where a call says it synchronises.  They keep tables on the device
+ *   between calls and cannot be recorded into a caller's graph: on a stream that
+ *   is being captured they return MM_E_HIP and record nothing.
  * - Every call returns an mm_status.  Arguments are validated before any HIP
  *   call; on MM_E_ARG nothing is launched.  mm_last_error() gives a
  *   thread-local message for the last failure.  On an integration error the
@@ -258,9 +260,8 @@ mm_status mm_heun_run(mm_plan* plan, const mm_params* params, int32_t batch, voi
 mm_status mm_sd_run(mm_plan* plan, const mm_params* params, int32_t batch, void* m, int64_t n_iter,
                     double tau0, double tau_min, double tau_max, double* tau_out, void* hip_stream);
 
-/* mm_sd_run for callers that cannot allocate device memory (code under HIP
- * graph capture, tight serving loops, harnesses that forbid allocation): the
- * same iteration and results, but the scratch that mm_sd_run keeps in the plan
+/* mm_sd_run for callers that cannot allocate device memory (tight serving
+ * loops, harnesses that forbid allocation): the same iteration and results, but the scratch that mm_sd_run keeps in the plan
  * and grows for larger batches (FP64 partial sums, 4 per 256 cells per instance,
  * and the step sizes) comes from a fixed 16 MiB array in device memory that every
  * GPU the library runs on holds until the process ends.  This call allocates

@@ -932,7 +932,9 @@ mm_status put(Engine& E, int region, void* dst, const void* src, size_t bytes, h
 }
 
 // The compute calls keep tables on the device between calls and are not
-// recorded into a caller's graph.
+// recorded into a caller's graph: each refuses a stream that is being captured
+// before it touches the stream or the plan, so that the caller's graph holds no
+// copy to or from buffers of a call that did not take place.
 mm_status not_capturing(hipStream_t s) {
   hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
   HIPCHK(hipStreamIsCapturing(s, &st));
@@ -943,7 +945,6 @@ mm_status not_capturing(hipStream_t s) {
 // Upload parameters (in group order) and remember whether demag is on.
 mm_status upload_params(Engine& E, const std::vector<const mm_params*>& q, const std::vector<int>& grp,
                         hipStream_t s) {
-  MMCHK(not_capturing(s));
   std::vector<DevParams> d(q.size());
   E.any_demag = false;
   E.any_pot = false;
@@ -2336,6 +2337,7 @@ mm_status mm_plan_set_cells(mm_plan* p, int32_t instance, const double* Ms, cons
     if (!is_fin(D[i])) return fail(MM_E_ARG, "cell D must be finite");
   }
   hipStream_t s = (hipStream_t)hip_stream;
+  MMCHK(not_capturing(s));
   return p->e.prec == MM_F32 ? set_cells_impl<float>(p, instance, Ms, A, D, s)
                              : set_cells_impl<double>(p, instance, Ms, A, D, s);
 }
@@ -2381,6 +2383,7 @@ mm_status mm_effective_field(mm_plan* p, const mm_params* q, int32_t batch, cons
   MMCHK(plan_checks(p, q, batch, kCallEval));
   if (!m || !H) return fail(MM_E_ARG, "null array");
   hipStream_t s = (hipStream_t)hip_stream;
+  MMCHK(not_capturing(s));
   return p->e.prec == MM_F32 ? single_eval<float>(p, batch, q, m, H, MODE_FIELD, nullptr, s)
                              : single_eval<double>(p, batch, q, m, H, MODE_FIELD, nullptr, s);
 }
@@ -2389,6 +2392,7 @@ mm_status mm_llg_rhs(mm_plan* p, const mm_params* q, int32_t batch, const void* 
   MMCHK(plan_checks(p, q, batch, kCallEval));
   if (!m || !dmdt) return fail(MM_E_ARG, "null array");
   hipStream_t s = (hipStream_t)hip_stream;
+  MMCHK(not_capturing(s));
   return p->e.prec == MM_F32 ? single_eval<float>(p, batch, q, m, dmdt, MODE_RHS, nullptr, s)
                              : single_eval<double>(p, batch, q, m, dmdt, MODE_RHS, nullptr, s);
 }
@@ -2397,6 +2401,7 @@ mm_status mm_energy(mm_plan* p, const mm_params* q, int32_t batch, const void* m
   MMCHK(plan_checks(p, q, batch, kCallEval));
   if (!m || !E_out) return fail(MM_E_ARG, "null array");
   hipStream_t s = (hipStream_t)hip_stream;
+  MMCHK(not_capturing(s));
   return p->e.prec == MM_F32 ? energy_impl<float>(p, q, batch, m, E_out, s)
                              : energy_impl<double>(p, q, batch, m, E_out, s);
 }
@@ -2406,6 +2411,7 @@ mm_status mm_rk45_step(mm_plan* p, const mm_params* q, int32_t batch, void* m, m
   MMCHK(plan_checks(p, q, batch, kCallIntegrator));
   if (!m || !st) return fail(MM_E_ARG, "null array");
   hipStream_t s = (hipStream_t)hip_stream;
+  MMCHK(not_capturing(s));
   return p->e.prec == MM_F32 ? plan_rk45<float>(p, q, batch, m, st, HUGE_VAL, 2, nullptr, 0, true, s)
                              : plan_rk45<double>(p, q, batch, m, st, HUGE_VAL, 2, nullptr, 0, true, s);
 }
@@ -2417,6 +2423,7 @@ mm_status mm_rk45_run(mm_plan* p, const mm_params* q, int32_t batch, void* m, mm
   if (max_steps < 1) return fail(MM_E_ARG, "max_steps must be >= 1");
   if (!replay_h && !is_fin(t_end)) return fail(MM_E_ARG, "t_end must be finite");
   hipStream_t s = (hipStream_t)hip_stream;
+  MMCHK(not_capturing(s));
   return p->e.prec == MM_F32
              ? plan_rk45<float>(p, q, batch, m, st, t_end, max_steps, replay_h, n_replay, false, s)
              : plan_rk45<double>(p, q, batch, m, st, t_end, max_steps, replay_h, n_replay, false, s);
@@ -2430,6 +2437,7 @@ mm_status mm_sd_run(mm_plan* p, const mm_params* q, int32_t batch, void* m, int6
   if (!(tau_min > 0) || !is_fin(tau_max) || !(tau_min <= tau0) || !(tau0 <= tau_max))
     return fail(MM_E_ARG, "need 0 < tau_min <= tau0 <= tau_max (finite)");
   hipStream_t s = (hipStream_t)hip_stream;
+  MMCHK(not_capturing(s));
   return p->e.prec == MM_F32
              ? sd_impl<float>(p, q, batch, (float*)m, n_iter, tau0, tau_min, tau_max, tau_out, 0.0, nullptr, nullptr, s)
              : sd_impl<double>(p, q, batch, (double*)m, n_iter, tau0, tau_min, tau_max, tau_out, 0.0, nullptr, nullptr,
@@ -2447,9 +2455,10 @@ mm_status mm_sd_run_noalloc(mm_plan* p, const mm_params* q, int32_t batch, void*
   if (need > kScratchBytes)
     return fail(MM_E_ARG, "mm_sd_run_noalloc needs " + std::to_string(need) + " bytes of scratch for this batch; "
                           "the fixed scratch holds " + std::to_string(kScratchBytes));
+  hipStream_t s = (hipStream_t)hip_stream;
+  MMCHK(not_capturing(s));
   unsigned char* ptr = nullptr;
   MMCHK(scratch_address(&ptr));
-  hipStream_t s = (hipStream_t)hip_stream;
   return p->e.prec == MM_F32
              ? sd_impl<float>(p, q, batch, (float*)m, n_iter, tau0, tau_min, tau_max, tau_out, 0.0, nullptr, nullptr, s,
                               ptr)
@@ -2470,6 +2479,7 @@ mm_status mm_sd_relax(mm_plan* p, const mm_params* q, int32_t batch, void* m, do
   if (!(tau_min > 0) || !is_fin(tau_max) || !(tau_min <= tau0) || !(tau0 <= tau_max))
     return fail(MM_E_ARG, "need 0 < tau_min <= tau0 <= tau_max (finite)");
   hipStream_t s = (hipStream_t)hip_stream;
+  MMCHK(not_capturing(s));
   std::vector<long long> it(batch, 0);
   std::vector<double> dm(batch, 0.0);
   const double stop = dmdt_rad_s(stopping_dmdt);
@@ -2493,6 +2503,7 @@ mm_status mm_rk45_relax(mm_plan* p, const mm_params* q, int32_t batch, void* m, 
   if (!(stopping_dmdt > 0) || !is_fin(stopping_dmdt)) return fail(MM_E_ARG, "stopping_dmdt must be finite and > 0");
   if (max_steps < 1) return fail(MM_E_ARG, "max_steps must be >= 1");
   hipStream_t s = (hipStream_t)hip_stream;
+  MMCHK(not_capturing(s));
   const double stop = dmdt_rad_s(stopping_dmdt);
   mm_status r = p->e.prec == MM_F32
                     ? plan_rk45<float>(p, q, batch, m, st, HUGE_VAL, max_steps, nullptr, 0, false, s, nullptr, stop)
@@ -2509,6 +2520,7 @@ mm_status mm_heun_run(mm_plan* p, const mm_params* q, int32_t batch, void* m, do
   if (!(h > 0) || !is_fin(h)) return fail(MM_E_ARG, "h must be finite and > 0");
   if (n_steps < 0) return fail(MM_E_ARG, "n_steps must be >= 0");
   hipStream_t s = (hipStream_t)hip_stream;
+  MMCHK(not_capturing(s));
   return p->e.prec == MM_F32 ? heun_impl<float>(p, q, batch, (float*)m, h, n_steps, s)
                              : heun_impl<double>(p, q, batch, (double*)m, h, n_steps, s);
 }
@@ -2520,6 +2532,7 @@ mm_status mm_profile_step(mm_plan* p, const mm_params* q, int32_t batch, void* m
   if (!m || !st || !us_out || !n_out || !fused_out) return fail(MM_E_ARG, "null argument");
   if (reps < 1) return fail(MM_E_ARG, "reps must be >= 1");
   hipStream_t s = (hipStream_t)hip_stream;
+  MMCHK(not_capturing(s));
   std::vector<mm_rk45_state> copy(st, st + batch);  // the caller's states are not advanced
   // ... nor its m: the attempts timed in order run on a copy
   const size_t bytes = p->e.rsz * 3 * (size_t)p->e.groups[0].g.N * batch;
@@ -2556,6 +2569,7 @@ mm_status mm_profile_passes(mm_plan* p, const mm_params* q, int32_t batch, const
   if (!m || !work || !us_out || !n_pass) return fail(MM_E_ARG, "null argument");
   if (reps < 1) return fail(MM_E_ARG, "reps must be >= 1");
   hipStream_t s = (hipStream_t)hip_stream;
+  MMCHK(not_capturing(s));
   mm_status st = p->e.prec == MM_F32 ? profile_impl<float>(p, q, batch, m, work, reps, us_out, s, seq_out)
                                      : profile_impl<double>(p, q, batch, m, work, reps, us_out, s, seq_out);
   *n_pass = pass_count(p->e);
@@ -2576,6 +2590,7 @@ mm_status mm_plan_autotune(mm_plan* p, const mm_params* q, int32_t batch, const 
   if (!m || !work) return fail(MM_E_ARG, "null array");
   if (reps < 1) return fail(MM_E_ARG, "reps must be >= 1");
   hipStream_t s = (hipStream_t)hip_stream;
+  MMCHK(not_capturing(s));
   MMCHK(p->e.prec == MM_F32 ? autotune_impl<float>(p, q, batch, m, work, reps, s)
                             : autotune_impl<double>(p, q, batch, m, work, reps, s));
   if (shape_out) shapes_of(p, shape_out);
@@ -2588,6 +2603,7 @@ mm_status mm_plan_tune_padding(mm_plan* p, const mm_params* q, int32_t batch, co
   if (!m || !work) return fail(MM_E_ARG, "null pointer");
   if (reps < 1) return fail(MM_E_ARG, "reps must be >= 1");
   hipStream_t s = (hipStream_t)hip_stream;
+  MMCHK(not_capturing(s));
   MMCHK(p->e.prec == MM_F32 ? tune_padding_impl<float>(p, q, batch, m, work, reps, s)
                             : tune_padding_impl<double>(p, q, batch, m, work, reps, s));
   if (padded_out) {
@@ -2650,6 +2666,7 @@ mm_status mm_neb_run(mm_plan* p, const mm_params* q, void* images, int32_t n_img
   if (!images) return fail(MM_E_ARG, "images is null");
   if (!is_fin(k_spring) || !is_fin(h) || h <= 0 || n_iter < 0) return fail(MM_E_ARG, "invalid k_spring, h or n_iter");
   hipStream_t s = (hipStream_t)hip_stream;
+  MMCHK(not_capturing(s));
   return p->e.prec == MM_F32 ? neb_impl<float>(p, q, images, n_img, k_spring, h, n_iter, E_out, s)
                              : neb_impl<double>(p, q, images, n_img, k_spring, h, n_iter, E_out, s);
 }
@@ -2692,6 +2709,7 @@ mm_status mm_batch_run(mm_batch* bt, mm_instance* inst, int32_t n_inst, int64_t 
     MMCHK(check_params(bt->e, &inst[i].p, 1));
   }
   hipStream_t s = (hipStream_t)hip_stream;
+  MMCHK(not_capturing(s));
   return bt->e.prec == MM_F32 ? batch_run<float>(bt, inst, n_inst, max_steps, s)
                               : batch_run<double>(bt, inst, n_inst, max_steps, s);
 }
