@@ -126,3 +126,42 @@ int main() {
             assert own, (prec, nx, ny, nz, n, Lx)
     sweep = [line[1:] for line in lines if line[0] == "sweep"]
     assert len(sweep) == 48 and all(takes == "1" for _, _, takes in sweep)
+
+
+def test_forced_shapes_of_the_dispatch_tests_are_accepted(tmp_path):
+    """The launch shapes that the GPU dispatch tests force are valid ones, so that
+    none of them falls back to the default shape or is left out; shapes past the
+    threads, the LDS or the rows are refused."""
+    lines = _run(tmp_path, r"""
+bool ok(mm_precision prec, int nx, int ny, int nz, int ty, int nt, bool pot) {
+  Group G = group(nx, ny, nz, pot);
+  if (choose_tuning(G, prec, csz_of(prec), pot) != MM_OK) return false;
+  Tuning t = G.tu;
+  if (pot) {
+    t.ty_f = 1;
+    t.tpc_f = t.nt_f;
+  }
+  t.ty_x = ty;
+  t.nt_i = nt;
+  t.tpc_x = nt / (3 * ty);
+  if (!tuning_ok(G, t, prec, csz_of(prec))) return false;
+  G.tu = t;
+  return !pot || (prec == MM_F32 ? pot_fits<float>(G) : pot_fits<double>(G));
+}
+int main() {
+  using S = std::array<int, 3>;
+  for (int nx : {24, 81, 100, 128, 162, 200})
+    for (S s : {S{1, 64}, S{2, 128}, S{4, 256}}) printf("taken %d\n", ok(MM_F64, nx, 6, 1, s[0], s[1], false));
+  for (mm_precision prec : {MM_F32, MM_F64}) {
+    for (S s : {S{128, 1}, S{127, 4}, S{256, 2}, S{512, 4}, S{512, 1}, S{509, 2}, S{1024, 2}, S{256, 8}, S{509, 4}, S{512, 2}})
+      printf("taken %d\n", ok(prec, s[0], 9, 2, s[1], 512, true));
+    printf("refused %d\n", ok(prec, 128, 6, 1, 8, 256, false));   // more rows than the mesh has
+    printf("refused %d\n", ok(prec, 128, 6, 1, 3, 256, false));   // not a power of two
+    printf("refused %d\n", ok(prec, 128, 6, 1, 4, 64, false));    // too few threads a column
+    printf("refused %d\n", ok(prec, 128, 6, 1, 1, 1024, false));  // too many threads
+    printf("refused %d\n", ok(prec, 1024, 9, 2, 4, 512, true));   // too few threads a column
+  }
+}
+""")
+    assert [v for k, v in lines if k == "taken"] == ["1"] * 38
+    assert [v for k, v in lines if k == "refused"] == ["0"] * 10
