@@ -371,3 +371,28 @@ def test_mixed_batch_has_the_bits_of_each_mesh_alone(mm, prec):
     for i in (0, 1, 2, 45, 46, 47):
         plans[which[i]].rk45_run(gp, m0[i], state(), t_end=3e-14)
         assert torch.equal(m0[i], md[i]), i
+
+
+def test_long_runs_follow_the_material_form_fp64(mm):
+    """Two runs of 99 steps (graphs of eight attempts) on one plan and one array, the
+    first with cell material and torques, the second uniform, and the other way
+    round: the second has the bits of a fresh plan's."""
+    mesh = (32, 24, 3, 3e-9, 2.5e-9, 2e-9)
+    general = F.ALL_TERMS | mm.CELLS | mm.STT_SOT
+    cells = lambda v: np.full(mesh[2::-1], v)
+
+    def plan():
+        p = mm.Plan(mesh, "f64", terms=general)
+        p.set_cells(0, cells(6e5), cells(1.3e-11), cells(1e-3))
+        return p
+
+    run = lambda p, q, m: p.rk45_run(q, m, mm.new_states(1, h=2e-15, h_max=2e-15), t_end=99 * 2e-15)
+    m0 = to_dev(_m(mesh, 7), torch.float64)
+    qs = [mm.make_params(terms=general, a_J=5e7, p=(0, 1, 0), **PAR), mm.make_params(terms=F.ALL_TERMS, **PAR)]
+    for first, second in (qs, qs[::-1]):
+        p, m, ref = plan(), m0.clone(), m0.clone()
+        run(p, first, m)
+        m.copy_(m0)
+        run(p, second, m)
+        run(plan(), second, ref)
+        assert torch.equal(m, ref)
