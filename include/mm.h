@@ -27,7 +27,11 @@
  *   call; on MM_E_ARG nothing is launched.  mm_last_error() gives a
  *   thread-local message for the last failure.  On an integration error the
  *   magnetisation holds the last accepted state.
- * - Plans are not thread safe; use one plan per host thread.
+ * - Plans are not thread safe; use one plan per host thread.  A run of 64
+ *   attempts (NEB: iterations) or more records a HIP graph; the HIP runtime ends
+ *   the recording when another thread synchronises the device or uses the
+ *   default stream in that millisecond: the run returns MM_E_HIP, and the plan
+ *   is to be destroyed.
  */
 #ifndef MM_H
 #define MM_H
@@ -227,7 +231,8 @@ mm_status mm_rk45_step(mm_plan* plan, const mm_params* params, int32_t batch,
 /* Integrate every instance to t_end (or, with replay_h, take exactly the
  * n_replay accepted steps replay_h[0..n_replay) of host memory, shared by all
  * instances).  max_steps bounds the attempts per instance.  Steps run under a
- * device-side controller and a captured HIP graph; the host only polls.
+ * device-side controller; the host submits the attempts that the step sizes
+ * ask for (in captured HIP graphs of eight in long runs) and polls.
  * Synchronises.  Returns the first non-OK instance status. */
 mm_status mm_rk45_run(mm_plan* plan, const mm_params* params, int32_t batch,
                       void* m, mm_rk45_state* st, double t_end, int64_t max_steps,
@@ -240,8 +245,8 @@ mm_status mm_rk45_run(mm_plan* plan, const mm_params* params, int32_t batch,
  * the section "Performance" (N x N x 1 films, demagnetisation + exchange +
  * Zeeman); the projection as in section "LLG equation".  Uses the plan's
  * stage buffers: a later mm_rk45_* call on the plan recomputes its first
- * slope, whatever fsal_valid says.  Asynchronous on hip_stream apart from the
- * upload of the step tables. */
+ * slope, whatever fsal_valid says.  Asynchronous on hip_stream (tables of more
+ * than 17 KB, those of large batches, are copied and waited for). */
 mm_status mm_heun_run(mm_plan* plan, const mm_params* params, int32_t batch, void* m, double h,
                       int64_t n_steps, void* hip_stream);
 
@@ -319,9 +324,10 @@ mm_status mm_neb_run(mm_plan* plan, const mm_params* params, void* images, int32
 /* Batched integration of instances of different meshes (parameter sweeps).
  * A batch is created for up to 16 distinct meshes; each run takes any number
  * of instances, each naming its mesh, and advances all of them together:
- * every kernel pass is one launch over all meshes' instances, each instance
- * has its own parameters, adaptive step size, controller and t_end, and the
- * step sequence is a captured HIP graph (finished instances idle).  This is
+ * every kernel pass is one launch over the instances of all meshes (one more
+ * each for meshes whose transform lengths take other kernels), each instance
+ * has its own parameters, adaptive step size, controller and t_end (finished
+ * instances idle).  This is
  * the paper's parameter sweep (section "Design", sim_with with _s suffixes,
  * run there one instance after the other) batched on one GPU. */
 typedef struct mm_batch mm_batch;

@@ -539,9 +539,6 @@ __device__ __forceinline__ void fft_mix(Cx<T>* lds, const Cx<T>* tw, int cs, int
   Cx<T>* col = lds + (active ? c : 0) * cs;
   fft_mix_from<T, L, INV, GIN, GOUT, TWL, HIN, HOUT, CHK, 0, 1>(col, c, lane, active, tw, ld, st, hook);
 }
-// Whether the plan of L leaves the upper half of its input unread
-constexpr bool mix_hin(int L) { return sr_plan(L).rad[0] % 2 == 0; }
-
 // Loads / stores that are never called (LDS input or output)
 template <typename T>
 struct NoLoad {

@@ -831,8 +831,9 @@ __global__ void __launch_bounds__(512) k_yinv_s(Launch<T> L) {
 // The y passes of groups with a compiled 3-smooth Py and any ny, each group by
 // its own length (3-D tiles inside one kx block).  M > 0: the launch's 3-D
 // groups take the fused y and z passes with Pz = 2 M.  The run-time engine holds
-// every radix with a predicate a butterfly: 160 registers in FP32, three waves a
-// SIMD, and three times the time a point of these.
+// every radix with a predicate a butterfly: 156 registers in FP32 (177 with
+// radix 16), three waves a SIMD, for 34 to 42 here (88 with M = 4), and three times
+// the time a point of these.
 // SL > 0: all have Py = SL (a kernel of its own is 2 to 4% faster where a launch is
 // one short chain: no switch to fetch).
 template <typename T, int M, int SL>
@@ -2451,10 +2452,11 @@ void inv_x_launch_len(int mode, int len, const Launch<T>& L, long long total, in
 }
 
 // The inverse-x pass compiled for the lengths of the list and 1024, each group by
-// its own; inv_x_any() says where it applies.  inv_x_launch()'s kernels hold the
-// run-time engine and take 121 registers whatever their epilogue; these take 83
-// with one cell a thread (144 there; 103 for 166 with a stage epilogue) and 60 to
-// 97 with two (122), four to eight waves a SIMD instead of three or four.
+// its own; inv_x_any() says where it applies.  FP32 registers, and those of
+// inv_x_launch()'s kernels, which hold the run-time engine: one cell a thread 74
+// to 76 (137, 138), 95 with a stage epilogue (159); two cells 60 to 96 (115, 116);
+// four 77 to 111 (116, 117): four to eight waves a SIMD for three or four.  The
+// stage epilogue of four cells gains nothing, 127 for 126: its loads take them.
 template <typename T, bool CELLS, int CPT>
 void inv_x_launch_any(int mode, bool fuse, const Launch<T>& L, long long total, int nt, size_t lds, hipStream_t s) {
   inv_x_launch_c<T, true, CPT, CELLS, -1>(mode, fuse, L, total, nt, lds, s);

@@ -143,6 +143,9 @@ __host__ __device__ constexpr int sr_psh(int L) {
   return 3;
 }
 // The lengths with kernels compiled so (y columns, and x rows by Lx = Px / 2).
+// Left to the run-time transform: odd lengths (27, 81, 243, 729), whose plans have
+// no even radix for the half-length ends that inverse x relies on, and 18 and 486,
+// which have not been measured.
 #define MMX_SR_LENGTHS(X) \
   X(16) X(24) X(32) X(36) X(48) X(54) X(64) X(72) X(96) X(108) X(128) X(144) X(162) X(192) X(216) X(256) X(288) \
   X(324) X(384) X(432) X(512) X(576) X(648) X(768) X(864) X(972)
@@ -155,7 +158,7 @@ __host__ __device__ constexpr bool sr_compiled(int L) {
 // Longer y columns compiled the same way, each length a kernel of its own (their
 // 16 entries a thread would cost the kernels that hold the lengths above their
 // registers): y of 900x900x1 93 -> 35 us (FP64 131 -> 76), forward and inverse y of
-// 600x600x8 178 -> 48 and 126 -> 54 us, with 42 to 62 registers in FP32, 74 to 114 in
+// 600x600x8 178 -> 48 and 126 -> 54 us, with 52 to 62 registers in FP32, 82 to 114 in
 // FP64.  1944 points: films only (a 3-D tile of four columns does not fit the
 // run-time transform's threads, and such meshes are refused).
 #define MMX_SR_LONG(X) X(1152) X(1296) X(1458) X(1536) X(1728) X(1944)

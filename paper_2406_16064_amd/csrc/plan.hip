@@ -491,11 +491,11 @@ mm_status choose_tuning(Group& G, mm_precision prec, size_t csz, bool pot, long 
     while (!pot && launch_rows > 0 && sr_compiled(g.Lx) && g.Lx <= 256 && ty > 1 && 3 * ty * sr_tpc(g.Lx) > 512)
       ty /= 2;
     t.ty_x = ty;
-    // Threads.  One cell a thread is the shortest chain but takes 145-166
-    // registers with the run-time transform, 83 in FP32 with compiled rows (three
+    // Threads.  One cell a thread is the shortest chain but takes 137-159
+    // registers with the run-time transform, 74-99 in FP32 with compiled rows (three
     // waves a SIMD of the former, and one workgroup of 512 threads a CU):
     // kept while the launch's waves all run at once, 12 a CU.  Beyond that two
-    // or four cells a thread (122-126 registers) in workgroups of 256 threads,
+    // or four cells a thread (115-127 registers) in workgroups of 256 threads,
     // 512 where a tile has more than 1024 cells (256x256x8 stage kernel 41.2 ->
     // 22.6, 512x512x4 38.4 -> 36.1, 32 films of 128x128 29 -> 14; 512x512x16
     // FP64 346 -> 288).  With at most two workgroups a CU the transform's
@@ -933,8 +933,8 @@ mm_status put(Engine& E, int region, void* dst, const void* src, size_t bytes, h
 
 // The compute calls keep tables on the device between calls and are not
 // recorded into a caller's graph: each refuses a stream that is being captured
-// before it touches the stream or the plan, so that the caller's graph holds no
-// copy to or from buffers of a call that did not take place.
+// before it touches the stream or the plan, so that a call that does not take
+// place spoils neither the caller's capture nor the plan.
 mm_status not_capturing(hipStream_t s) {
   hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
   HIPCHK(hipStreamIsCapturing(s, &st));
@@ -1173,12 +1173,11 @@ mm_status profile_impl(mm_plan* p, const mm_params* q, int batch, const void* m,
 }
 
 // Energies from the partial sums `partial` (device, [batch][blocks][5]) of one
-// MODE_ENERGY evaluation: reduce into e5 (device, [batch][5]), copy to the
-// plan's pinned host buffer, scale to joules.
-mm_status energy_finish(Engine& E, const mm_params* q, int batch, const double* partial, double* e5,
-                        double* E_out, hipStream_t s) {
+// MODE_ENERGY evaluation: reduced straight into the plan's pinned host buffer,
+// scaled to joules.
+mm_status energy_finish(Engine& E, const mm_params* q, int batch, const double* partial, double* E_out,
+                        hipStream_t s) {
   const Group& G = E.groups[0];
-  // the sums go straight to the pinned host buffer
   HIPCHK(launch_energy_reduce(partial, batch, eval_blocks_per_inst(G.g, G.tu), E.he5, s));
   HIPCHK(hipStreamSynchronize(s));
   for (int b = 0; b < batch; ++b) {
@@ -1192,7 +1191,7 @@ template <typename T>
 mm_status energy_impl(mm_plan* p, const mm_params* q, int batch, const void* m, double* E_out, hipStream_t s) {
   Engine& E = p->e;
   MMCHK(single_eval<T>(p, batch, q, m, nullptr, MODE_ENERGY, E.partial, s));
-  return energy_finish(E, q, batch, E.partial, E.e5, E_out, s);
+  return energy_finish(E, q, batch, E.partial, E_out, s);
 }
 
 // --- Dormand-Prince over every group -----------------------------------------
@@ -1358,7 +1357,7 @@ mm_status heun_impl(mm_plan* p, const mm_params* q, int batch, T* m, double h, l
 // (rad/s).  Synchronises.
 constexpr long long kPollSd = 16;
 
-// Bytes of per-call scratch of sd_impl for `batch` instances of G: the block
+// Bytes of scratch of sd_impl for `batch` instances of G: the block
 // partial sums (4 doubles per block), padded to 256 bytes, then the step sizes.
 size_t sd_part_bytes(const Group& G, int batch) {
   const size_t bpi = (size_t)((G.g.N + 255) / 256);
@@ -2235,9 +2234,9 @@ mm_status set_cells_impl(mm_plan* p, int inst, const double* Ms, const double* A
 }  // namespace
 
 // --- allocation-free steepest descent ---------------------------------------
-// mm_sd_run allocates its per-block partial sums and step sizes on every call;
-// mm_sd_run_noalloc takes them from `scratch`, a fixed array in device memory
-// of kScratchBytes.  Each GPU the library runs on holds its own copy until the
+// mm_sd_run keeps its per-block partial sums and step sizes in the plan and
+// allocates them for the first call and for larger batches; mm_sd_run_noalloc
+// takes them from `scratch`, a fixed array in device memory of kScratchBytes.  Each GPU the library runs on holds its own copy until the
 // process ends.  In host code the array's name is not a device address: the
 // address comes from hipGetSymbolAddress, once per device, with that device
 // current, and only that address is passed to kernels and copies.

@@ -232,9 +232,10 @@ __global__ void __launch_bounds__(512) k_pot_yinv_s(HotPlan<T> hp, int CB) {
 // its eight corners from LDS.
 // P2: only the compiled transforms of 128 to 1024 points (Lx / 16 threads a
 // column), without the run-time one, whose registers the other loops would pay
-// for: 60 to 93 in FP32 instead of 114, three workgroups of 512 threads a CU
-// (512x512x16 dm/dt, two rows: 76 -> 67 us, 2.2 TB/s of its 150 MB; LDS traffic
-// and the divisions of the tile's indices bound it).
+// for: 60 to 93 in FP32 with one and two cells a thread instead of 114, three
+// workgroups of 512 threads a CU (512x512x16 dm/dt, two rows: 76 -> 67 us, 2.2 TB/s
+// of its 150 MB; LDS traffic and the divisions of the tile's indices bound it).
+// Four cells take 80 (stage epilogue 119).
 // ---------------------------------------------------------------------------
 template <typename T, int MODE, int CPT, bool P2>
 __global__ void __launch_bounds__(512) k_pot_x(HotPlan<T> hp, const Epi<T>* __restrict__ epis, int tpc, T gx, T gy,
