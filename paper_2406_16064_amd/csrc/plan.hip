@@ -4,7 +4,8 @@
 // padded grid, radix plans, twiddles, launch shapes, tensor spectrum, spectral
 // work buffers) plus the per-instance parameter and controller arrays.  A plan
 // is an engine with one group; a batch has one group per distinct mesh, and
-// every pass of an evaluation is a single launch over all groups.  On top:
+// a pass of an evaluation is one launch over the groups whose transforms take
+// the same kernel.  On top:
 // validation, effective field / LL / energy calls, device-controlled
 // Dormand-Prince runs with HIP-graph replay, and the NEB driver.
 #include <hip/hip_runtime.h>
